@@ -277,4 +277,16 @@ __device__ __forceinline__ int group_member(const MacroGroup &g, int i)
         }                         \
     } while (0)
 
+// Instantiate for a flag known at launch.
+#define DVM_FLAG(cond, NAME, ...)          \
+    do {                                   \
+        if (cond) {                        \
+            constexpr bool NAME = true;    \
+            __VA_ARGS__;                   \
+        } else {                           \
+            constexpr bool NAME = false;   \
+            __VA_ARGS__;                   \
+        }                                  \
+    } while (0)
+
 }  // namespace dvm

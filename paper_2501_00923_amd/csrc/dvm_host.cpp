@@ -374,6 +374,13 @@ P *at(const dvm_solver &s, size_t off)
     return off == (size_t)-1 ? nullptr : reinterpret_cast<P *>(s.base + off);
 }
 
+// bytes of the rows one sweep touches: f or phi read and written, the
+// adjoint's frozen f, the second-order scheme's held correction
+size_t sweep_bytes(const dvm_solver &s, int adjoint)
+{
+    return 2 * (size_t)s.nc * s.nv * elt_bytes(s) * (2 + adjoint + (s.order == 2 ? 1 : 0));
+}
+
 void fill_dev(dvm_solver &s)
 {
     dvm::DevSolve &d = s.dev;
@@ -391,6 +398,8 @@ void fill_dev(dvm_solver &s)
     d.order = s.order;
     d.limiter = s.limiter;
     d.equil = s.equil;
+    d.lm = dvm::lane_map(s.n1, s.n2, s.mixed);
+    for (int adj = 0; adj < 2; adj++) d.nt[adj] = sweep_bytes(s, adj) > dvm::kMallBytes;
     d.nbr = at<int32_t>(s, s.off.nbr);
     d.patch = at<int32_t>(s, s.off.patch);
     d.cell_of = at<int32_t>(s, s.off.cell_of);
@@ -508,7 +517,7 @@ int sweeps(dvm_solver &s, int adjoint, int n)
             s.since[adjoint] = 0;
         }
         if (adjoint) {
-            HIP_OK(dvm::launch_adjoint_sweep(s.dev, s.ppar, s.stream));
+            HIP_OK(dvm::launch_adjoint_sweep(s.dev, s.ppar, i == n - 1, s.stream));   // residuals: of the last sweep
             s.ppar ^= 1;
             if (s.acc_every > 0 && ++s.acc_acount % s.acc_every == 0)
                 HIP_OK(dvm::launch_macro_adjoint_predict(s.dev, s.ppar, s.acc_inner, s.stream));
@@ -619,8 +628,8 @@ struct dvm_batch {
     int static_dev = -1;                 // >= 0: the allocation-free batch of this device
     char *work = nullptr;
     hipStream_t stream = nullptr;
-    int nblocks = 0, mixed = 0;
-    int nb_group[4] = {0, 0, 0, 0};      // blocks of group 2 * phase + (order == 2), in that order
+    int nblocks = 0;
+    dvm::BatchLaunch group[4];           // group 2 * phase + (order == 2), in that order
     int step = 0;
     size_t off_tab = 0, off_par = 0, off_phase = 0, off_bs = 0, off_bc = 0, off_out = 0;
 };
@@ -1280,6 +1289,27 @@ static int batch_check(dvm_solver *const *solvers, int n, int *mixed_out, int64_
     return DVM_OK;
 }
 
+// Launch parameters of the four groups.
+static void batch_groups(dvm_solver *const *solvers, int n, int mixed, const int64_t per_group[4],
+                         dvm::BatchLaunch group[4])
+{
+    size_t bytes[4] = {0, 0, 0, 0};
+    for (int g = 0; g < 4; g++) {
+        group[g] = dvm::BatchLaunch();
+        group[g].blocks = (int)(8 * per_group[g]);
+        group[g].mixed = mixed;
+        group[g].adjoint = g >> 1;
+        group[g].so = g & 1;
+    }
+    for (int i = 0; i < n; i++) {
+        const dvm_solver *s = solvers[i];
+        const int g = batch_group(s);
+        bytes[g] += sweep_bytes(*s, g >> 1);
+        group[g].lds = std::max(group[g].lds, g >> 1 ? dvm::adjoint_lds(s->dev) : dvm::primal_lds(s->dev));
+    }
+    for (int g = 0; g < 4; g++) group[g].nt = bytes[g] > dvm::kMallBytes;
+}
+
 int dvm_batch_create(dvm_solver *const *solvers, int n, void *work_dev, size_t work_bytes, void *hip_stream,
                      dvm_batch **out)
 {
@@ -1304,8 +1334,7 @@ int dvm_batch_create(dvm_solver *const *solvers, int n, void *work_dev, size_t w
         b->work = static_cast<char *>(work_dev);
         b->stream = static_cast<hipStream_t>(hip_stream);
         b->nblocks = (int)nblocks;
-        for (int g = 0; g < 4; g++) b->nb_group[g] = (int)(8 * per_group[g]);
-        b->mixed = mixed;
+        batch_groups(solvers, n, mixed, per_group, b->group);
         std::vector<dvm::DevSolve> tab(n);
         std::vector<int32_t> par(n), phase(n);
         for (int i = 0; i < n; i++) {
@@ -1414,8 +1443,7 @@ int dvm_batch_create_static(dvm_solver *const *solvers, int n, void *hip_stream,
     b->work = w;
     b->stream = st;
     b->nblocks = (int)nblocks;
-    for (int g = 0; g < 4; g++) b->nb_group[g] = nbg[g];
-    b->mixed = mixed;
+    batch_groups(solvers, n, mixed, per_group, b->group);
     b->step = 0;
     for (int i = 0; i < n; i++) solvers[i]->in_batch = 1;
     g_static_live[dev] = true;
@@ -1481,9 +1509,9 @@ int dvm_batch_run(dvm_batch *b, int iters)
         }
         int off = 0;
         for (int g = 0; g < 4; g++) {
-            HIP_OK(dvm::launch_batch(tab, bs + off, bc + off, par, b->step + it, b->nb_group[g], b->mixed, g >> 1,
-                                     g & 1, b->stream));
-            off += b->nb_group[g];
+            HIP_OK(dvm::launch_batch(tab, bs + off, bc + off, par, b->step + it, b->group[g], it == iters - 1,
+                                     b->stream));
+            off += b->group[g].blocks;
         }
         // members with the macroscopic prediction, on their own cadence (the
         // state after this sweep sits in buffer par ^ ((it + 1) & 1)): each

@@ -24,6 +24,82 @@ constexpr int kEqState = 20;       // doubles per cell of mstate: P' (4), dP'/dW
 constexpr int kPatchI = 2, kPatchJ = 2, kPatchCells = kPatchI * kPatchJ;
 constexpr int kTileI = 32, kTileJ = 16;
 
+// How a wave's lanes walk one cell's velocities (Walk in dvm_kernels.hip).
+// In units of V adjacent velocities (V = 2 in FP32 with an even n1), a grid
+// row holds na units.  Walk i of `isteps` gives lane l the unit
+// k = i ks + l, column m + i as and row r of r = k / width, m = k % width,
+// and then every `brow`-th row below it: tq (+ 1 for i < tr) steps.
+struct LaneMap {
+    int width, ks, as, rows; // lanes with r >= rows run along outside the grid
+    float inv_width;
+    int isteps, tq, tr, brow;
+    int n1p, n2p;            // LDS table sizes: columns and rows that some lane visits
+};
+
+// Two shapes of walk.  "phase": the units in storage order, 64 a step; the
+// column of a lane repeats after isteps = na / gcd(64, na) steps, so the steps
+// are taken isteps apart.  "block": lane rows of la units, 64 / la of them.
+// The one with the fewer steps, a walk's own set-up counted a sixteenth of
+// a step (an eighth in FP32); a block walk with several pieces per grid row
+// touches cache lines twice and counts half more.  Measured on 128x64 cells,
+// primal / adjoint us, phase against block: 59x52 velocities in FP64 187 / 267
+// against 200 / 287 (48 steps against 52), 43x39 109 / 156 against 139 / 201
+// (27 against 39), 10x18 14.5 / 20.9 against 13.6 / 20.4 (3 and 3), FP32
+// 62x22 42 / 68 against 35 / 65 (11 and 11).
+inline LaneMap lane_map(int n1, int n2, int mixed)
+{
+    const int V = mixed && n1 % 2 == 0 ? 2 : 1, na = n1 / V;
+    int g = kWave, h = na;                      // gcd(64, na)
+    while (h) {
+        const int t = g % h;
+        g = h;
+        h = t;
+    }
+    LaneMap best{};
+    const int total = (na * n2 + kWave - 1) / kWave;
+    best.width = na;
+    best.ks = kWave;
+    best.as = 0;
+    best.isteps = na / g < total ? na / g : total;
+    best.brow = kWave / g;
+    best.rows = 1 << 30;
+    best.tq = total / best.isteps;
+    best.tr = total % best.isteps;
+    best.n1p = n1;
+    best.n2p = (total * kWave - 1) / na + 1;
+    const int setup = mixed ? 2 : 1;
+    int cost = 16 * total + setup * best.isteps;
+    for (int la = na < kWave ? na : kWave; la >= 1; la--) {
+        const int isteps = (na + la - 1) / la, nb = kWave / la, bsteps = (n2 + nb - 1) / nb;
+        if (isteps > 1 && la * V * (mixed ? 8 : 16) < 128) break;       // less than a cache line a piece
+        const int c = (isteps > 1 ? 24 : 16) * isteps * bsteps + setup * isteps;
+        if (c >= cost) continue;
+        cost = c;
+        best.width = la;
+        best.ks = 0;
+        best.as = la;
+        best.rows = nb;
+        best.isteps = isteps;
+        best.tq = bsteps;
+        best.tr = 0;
+        best.brow = nb;
+        best.n1p = (isteps * la + 1) * V;       // the last V: lanes outside the rows
+        best.n2p = bsteps * nb;
+    }
+    best.inv_width = 1.0f / best.width;
+    return best;
+}
+
+// A sweep whose rows (those of one cell-velocity array times the arrays it
+// touches) fit the 256 MiB memory-side cache (MALL) uses plain loads and
+// stores, a larger one non-temporal ones: copies of up to 128 MB per buffer
+// run at 8.2 TB/s with plain and 4.7 TB/s with non-temporal stores (which
+// bypass the MALL), larger ones at 5.1 TB/s either way, and there the sweeps
+// keep neighbour rows longer in L2 with non-temporal ones (FP64 primal and
+// adjoint of the 256x128 C-grid with 2304 velocities 496 and 733 against 507
+// and 762 us; of 128x64 cells with 1024 velocities 86 against 63 us).
+constexpr size_t kMallBytes = size_t(256) << 20;
+
 // Everything a kernel needs about one solve, passed by value (single solve)
 // or read from a device table (batched).  Pointers are device pointers into
 // the solver's workspace.  Storage type of f / phi / fd / gM is float in
@@ -38,6 +114,8 @@ struct DevSolve {
     int order;               // spatial order of the scheme: 1, or 2 (reconstructed face values)
     int equil;               // equilibrium: 0 pointwise Maxwellian, 1 discrete-conservative
     int limiter;             // order 2: 0 none, 1 Venkatakrishnan
+    int nt[2];               // primal, adjoint sweeps with non-temporal rows
+    LaneMap lm;
     // mesh
     const int32_t *nbr;      // [nc][4] (device cell numbering)
     const int32_t *patch;    // [np + 1] first cell of each patch; patch p = cells [patch[p], patch[p+1])
@@ -92,14 +170,28 @@ struct DevSolve {
     double *mx[2];           // [nc][4] red-black iterates
 };
 
-// launches (all on `st`); par = index of the current f / phi buffer
+// dynamic LDS of the patch kernels (layouts in dvm_kernels.hip); a thread of
+// the adjoint's parks kWalkSums sums there between walks
+constexpr int kWalkSums = 6;
+inline unsigned factor_lds(const LaneMap &m) { return 32u * m.n2p + 16u * m.n1p; }
+inline unsigned primal_lds(const DevSolve &d)
+{
+    return factor_lds(d.lm) + kPatchCells * (d.lm.n1p + d.lm.n2p) * (d.mixed ? 4u : 8u);
+}
+inline unsigned adjoint_lds(const DevSolve &d)
+{
+    return kWalkSums * 8u * kPatchCells * kWave + factor_lds(d.lm) + kPatchCells * (d.lm.n2p * (32u + (d.mixed ? 4u : 8u)) + d.lm.n1p * 8u);
+}
+
+// launches (all on `st`); par = index of the current f / phi buffer; res:
+// the adjoint sweep also leaves its residual partials
 hipError_t launch_primal_init(const DevSolve &d, hipStream_t st);
 hipError_t launch_primal_sweep(const DevSolve &d, int par, hipStream_t st);
 hipError_t launch_moments(const DevSolve &d, int par, hipStream_t st);
 hipError_t launch_residual(const DevSolve &d, int adjoint, hipStream_t st);
 hipError_t launch_objective(const DevSolve &d, int par, hipStream_t st);
 hipError_t launch_adjoint_init(const DevSolve &d, int fpar, hipStream_t st);
-hipError_t launch_adjoint_sweep(const DevSolve &d, int par, hipStream_t st);
+hipError_t launch_adjoint_sweep(const DevSolve &d, int par, int res, hipStream_t st);
 // adjoint moments (What, rho_tau) and wall multipliers of phi[par] (a loaded phi)
 hipError_t launch_adjoint_moments(const DevSolve &d, int par, hipStream_t st);
 hipError_t launch_adjoint_correct_moments(const DevSolve &d, int par, const double *z, hipStream_t st);
@@ -146,8 +238,12 @@ hipError_t launch_so_objective_elem(const DevSolve &d, int par, hipStream_t st);
 // per-solve buffer parity at batch creation; step = sweeps done since batch
 // creation; adjoint selects the kernel of that phase, so the scheme (the
 // blocks of one launch are members of one phase and one scheme)
+struct BatchLaunch {
+    int blocks = 0, mixed = 0, adjoint = 0, so = 0, nt = 0;
+    unsigned lds = 0;        // the largest member's
+};
 hipError_t launch_batch(const DevSolve *tab, const int32_t *blk_solve, const int32_t *blk_patch,
-                        const int32_t *par0, int step, int nblocks, int mixed, int adjoint, int so, hipStream_t st);
+                        const int32_t *par0, int step, const BatchLaunch &g, int res, hipStream_t st);
 hipError_t launch_batch_residual(const DevSolve *tab, int n, double *out, hipStream_t st);
 
 // The allocation-free batch (dvm_batch_create_static) keeps its launch

@@ -6,19 +6,26 @@
 // Cells are numbered on the device in sweep order (see dvm_internal.h).
 //
 // Sweeps: one workgroup per patch of up to kPatchCells cells, one wave per
-// cell.  A wave walks its cell's velocities 64 at a time; at each step every
-// wave puts its own row's values into LDS, and after one barrier a face
-// whose neighbour lies in the same patch reads the neighbour's values from
-// LDS, a face to a cell outside the patch reads them from global memory
-// (L2 in the common case: the neighbouring patch ran shortly before or runs
-// alongside on the same XCD), and a boundary face reads the far-field or
-// wall table.  The loads of the next step are issued before the current
-// step's arithmetic.  The FP64 velocity moments of the new row are summed
-// in registers and reduced across the wave with shuffles in a fixed order,
-// so the next sweep finds W^{n+1} ready and f is streamed once per sweep.
-// The Maxwellian is evaluated as rho/(2 pi theta) * ex[a] * ey[b] with the
-// per-cell 1-D factors in LDS (tensor-product velocity grid), i.e. n1 + n2
-// exponentials per cell instead of n1*n2.
+// cell.  A wave walks its cell's velocities 64 or 128 at a time (Walk below)
+// and reads the neighbour rows it needs from L2 (the neighbouring patch ran
+// shortly before or runs alongside on the same XCD; a neighbour in the same
+// patch is in L1), far-field and wall rows from tables.  The FP64 velocity
+// moments of the new row are summed in registers and reduced across the wave
+// in a fixed order, so the next sweep finds W^{n+1} ready and f is streamed
+// once per sweep.  The Maxwellian is evaluated as rho/(2 pi theta) * ex[a] *
+// ey[b] with the per-cell 1-D factors in LDS (tensor-product velocity grid),
+// i.e. n1 + n2 exponentials per cell instead of n1*n2.
+//
+// What bounds them, 256x128 C-grid with 2304 velocities: memory (FP64 primal
+// 488 us, adjoint 694 us: 4.9 and 5.2 TB/s of the rows' own bytes, against
+// 5.1-5.4 for a plain copy of that size; FP32 256 and 355 us).  States that
+// fit the MALL are bound by instruction issue and, below some ten thousand
+// cells, by the latency of a patch's prologue and steps (64x32 cells with 256
+// velocities: 7.2 and 8.2 us; 9.7 and 12.8 us with a walk in storage order,
+// FP64 neighbour rows exchanged through LDS and butterflies for the sums).  A
+// software-pipelined loop (the next step's loads issued before this step's
+// arithmetic) and tighter register limits measured within 1% at large sizes
+// and up to 20% slower at small.
 
 #include <math.h>
 
@@ -29,44 +36,107 @@
 
 namespace dvm {
 
-// In FP32 a lane can take two adjacent velocities of one velocity-grid row
-// (n1 even): the pair's (f1, f2, f1', f2') is one 16-byte load or store, as
-// one velocity is in FP64.  Measured on the 256x128 C-grid with 2304
-// velocities: mixed primal sweep 325 -> 299 us.
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef unsigned u4 __attribute__((ext_vector_type(4)));
+typedef unsigned u2 __attribute__((ext_vector_type(2)));
+
+// Velocities per lane and step: two adjacent ones of a velocity-grid row in
+// FP32 with an even n1, so that a lane moves 16 bytes as in FP64.
 template <typename T>
 __device__ __forceinline__ bool pair_velocities(int n1)
 {
     return sizeof(T) == 4 && (n1 & 1) == 0;
 }
 
-// LDS of a patch sweep: the velocity tables, each cell's Maxwellian
-// factors and, for a sweep that exchanges rows (XCH), the double-buffered
-// exchange of the patch's own rows.
-template <typename T, bool XCH>
-struct PatchLds {
-    double vx[kMaxN1D], vy[kMaxN1D], wx[kMaxN1D], wy[kMaxN1D];
-    T ex[kPatchCells][kMaxN1D], ey[kPatchCells][kMaxN1D];
-    typename Vec2<T>::type xch[XCH ? 2 : 1][XCH ? kPatchCells : 1][kWave];
+// ---------------------------------------------------------------------------
+// a wave's walk over one cell's velocities
+//
+// A lane stays on one column of the velocity grid (V adjacent ones) for a
+// whole walk down its rows (LaneMap of dvm_internal.h), so every factor of
+// v1 is a per-lane constant of the inner loop, and the sums over the rows
+// carry only the v2 factors (from LDS); the v1 factors join once per walk.
+// Compared with a column that changes every step this takes the vector
+// instructions per velocity from 100 to 72 (FP64 primal), 105 to 70 (FP32
+// primal), 168 to 88 (FP64 adjoint) and 142 to 85 (FP32 adjoint).
+// Lanes outside the grid run along on padded table entries (v = 1, weight 0)
+// and buffer accesses that the row's range check drops.
+// ---------------------------------------------------------------------------
+constexpr int kOutside = 0x40000000;            // byte offset past any row (rows have at most 256 KB)
+
+struct Walk {
+    int a, b, off;           // column, first row, byte offset there
+    bool in;                 // in the grid's columns
 };
 
-// Non-temporal load of a (x, y) pair: rows read by their own cell only (the
-// frozen f of the adjoint, held corrections) so that they do not push the
-// neighbour rows other cells reuse out of L2 (FP64 adjoint sweep on the
-// 256x128 C-grid with 2304 velocities: 735 -> 727 us).
-template <typename V>
-__device__ __forceinline__ V ntload2(const V *p)
+template <typename T, int V>
+__device__ __forceinline__ Walk make_walk(const DevSolve &d, int lane, int i)
 {
-    V r;
-    r.x = __builtin_nontemporal_load(&p->x);
-    r.y = __builtin_nontemporal_load(&p->y);
-    return r;
+    Walk w;
+    const int k = i * d.lm.ks + lane;
+    const int r = (int)(((float)k + 0.5f) * d.lm.inv_width), m = k - r * d.lm.width;
+    const bool idle = r >= d.lm.rows;
+    w.a = idle ? d.lm.n1p - V : V * (m + i * d.lm.as);
+    w.b = idle ? 0 : r;
+    w.in = !idle && w.a < d.n1;
+    w.off = w.in ? (r * d.n1 + w.a) * 2 * (int)sizeof(T) : kOutside;
+    return w;
 }
 
-// Reciprocal for the FP64 update: hardware estimate and two Newton steps
-// (error about one ulp; the IEEE division costs twice the instructions).
-// FP32 keeps the IEEE division: a one-ulp reciprocal there raised the
-// mixed-precision drag error against FP64 from 1e-8 to 2e-7 relative.
+// V velocities' two components
+template <typename T, int V>
+struct Vals {
+    T x[V], y[V];
+};
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void *p, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00027000);
+}
+
+// NT: non-temporal
+template <typename T, int V, bool NT>
+__device__ __forceinline__ Vals<T, V> row_load(__amdgpu_buffer_rsrc_t r, int off)
+{
+    Vals<T, V> o;
+    if constexpr (V * sizeof(T) == 8) {
+        const u4 v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, NT ? 2 : 0);
+        if constexpr (sizeof(T) == 8) {
+            o.x[0] = __longlong_as_double(((unsigned long long)v.y << 32) | v.x);
+            o.y[0] = __longlong_as_double(((unsigned long long)v.w << 32) | v.z);
+        } else {
+            o.x[0] = __uint_as_float(v.x);
+            o.y[0] = __uint_as_float(v.y);
+            o.x[1] = __uint_as_float(v.z);
+            o.y[1] = __uint_as_float(v.w);
+        }
+    } else {
+        const u2 v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, NT ? 2 : 0);
+        o.x[0] = __uint_as_float(v.x);
+        o.y[0] = __uint_as_float(v.y);
+    }
+    return o;
+}
+
+template <typename T, int V, bool NT>
+__device__ __forceinline__ void row_store(__amdgpu_buffer_rsrc_t r, int off, const Vals<T, V> &o)
+{
+    if constexpr (V * sizeof(T) == 8) {
+        u4 v;
+        if constexpr (sizeof(T) == 8) {
+            const unsigned long long a = __double_as_longlong(o.x[0]), b = __double_as_longlong(o.y[0]);
+            v = u4{(unsigned)a, (unsigned)(a >> 32), (unsigned)b, (unsigned)(b >> 32)};
+        } else {
+            v = u4{__float_as_uint(o.x[0]), __float_as_uint(o.y[0]), __float_as_uint(o.x[1]), __float_as_uint(o.y[1])};
+        }
+        __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, NT ? 2 : 0);
+    } else {
+        __builtin_amdgcn_raw_buffer_store_b64(u2{__float_as_uint(o.x[0]), __float_as_uint(o.y[0])}, r, off, 0, NT ? 2 : 0);
+    }
+}
+
+// Reciprocal: hardware estimate and Newton steps, two in FP64 (error about
+// one ulp) and one in FP32, where it is the correctly rounded 1 / x (checked
+// for every mantissa) at a third of the division's instructions.
 __device__ __forceinline__ double recip(double x)
 {
     double r = __builtin_amdgcn_rcp(x);
@@ -75,79 +145,261 @@ __device__ __forceinline__ double recip(double x)
     e = fma(-x, r, 1.0);
     return fma(r, e, r);
 }
-__device__ __forceinline__ float recip(float x) { return 1.0f / x; }
-
-// The adjoint sweep exchanges the patch's rows through LDS in FP64 (4%
-// faster than every face reading global memory on the 256x128 C-grid with
-// 2304 velocities); in FP32 and in the primal sweep the per-step barrier
-// costs more than the L2 requests it saves.
-template <typename T>
-constexpr bool kAdjointExchange = sizeof(T) == 8;
-
-// Shared velocity tables (threads 0 .. n1+n2-1; a patch workgroup has at
-// least 4 waves, n1 + n2 <= 256) and this wave's Maxwellian factors
-// exp(-(v - u)^2 / (2 theta)) per direction.
-template <typename T, bool XCH>
-__device__ __forceinline__ void patch_tables(const DevSolve &d, PatchLds<T, XCH> &sm, int w, int lane, double u1,
-                                             double u2, double inv2th)
+__device__ __forceinline__ float recip(float x)
 {
-    const int t = threadIdx.x, n1 = d.n1, n2 = d.n2;
-    if (t < n1) {
-        sm.vx[t] = d.vx[t];
-        sm.wx[t] = d.wx[t];
-    } else if (t - n1 < n2) {
-        sm.vy[t - n1] = d.vy[t - n1];
-        sm.wy[t - n1] = d.wy[t - n1];
+    const float r = __builtin_amdgcn_rcpf(x);
+    return fmaf(r, fmaf(-x, r, 1.0f), r);
+}
+
+// c + a b: fused in FP64, rounded twice in FP32, where the stored values
+// carry the rounding: FP32 results stay those of the plain expressions to the
+// last bit, so that a derivative's FP32 noise does not depend on the kernel
+__device__ __forceinline__ double madd(double a, double b, double c) { return fma(a, b, c); }
+__device__ __forceinline__ float madd(float a, float b, float c) { return c + a * b; }
+// keeps a per-lane constant in its register (the compiler would recompute the
+// product in every step)
+__device__ __forceinline__ void keep(double &x) { asm("" : "+v"(x)); }
+__device__ __forceinline__ void keep(float &x) { asm("" : "+v"(x)); }
+// the loads above are issued before any LDS read below (table entries read
+// late do not hold registers while the loads are in flight)
+__device__ __forceinline__ void loads_first() { asm volatile("" ::: "memory"); }
+__device__ __forceinline__ double min0(double x) { return fmin(x, 0.0); }
+__device__ __forceinline__ float min0(float x) { return fminf(x, 0.0f); }
+__device__ __forceinline__ double max0(double x) { return fmax(x, 0.0); }
+__device__ __forceinline__ float max0(float x) { return fmaxf(x, 0.0f); }
+
+// v2 factors of a grid row b, shared by a workgroup's cells: v2, w, w v2, w v2^2 / 2
+struct alignas(16) RowFactor {
+    double v, w, wv, wh;
+};
+// v1 factors of a column a: v1, w
+struct alignas(16) ColFactor {
+    double v, w;
+};
+// weighted Maxwellian factors of a grid row in one cell (adjoint moments):
+// e = w Y, e c2, e c2^2
+struct alignas(16) AdjRow {
+    double e, ec, ecc, pad;
+};
+
+// the workgroup's dynamic LDS (launch bytes: sweep_lds of dvm_internal.h)
+extern __shared__ __align__(16) unsigned char sweep_smem[];
+
+// The adjoint's sums of a thread over the walks before the current one, parked
+// in LDS so that the inner loop does not hold 12 registers for them (sum k of
+// a thread is a block's stride from the next: no bank conflicts).  256x128
+// cells with 256 velocities, FP64 / FP32: 108 / 70 -> 99 / 60 us.  The primal
+// keeps its four in registers: with fewer, more waves run at once and push
+// each other's neighbour rows out of L2 (128x64 cells with 4096 velocities in
+// FP64 234 -> 244 us).
+struct WalkSums {
+    double *p;
+    __device__ __forceinline__ WalkSums() : p(reinterpret_cast<double *>(sweep_smem) + threadIdx.x) {}
+    __device__ __forceinline__ double &operator[](int k) const { return p[k * kPatchCells * kWave]; }
+};
+
+// The workgroup's shared tables from byte `at` of its LDS.
+struct Factors {
+    RowFactor *row;
+    ColFactor *col;
+    void *end;
+    __device__ __forceinline__ Factors(const DevSolve &d, int at)
+    {
+        row = reinterpret_cast<RowFactor *>(sweep_smem + at);
+        col = reinterpret_cast<ColFactor *>(row + d.lm.n2p);
+        end = col + d.lm.n1p;
     }
-    for (int i = lane; i < n1 + n2; i += kWave) {
-        if (i < n1) {
-            const double e = d.vx[i] - u1;
-            sm.ex[w][i] = (T)exp(-e * e * inv2th);
-        } else {
-            const double e = d.vy[i - n1] - u2;
-            sm.ey[w][i - n1] = (T)exp(-e * e * inv2th);
+    // padded past the grid with v = 1 and weight 0; all threads of the
+    // workgroup, no barrier
+    __device__ __forceinline__ void fill(const DevSolve &d) const
+    {
+        for (int i = threadIdx.x; i < d.lm.n2p + d.lm.n1p; i += kPatchCells * kWave) {
+            const bool first = i < d.lm.n2p;
+            const int k = first ? i : i - d.lm.n2p;
+            double v = 1.0, w = 0.0;
+            if (k < (first ? d.n2 : d.n1)) {
+                v = (first ? d.vy : d.vx)[k];
+                w = (first ? d.wy : d.wx)[k];
+            }
+            if (first) {
+                const double wv = w * v;
+                row[k] = {v, w, wv, 0.5 * (wv * v)};
+            } else {
+                col[k] = {v, w};
+            }
         }
     }
+};
+
+// ---------------------------------------------------------------------------
+// sums over the wave: lane l ends with the total of v[l / 8], by pairwise
+// exchanges that halve the number of values carried (34 vector instructions
+// for 8 values; a butterfly of each value takes 12 LDS exchanges per value).
+// The order is fixed and the same in every kernel that sums moments.
+// ---------------------------------------------------------------------------
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double x)
+{
+    const unsigned long long u = __double_as_longlong(x);
+    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, 0xf, 0xf, true);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(((unsigned long long)hi << 32) | lo);
 }
+
+template <int HALF>
+__device__ __forceinline__ double swap_add(double a, double b)
+{
+    const unsigned long long ua = __double_as_longlong(a), ub = __double_as_longlong(b);
+    u2 lo, hi;
+    if constexpr (HALF == 32) {
+        lo = __builtin_amdgcn_permlane32_swap((unsigned)ua, (unsigned)ub, false, false);
+        hi = __builtin_amdgcn_permlane32_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
+    } else {
+        lo = __builtin_amdgcn_permlane16_swap((unsigned)ua, (unsigned)ub, false, false);
+        hi = __builtin_amdgcn_permlane16_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
+    }
+    return __longlong_as_double(((unsigned long long)hi.x << 32) | lo.x) +
+           __longlong_as_double(((unsigned long long)hi.y << 32) | lo.y);
+}
+
+__device__ __forceinline__ double wave_scatter8(const double (&v)[8])
+{
+    double q[4], p[2];
+#pragma unroll
+    for (int i = 0; i < 4; i++) q[i] = swap_add<32>(v[i], v[i + 4]);
+#pragma unroll
+    for (int i = 0; i < 2; i++) p[i] = swap_add<16>(q[i], q[i + 2]);
+    const bool up = (threadIdx.x & 8) != 0;
+    double s = (up ? p[1] : p[0]) + dpp_move<0x128>(up ? p[0] : p[1]);     // lane ^ 8
+    s += dpp_move<0x141>(s);                                               // lane ^ 7
+    s += dpp_move<0x4e>(s);                                                // lane ^ 2
+    s += dpp_move<0xb1>(s);                                                // lane ^ 1
+    return s;
+}
+
+// value of a lane, the same in every lane
+__device__ __forceinline__ double lane_value(double x, int lane)
+{
+    const unsigned long long u = __double_as_longlong(x);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, lane);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), lane);
+    return __longlong_as_double(((unsigned long long)hi << 32) | lo);
+}
+
+// ---------------------------------------------------------------------------
+// FP64 moments of one cell: W (4) and the wall flux sum.  Per walk the
+// sums over the grid rows of f1 w, f1 w v2, f1 w v2^2/2 + f2 w.  The same
+// additions in the sweep and in k_moments, so a state loaded from a
+// checkpoint continues bit for bit.
+// ---------------------------------------------------------------------------
+template <int V>
+struct Moments {
+    double A[V], B[V], C[V], F; // of this walk; wall flux sum
+    double m[4];                // of the walks before
+
+    __device__ __forceinline__ void init()
+    {
+#pragma unroll
+        for (int i = 0; i < 4; i++) m[i] = 0;
+        F = 0;
+        clear();
+    }
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int v = 0; v < V; v++) A[v] = B[v] = C[v] = 0;
+    }
+    template <typename T>
+    __device__ __forceinline__ void add(const RowFactor &rf, const Vals<T, V> &r)
+    {
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            const double f1 = (double)r.x[v], f2 = (double)r.y[v];
+            A[v] = fma(rf.w, f1, A[v]);
+            B[v] = fma(rf.wv, f1, B[v]);
+            C[v] = fma(rf.w, f2, fma(rf.wh, f1, C[v]));
+        }
+    }
+    // outgoing flux through the wall face (S0x, S0y)
+    template <typename T>
+    __device__ __forceinline__ void add_wall(const RowFactor &rf, const ColFactor *col, double S0x, double S0y,
+                                             const Vals<T, V> &r)
+    {
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            const double s0 = col[v].v * S0x + rf.v * S0y;
+            if (s0 > 0) F = fma(col[v].w * rf.w * (double)r.x[v], s0, F);
+        }
+    }
+    // joins the v1 factors of this walk
+    __device__ __forceinline__ void fold(const ColFactor *col)
+    {
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            const double v1 = col[v].v, w = col[v].w;
+            const double wA = w * A[v];
+            m[0] += wA;
+            m[1] = fma(wA, v1, m[1]);
+            m[2] = fma(w, B[v], m[2]);
+            m[3] = fma(0.5 * v1 * v1, wA, fma(w, C[v], m[3]));
+        }
+        clear();
+    }
+    // totals over the wave, in every lane
+    __device__ __forceinline__ void total(double (&o)[5])
+    {
+        const double in[8] = {m[0], m[1], m[2], m[3], F, 0, 0, 0};
+        const double s = wave_scatter8(in);
+#pragma unroll
+        for (int i = 0; i < 5; i++) o[i] = lane_value(s, 8 * i);
+    }
+};
 
 // ---------------------------------------------------------------------------
 // primal sweep of one patch: eq. (numerpr_gov), first-order upwind, Jacobi
 // point-implicit: f^{n+1} = (sum_in |v.S| f_up + V g/tau) / (sum_out v.S + V/tau)
 // SO (second-order scheme, defect correction): the held correction c is
 // subtracted from the numerator and the wall flux is F + dF.
+// NT: rows are stored (and the held correction loaded) non-temporally.
 // ---------------------------------------------------------------------------
-template <typename T, bool SO>
-__device__ __forceinline__ void primal_patch(const DevSolve &d, int p, int par)
+template <typename T, int V, bool SO, bool NT>
+__device__ __forceinline__ void primal_cell(const DevSolve &d, int par, int c, bool act, int w, int lane)
 {
-    using T2 = typename Vec2<T>::type;
-    __shared__ PatchLds<T, false> sm;
-    const int w = uni((int)(threadIdx.x / kWave)), lane = threadIdx.x % kWave;
-    const int c0 = uni(d.patch[p]), cnt = uni(d.patch[p + 1]) - c0;
-    const bool act = w < cnt;                   // idle waves of a partial patch only join the barrier
-    const int c = c0 + (act ? w : 0);
-    const int nv = d.nv, n1 = d.n1;
-    const T2 *__restrict__ fin = static_cast<const T2 *>(d.f[par]);
-    T2 *__restrict__ fout = static_cast<T2 *>(d.f[par ^ 1]);
-    const T2 *__restrict__ corr = static_cast<const T2 *>(d.corr);
+    const Factors fac(d, 0);
+    fac.fill(d);
+    T *ex = static_cast<T *>(fac.end) + w * (d.lm.n1p + d.lm.n2p), *ey = ex + d.lm.n1p;
 
     const double *Win = d.W[par] + 4 * c;
     const double W0 = uni(Win[0]), W1 = uni(Win[1]), W2 = uni(Win[2]), W3 = uni(Win[3]);
-    const double rho = W0, u1 = W1 / rho, u2 = W2 / rho;
-    const double th = (2.0 / 3.0) * (W3 / rho - 0.5 * (u1 * u1 + u2 * u2));
-    const double itau = d.inv_tau_inf * rho * sqrt(2.0 * th);
+    const double ir = recip(W0), u1 = W1 * ir, u2 = W2 * ir;
+    const double th = (2.0 / 3.0) * (W3 * ir - 0.5 * (u1 * u1 + u2 * u2));
+    const double itau = d.inv_tau_inf * W0 * sqrt(2.0 * th);
     const double Vt = d.vol[c] * itau;
     // the equilibrium's parameters: the primitive variables, or those whose
     // grid moments equal W (found by k_eq_params before the sweep; tau keeps
     // the cell's own rho and theta)
-    double Pe[4] = {rho, u1, u2, th};
+    double Pe[4] = {W0, u1, u2, th};
     if (d.equil) {
         const double *pe = d.mstate + kEqState * c;
 #pragma unroll
         for (int a = 0; a < 4; a++) Pe[a] = uni(pe[a]);
     }
-    patch_tables<T, false>(d, sm, w, lane, Pe[1], Pe[2], 0.5 / Pe[3]);
+    const double ith = recip(Pe[3]), h = 0.5 * ith;
+    // Maxwellian factors: g1 = gc ex[a] ey[b]
+    for (int i = lane; i < d.lm.n1p + d.lm.n2p; i += kWave) {
+        const bool first = i < d.lm.n1p;
+        const int k = first ? i : i - d.lm.n1p;
+        double g = 0;
+        if (k < (first ? d.n1 : d.n2)) {
+            const double e = first ? d.vx[k] - Pe[1] : d.vy[k] - Pe[2];
+            g = exp(-e * e * h);
+        }
+        ex[i] = (T)g;
+    }
 
-    const size_t row = (size_t)c * nv;
+    const int nv = d.nv, rowb = nv * 2 * (int)sizeof(T);
+    const char *fin = static_cast<const char *>(d.f[par]);
+    char *fout = static_cast<char *>(d.f[par ^ 1]);
     int nb[4];
     T Sx[4], Sy[4];
 #pragma unroll
@@ -157,7 +409,7 @@ __device__ __forceinline__ void primal_patch(const DevSolve &d, int p, int par)
         Sy[q] = uni((T)d.S[8 * c + 2 * q + 1]);
     }
     const int wl = nb[0] <= -2 ? -2 - nb[0] : -1;
-    T wcoef = 0;
+    T wcoef = 1;
     double S0x = 0, S0y = 0;
     if (wl >= 0) {
         wcoef = uni((T)((SO ? d.F[par][wl] + d.dF[wl] : d.F[par][wl]) / d.D[wl]));
@@ -168,146 +420,92 @@ __device__ __forceinline__ void primal_patch(const DevSolve &d, int p, int par)
     // patch was read moments before by its own wave on this CU and is in
     // L1), the far-field table, or the wall table (g_M1, theta_w/2 g_M1)
     // scaled by F_l / D_l
-    const T2 *src[4];
-    T sc[4];
+    __amdgpu_buffer_rsrc_t src[4];
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
-        const int n = nb[q];
-        src[q] = n >= 0 ? fin + (size_t)n * nv : static_cast<const T2 *>(n == -1 ? d.fd : d.gw2);
-        sc[q] = n <= -2 ? wcoef : (T)1;
-    }
-    const T th2 = uni((T)(0.5 * Pe[3]));
-    const T gc = uni((T)(Pe[0] / (2.0 * kPi * Pe[3]))), VtT = uni((T)Vt);
+    for (int q = 0; q < 4; q++)
+        src[q] = row_rsrc(nb[q] >= 0 ? fin + (size_t)nb[q] * rowb : static_cast<const char *>(nb[q] == -1 ? d.fd : d.gw2),
+                          rowb);
+    const __amdgpu_buffer_rsrc_t dst = row_rsrc(fout + (size_t)c * rowb, act ? rowb : 0);
+    const __amdgpu_buffer_rsrc_t crow =
+        row_rsrc(SO ? static_cast<const char *>(d.corr) + (size_t)c * rowb : nullptr, SO ? rowb : 0);
+    const T th2 = uni((T)(0.5 * Pe[3])), VtT = uni((T)Vt), gc = uni((T)(Pe[0] * ith * (0.5 / kPi)));
+    const int bstep = d.lm.brow * d.n1 * 2 * (int)sizeof(T);
     __syncthreads();
 
-    double m0 = 0, m1 = 0, m2 = 0, m3 = 0, mF = 0;
-    // one velocity (1-D indices a, b): the point-implicit update from the
-    // four face sources, and the new value's share of the FP64 moments
-    auto update = [&](int a, int b, const T2 (&up)[4], T2 cr) {
-        const T v1 = (T)sm.vx[a], v2 = (T)sm.vy[b];
-        T out = 0, in1 = 0, in2 = 0;
+    Moments<V> mom;
+    mom.init();
+    for (int i = 0; i < d.lm.isteps; i++) {
+        const Walk wk = make_walk<T, V>(d, lane, i);
+        const int a = wk.a, steps = d.lm.tq + (i < d.lm.tr ? 1 : 0);
+        const ColFactor *col = fac.col + a;
+        T sx[4][V], e1[V];
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const T s = v1 * Sx[q] + v2 * Sy[q];
-            if (s > 0) {
-                out += s;
-            } else {
-                in1 -= s * (sc[q] * up[q].x);
-                in2 -= s * (sc[q] * up[q].y);
+        for (int v = 0; v < V; v++) {
+            const T v1 = (T)col[v].v;
+            e1[v] = gc * ex[a + v];
+            keep(e1[v]);
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                sx[q][v] = v1 * Sx[q];
+                keep(sx[q][v]);
             }
         }
-        if constexpr (SO) {
-            in1 -= cr.x;
-            in2 -= cr.y;
-        }
-        const T g1 = gc * sm.ex[w][a] * sm.ey[w][b];
-        const T g2 = th2 * g1;
-        const T rden = recip(out + VtT);
-        T2 r;
-        r.x = (in1 + VtT * g1) * rden;
-        r.y = (in2 + VtT * g2) * rden;
-        return r;
-    };
-    auto accumulate = [&](int a, int b, T2 r) {
-        const double v1d = sm.vx[a], v2d = sm.vy[b];
-        const double wt = sm.wx[a] * sm.wy[b];
-        const double f1 = (double)r.x, f2 = (double)r.y;
-        const double wf1 = wt * f1;
-        m0 += wf1;
-        m1 = fma(wf1, v1d, m1);
-        m2 = fma(wf1, v2d, m2);
-        m3 = fma(wf1, 0.5 * fma(v1d, v1d, v2d * v2d), fma(wt, f2, m3));
-        if (wl >= 0) {
-            const double s0 = v1d * S0x + v2d * S0y;
-            if (s0 > 0) mF = fma(wf1, s0, mF);
-        }
-    };
-    if (pair_velocities<T>(n1)) {
-        // FP32 with an even n1: two adjacent velocities (same b) per lane,
-        // 16-byte loads and stores
-        int a = (2 * lane) % n1, b = (2 * lane) / n1;
-        const int da = (2 * kWave) % n1, db = (2 * kWave) / n1;
-        const int nstep = (nv + 2 * kWave - 1) / (2 * kWave);
-        for (int t = 0; t < nstep; t++) {
-            const int k = 2 * (t * kWave + lane);
-            if (act && k < nv) {
-                // a face's source row only where it is upwind for either velocity
-                f4 u4[4];
-                {
-                    const T v1a = (T)sm.vx[a], v1b = (T)sm.vx[a + 1], v2 = (T)sm.vy[b];
+        int off = wk.off, b = wk.b;
+        for (int t = 0; t < steps; t++, b += d.lm.brow, off += bstep) {
+            const T v2 = (T)fac.row[b].v;
+            T s[4][V];
+            Vals<T, V> up[4], cr;
+            // a face's source row only where the face is upwind (the lanes
+            // of a wave split by the sign of v.S): about half the L2
+            // requests of loading all four
 #pragma unroll
-                    for (int q = 0; q < 4; q++) {
-                        u4[q] = f4{0, 0, 0, 0};
-                        if (!(v1a * Sx[q] + v2 * Sy[q] > 0) || !(v1b * Sx[q] + v2 * Sy[q] > 0))
-                            u4[q] = *reinterpret_cast<const f4 *>(src[q] + k);
-                    }
+            for (int q = 0; q < 4; q++) {
+                const T sy = v2 * Sy[q];
+                bool out = true;
+#pragma unroll
+                for (int v = 0; v < V; v++) {
+                    s[q][v] = sx[q][v] + sy;
+                    out = out && s[q][v] > 0;
                 }
-                T2 u0[4], u1[4], cr0 = {0, 0}, cr1 = {0, 0};
+                up[q] = row_load<T, V, false>(src[q], out ? kOutside : off);
+            }
+            if constexpr (SO) cr = row_load<T, V, NT>(crow, off);
+            loads_first();
+            const T eyb = ey[b];
+            Vals<T, V> r;
+#pragma unroll
+            for (int v = 0; v < V; v++) {
+                T out = 0, in1 = 0, in2 = 0;
 #pragma unroll
                 for (int q = 0; q < 4; q++) {
-                    u0[q].x = u4[q].x;
-                    u0[q].y = u4[q].y;
-                    u1[q].x = u4[q].z;
-                    u1[q].y = u4[q].w;
+                    out += max0(s[q][v]);
+                    const T m = min0(s[q][v]);
+                    T u1 = up[q].x[v], u2 = up[q].y[v];
+                    if (q == 0 && wl >= 0) {
+                        u1 *= wcoef;
+                        u2 *= wcoef;
+                    }
+                    in1 = madd(-m, u1, in1);
+                    in2 = madd(-m, u2, in2);
                 }
                 if constexpr (SO) {
-                    const f4 c4 = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(corr + row + k));
-                    cr0.x = c4.x;
-                    cr0.y = c4.y;
-                    cr1.x = c4.z;
-                    cr1.y = c4.w;
+                    in1 -= cr.x[v];
+                    in2 -= cr.y[v];
                 }
-                const T2 r0 = update(a, b, u0, cr0), r1 = update(a + 1, b, u1, cr1);
-                const f4 r4 = {(float)r0.x, (float)r0.y, (float)r1.x, (float)r1.y};
-                __builtin_nontemporal_store(r4, reinterpret_cast<f4 *>(fout + row + k));
-                accumulate(a, b, r0);
-                accumulate(a + 1, b, r1);
+                const T g1 = e1[v] * eyb, g2 = th2 * g1;
+                const T rden = recip(out + VtT);
+                r.x[v] = madd(VtT, g1, in1) * rden;
+                r.y[v] = madd(VtT, g2, in2) * rden;
             }
-            a += da;
-            b += db;
-            if (a >= n1) {
-                a -= n1;
-                b++;
-            }
+            row_store<T, V, NT>(dst, off, r);
+            const RowFactor rf = fac.row[b];
+            mom.add(rf, r);
+            if (wl >= 0) mom.add_wall(rf, col, S0x, S0y, r);
         }
-    } else {
-        int a = lane % n1, b = lane / n1;
-        const int da = kWave % n1, db = kWave / n1;
-        const int nstep = (nv + kWave - 1) / kWave;
-        for (int t = 0; t < nstep; t++) {
-            const int k = t * kWave + lane;
-            if (act && k < nv) {
-                // a face's source row only where the face is upwind (the
-                // lanes of a wave split by the sign of v.S): about half the
-                // L2 requests of loading all four (primal 557 -> 511 us on
-                // the 256x128 C-grid with 2304 velocities; the adjoint's
-                // downstream loads gain nothing from the same masking)
-                T2 up[4], cr = {0, 0};
-                {
-                    const T v1 = (T)sm.vx[a], v2 = (T)sm.vy[b];
-#pragma unroll
-                    for (int q = 0; q < 4; q++) {
-                        up[q] = T2{0, 0};
-                        if (!(v1 * Sx[q] + v2 * Sy[q] > 0)) up[q] = src[q][k];
-                    }
-                }
-                if constexpr (SO) cr = ntload2(&corr[row + k]);
-                const T2 r = update(a, b, up, cr);
-                // streaming stores: the new row is not read again in this sweep
-                __builtin_nontemporal_store(r.x, &fout[row + k].x);
-                __builtin_nontemporal_store(r.y, &fout[row + k].y);
-                accumulate(a, b, r);
-            }
-            a += da;
-            b += db;
-            if (a >= n1) {
-                a -= n1;
-                b++;
-            }
-        }
+        mom.fold(col);
     }
-    double acc[5] = {m0, m1, m2, m3, mF};
-    wave_sum<5>(acc);
+    double acc[5];
+    mom.total(acc);
     if (act && lane == 0) {
         double *Wo = d.W[par ^ 1] + 4 * c;
         Wo[0] = acc[0];
@@ -321,67 +519,60 @@ __device__ __forceinline__ void primal_patch(const DevSolve &d, int p, int par)
     }
 }
 
-// moments W and wall flux F of f[par] for one cell (no update), one wave
-// per cell: the same lane <-> velocity map, expressions and summation order
-// as the primal sweep's epilogue, so a state loaded from a checkpoint
-// continues bit for bit.
-template <typename T>
-__device__ __forceinline__ void moments_wave(const DevSolve &d, int c, int par)
+// the wave's cell of patch p: its number, whether it exists (idle waves of a
+// partial patch run along on the first cell without storing)
+__device__ __forceinline__ int patch_wave(const DevSolve &d, int p, int &w, bool &act)
 {
-    using T2 = typename Vec2<T>::type;
-    const int lane = threadIdx.x % kWave, nv = d.nv, n1 = d.n1;
-    const int l0 = d.nbr[4 * c];
+    w = uni((int)(threadIdx.x / kWave));
+    const int c0 = uni(d.patch[p]), cnt = uni(d.patch[p + 1]) - c0;
+    act = w < cnt;
+    return c0 + (act ? w : 0);
+}
+
+template <typename T, bool SO, bool NT>
+__device__ __forceinline__ void primal_patch(const DevSolve &d, int p, int par)
+{
+    int w;
+    bool act;
+    const int c = patch_wave(d, p, w, act), lane = threadIdx.x % kWave;
+    if (sizeof(T) == 4 && pair_velocities<T>(d.n1))
+        primal_cell<T, sizeof(T) == 4 ? 2 : 1, SO, NT>(d, par, c, act, w, lane);
+    else
+        primal_cell<T, 1, SO, NT>(d, par, c, act, w, lane);
+}
+
+// moments W and wall flux F of f[par] of a patch (no update): the walk,
+// expressions and summation order of the primal sweep.
+template <typename T, int V>
+__device__ __forceinline__ void moments_cell(const DevSolve &d, int par, int c, bool act, int lane)
+{
+    const Factors fac(d, 0);
+    fac.fill(d);
+    const int rowb = d.nv * 2 * (int)sizeof(T);
+    const int l0 = uni(d.nbr[4 * c]);
     const int wl = l0 <= -2 ? -2 - l0 : -1;
-    const double S0x = d.S[8 * c], S0y = d.S[8 * c + 1];
-    const T2 *__restrict__ f = static_cast<const T2 *>(d.f[par]);
-    double m0 = 0, m1 = 0, m2 = 0, m3 = 0, mF = 0;
-    auto accumulate = [&](int a, int b, T2 r) {
-        const double v1d = d.vx[a], v2d = d.vy[b];
-        const double wt = d.wx[a] * d.wy[b];
-        const double f1 = (double)r.x, f2 = (double)r.y;
-        const double wf1 = wt * f1;
-        m0 += wf1;
-        m1 = fma(wf1, v1d, m1);
-        m2 = fma(wf1, v2d, m2);
-        m3 = fma(wf1, 0.5 * fma(v1d, v1d, v2d * v2d), fma(wt, f2, m3));
-        if (wl >= 0) {
-            const double s0 = v1d * S0x + v2d * S0y;
-            if (s0 > 0) mF = fma(wf1, s0, mF);
+    const double S0x = uni(d.S[8 * c]), S0y = uni(d.S[8 * c + 1]);
+    const __amdgpu_buffer_rsrc_t src = row_rsrc(static_cast<const char *>(d.f[par]) + (size_t)c * rowb, rowb);
+    const int bstep = d.lm.brow * d.n1 * 2 * (int)sizeof(T);
+    __syncthreads();
+    Moments<V> mom;
+    mom.init();
+    for (int i = 0; i < d.lm.isteps; i++) {
+        const Walk wk = make_walk<T, V>(d, lane, i);
+        const int a = wk.a, steps = d.lm.tq + (i < d.lm.tr ? 1 : 0);
+        const ColFactor *col = fac.col + a;
+        int off = wk.off, b = wk.b;
+        for (int t = 0; t < steps; t++, b += d.lm.brow, off += bstep) {
+            const RowFactor rf = fac.row[b];
+            const Vals<T, V> r = row_load<T, V, false>(src, off);
+            mom.add(rf, r);
+            if (wl >= 0) mom.add_wall(rf, col, S0x, S0y, r);
         }
-    };
-    const size_t row = (size_t)c * nv;
-    if (pair_velocities<T>(n1)) {
-        int a = (2 * lane) % n1, b = (2 * lane) / n1;
-        const int da = (2 * kWave) % n1, db = (2 * kWave) / n1;
-        for (int k = 2 * lane; k < nv; k += 2 * kWave) {
-            T2 r0, r1;
-            r0 = f[row + k];
-            r1 = f[row + k + 1];
-            accumulate(a, b, r0);
-            accumulate(a + 1, b, r1);
-            a += da;
-            b += db;
-            if (a >= n1) {
-                a -= n1;
-                b++;
-            }
-        }
-    } else {
-        int a = lane % n1, b = lane / n1;
-        const int da = kWave % n1, db = kWave / n1;
-        for (int k = lane; k < nv; k += kWave) {
-            accumulate(a, b, f[row + k]);
-            a += da;
-            b += db;
-            if (a >= n1) {
-                a -= n1;
-                b++;
-            }
-        }
+        mom.fold(col);
     }
-    double acc[5] = {m0, m1, m2, m3, mF};
-    wave_sum<5>(acc);
-    if (lane == 0) {
+    double acc[5];
+    mom.total(acc);
+    if (act && lane == 0) {
         double *Wo = d.W[par] + 4 * c;
         Wo[0] = acc[0];
         Wo[1] = acc[1];
@@ -391,107 +582,206 @@ __device__ __forceinline__ void moments_wave(const DevSolve &d, int c, int par)
     }
 }
 
-// Per-cell constants of the adjoint moments: the frozen velocity u, theta/2,
-// theta_w/2, the wall face vector and wall element (-1: none), objective.
+// ---------------------------------------------------------------------------
+// FP64 adjoint moments of phi (eqs. adjoint_macdefines, formula_adjointbgk)
+// of one cell: phi . dg/dP for P = (rho, u1, u2, theta) from
+// A0 = sum w g1 qq, A1 = sum w g1 c1 qq, A2, A3 = sum w g1 |c|^2 qq and
+// A4 = sum w g1 phi2 (qq = phi1 + theta/2 phi2, c = v - u); the rho_tau sum
+// sum w (phi . (g - f)) = A0 - R, R = sum w phi . f; the wall multiplier sum
+// Pw over the wall face's incoming velocities.  Per walk the sums over
+// the grid rows carry w Y c2^p (AdjRow); the factors w gc X(v1), c1 join once
+// per walk.  Shared by the adjoint sweep's epilogue and k_adjoint_moments, so
+// both give the same bits.
+// ---------------------------------------------------------------------------
+// Per-cell constants: the frozen velocity u1, theta/2, theta_w/2, the wall
+// face vector and wall element (-1: none), objective.
 struct AdjCell {
-    double u1, u2, hth, thw2, S0x, S0y;
+    double u1, hth, thw2, S0x, S0y;
     int wl, obj;
 };
 
-// One velocity's share of the FP64 adjoint moments of phi (eqs.
-// adjoint_macdefines, formula_adjointbgk): phi . dg/dP for P = (rho, u1, u2,
-// theta) summed as A0..A4, the rho_tau sum R and the wall multiplier sum Pw
-// (incoming velocities of the wall face).  g1, g2: the frozen Maxwellian at
-// this velocity; gM[k]: g_M1(1, 0, theta_w) there, read only in wall cells.
-// Shared by the adjoint sweep's epilogue and k_adjoint_moments, so both give
-// the same bits.
-template <typename T>
-__device__ __forceinline__ void adjoint_terms(double &A0, double &A1, double &A2, double &A3, double &A4, double &R,
-                                              double &Pw, const AdjCell &q, double v1d, double v2d, double wt,
-                                              double g1, double g2, double p1, double p2, double fs1, double fs2,
-                                              const T *__restrict__ gM, int k)
-{
-    const double qq = fma(q.hth, p2, p1);
-    const double c1 = v1d - q.u1, c2 = v2d - q.u2;
-    const double wg = wt * g1, wq = wg * qq;
-    A0 += wq;
-    A1 = fma(wq, c1, A1);
-    A2 = fma(wq, c2, A2);
-    A3 = fma(wq, fma(c1, c1, c2 * c2), A3);
-    A4 = fma(wg, p2, A4);
-    R = fma(wt, fma(p1, g1 - fs1, p2 * (g2 - fs2)), R);
-    if (q.wl >= 0) {
-        const double s0 = v1d * q.S0x + v2d * q.S0y;
-        if (s0 <= 0) Pw += wt * s0 * (double)gM[k] * ((p1 + mJ_of(q.obj, v1d, v2d)) + q.thw2 * p2);
+template <int V>
+struct AdjMoments {
+    double Q[V], Qc[V], Qcc[V], E[V], R[V], Pw; // of this walk; wall multiplier sum
+    WalkSums m;                                 // of the walks before (6)
+
+    __device__ __forceinline__ void init()
+    {
+#pragma unroll
+        for (int i = 0; i < 6; i++) m[i] = 0;
+        Pw = 0;
+        clear();
     }
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int v = 0; v < V; v++) Q[v] = Qc[v] = Qcc[v] = E[v] = R[v] = 0;
+    }
+    template <typename T>
+    __device__ __forceinline__ void add(const AdjCell &q, const AdjRow &ar, double w, const Vals<T, V> &r,
+                                        const Vals<T, V> &fs)
+    {
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            const double p1 = (double)r.x[v], p2 = (double)r.y[v];
+            const double qq = fma(q.hth, p2, p1);
+            Q[v] = fma(ar.e, qq, Q[v]);
+            Qc[v] = fma(ar.ec, qq, Qc[v]);
+            Qcc[v] = fma(ar.ecc, qq, Qcc[v]);
+            E[v] = fma(ar.e, p2, E[v]);
+            R[v] = fma(w, fma(p1, (double)fs.x[v], p2 * (double)fs.y[v]), R[v]);
+        }
+    }
+    // incoming velocities of the wall face; gM: g_M1(1, 0, theta_w) of the V velocities
+    template <typename T>
+    __device__ __forceinline__ void add_wall(const AdjCell &q, const RowFactor &rf, const ColFactor *col,
+                                             const Vals<T, V> &r, const T *__restrict__ gM, bool in)
+    {
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            const double s0 = col[v].v * q.S0x + rf.v * q.S0y;
+            if (in && s0 <= 0)
+                Pw += col[v].w * rf.w * s0 * (double)gM[v] *
+                      (((double)r.x[v] + mJ_of(q.obj, col[v].v, rf.v)) + q.thw2 * (double)r.y[v]);
+        }
+    }
+    // joins the v1 factors of this walk (gx: w gc X of the V columns)
+    __device__ __forceinline__ void fold(const AdjCell &q, const ColFactor *col, const double *gx)
+    {
+        double t[6];
+#pragma unroll
+        for (int i = 0; i < 6; i++) t[i] = m[i];
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            const double g = gx[v], c1 = col[v].v - q.u1;
+            const double gQ = g * Q[v];
+            t[0] += gQ;
+            t[1] = fma(gQ, c1, t[1]);
+            t[2] = fma(g, Qc[v], t[2]);
+            t[3] = fma(gQ, c1 * c1, fma(g, Qcc[v], t[3]));
+            t[4] = fma(g, E[v], t[4]);
+            t[5] = fma(col[v].w, R[v], t[5]);
+        }
+#pragma unroll
+        for (int i = 0; i < 6; i++) m[i] = t[i];
+        clear();
+    }
+    // totals: A0..A4, R, Pw
+    __device__ __forceinline__ void total(double (&o)[7])
+    {
+        const double in[8] = {m[0], m[1], m[2], m[3], m[4], m[5], Pw, 0};
+        const double s = wave_scatter8(in);
+#pragma unroll
+        for (int i = 0; i < 7; i++) o[i] = lane_value(s, 8 * i);
+    }
+};
+
+// dP/dW of the cell (P = the equilibrium's (rho, u1, u2, theta)) for
+// adjoint_store: entry `lane` of the row-major 4x4 in lanes 0 .. 15, loaded
+// ahead of the sums
+__device__ __forceinline__ double adjoint_jacobian(const double *ac, int lane) { return ac[16 + (lane & 15)]; }
+
+// The wave's totals -> What (4) and rho_tau of the cell (ao[0..4]) and the
+// wall multiplier Phi_l of its wall element.
+__device__ __forceinline__ void adjoint_store(const DevSolve &d, double rho, double th, double itau, double M, bool act,
+                                              int lane, int wl, const double (&acc)[7], double *ao, double *Phi)
+{
+    const double ith = recip(th);
+    // phi . dg/dP
+    const double P0 = acc[0] * recip(rho), P1 = acc[1] * ith, P2 = acc[2] * ith;
+    const double P3 = 0.5 * acc[3] * (ith * ith) - acc[0] * ith + 0.5 * acc[4];
+    // What_m = sum_q (phi . dg/dP_q) dP_q/dW_m: lane 4 q + m, summed over q
+    const int q = (lane >> 2) & 3;
+    double s = (q < 2 ? (q == 0 ? P0 : P1) : (q == 2 ? P2 : P3)) * M;
+    s += dpp_move<0x128>(s);                                    // lane ^ 8
+    s += dpp_move<0x124>(s);                                    // lane - 4 in the row of 16
+    if (lane == 4) s = (acc[0] - acc[5]) * itau;
+    if (act && lane < 5) ao[lane] = s;
+    if (act && wl >= 0 && lane == 0) Phi[wl] = -acc[6] / (d.wall_A[wl] * d.D[wl]);
 }
 
-// The wave-reduced sums acc[0..6] of adjoint_terms -> What (4) and rho_tau
-// of the cell (ao[0..4]) and the wall multiplier Phi_l of its wall element.
-__device__ __forceinline__ void adjoint_store(const DevSolve &d, const double *ac, int wl, const double *acc,
-                                              double *ao, double *Phi)
-{
-    const double rho = ac[0], th = ac[3], itau = ac[4];
-    const double *M = ac + 16;      // dP/dW, P = the equilibrium's (rho, u1, u2, theta)
-    // phi . dg/dP
-    double Pq[4];
-    Pq[0] = acc[0] / rho;
-    Pq[1] = acc[1] / th;
-    Pq[2] = acc[2] / th;
-    Pq[3] = acc[3] / (2.0 * th * th) - acc[0] / th + 0.5 * acc[4];
-    // What_m = sum_q (phi . dg/dP_q) dP_q/dW_m
-#pragma unroll
-    for (int m = 0; m < 4; m++)
-        ao[m] = ((Pq[0] * M[m] + Pq[1] * M[4 + m]) + Pq[2] * M[8 + m]) + Pq[3] * M[12 + m];
-    ao[4] = acc[5] * itau;
-    if (wl >= 0) Phi[wl] = -acc[6] / (d.wall_A[wl] * d.D[wl]);
-}
+// LDS tables of the adjoint kernels: the shared factors, then per cell the
+// weighted Maxwellian factors (adj, gx) and the source's v2 part (qb)
+template <typename T>
+struct AdjLds {
+    Factors fac;
+    AdjRow *adj;
+    double *gx;
+    T *qb;
+    __device__ __forceinline__ AdjLds(const DevSolve &d, int w) : fac(d, kWalkSums * (int)sizeof(double) * kPatchCells * kWave)
+    {
+        AdjRow *a0 = static_cast<AdjRow *>(fac.end);
+        double *g0 = reinterpret_cast<double *>(a0 + kPatchCells * d.lm.n2p);
+        T *q0 = reinterpret_cast<T *>(g0 + kPatchCells * d.lm.n1p);
+        adj = a0 + w * d.lm.n2p;
+        gx = g0 + w * d.lm.n1p;
+        qb = q0 + w * d.lm.n2p;
+    }
+    // this wave's Maxwellian factors of the frozen state; no barrier
+    __device__ __forceinline__ void fill(const DevSolve &d, const double *ac, int lane) const
+    {
+        const double u1 = uni(ac[1]), u2 = uni(ac[2]), h = 0.5 * recip(uni(ac[3])), gc = uni(ac[5]);
+        for (int i = lane; i < d.lm.n1p + d.lm.n2p; i += kWave) {
+            const bool first = i < d.lm.n1p;
+            const int k = first ? i : i - d.lm.n1p;
+            const bool in = k < (first ? d.n1 : d.n2);
+            const double c = in ? (first ? d.vx[k] - u1 : d.vy[k] - u2) : 0.0;
+            const double w = in ? (first ? d.wx[k] : d.wy[k]) : 0.0;
+            const double g = w * exp(-c * c * h);
+            if (first)
+                gx[k] = gc * g;
+            else
+                adj[k] = {g, g * c, g * c * c, 0.0};
+        }
+    }
+};
 
 // ---------------------------------------------------------------------------
 // adjoint sweep of one patch: eq. (numerad_gov) with the wall and far-field
 // conditions of eq. (formula_adjointbgk), Jacobi point-implicit:
 // phi^{n+1} = (sum_out v.S phi_down + V (phi_eq/tau + phi_tau)) / (sum_out v.S + V/tau)
 // Epilogue: What (eq. adjoint_macdefines, via primitive variables),
-// rho_tau, the wall multiplier Phi_l and the residual partials of phi^{n+1}.
-// SO (second-order scheme): the held reconstruction term E is subtracted
-// from the numerator.
+// rho_tau, the wall multiplier Phi_l and (RES) the residual partials of
+// phi^{n+1}.  SO (second-order scheme): the held reconstruction term E is
+// subtracted from the numerator.  NT: rows only this cell touches are loaded
+// and stored non-temporally.
 // ---------------------------------------------------------------------------
-template <typename T, bool XCH, bool SO>
-__device__ __forceinline__ void adjoint_patch(const DevSolve &d, int p, int par)
+template <typename T, int V, bool SO, bool NT, bool RES>
+__device__ __forceinline__ void adjoint_cell(const DevSolve &d, int par, int c, bool act, int w, int lane)
 {
-    using T2 = typename Vec2<T>::type;
-    __shared__ PatchLds<T, XCH> sm;
-    const int w = uni((int)(threadIdx.x / kWave)), lane = threadIdx.x % kWave;
-    const int c0 = uni(d.patch[p]), cnt = uni(d.patch[p + 1]) - c0;
-    const bool act = w < cnt;
-    const int c = c0 + (act ? w : 0);
-    const int nv = d.nv, n1 = d.n1;
-    const T2 *__restrict__ pin = static_cast<const T2 *>(d.phi[par]);
-    T2 *__restrict__ pout = static_cast<T2 *>(d.phi[par ^ 1]);
-    const T2 *__restrict__ fst = static_cast<const T2 *>(d.fstar);
-    const T2 *__restrict__ eterm = static_cast<const T2 *>(d.corr);
-
+    const AdjLds<T> sm(d, w);
+    sm.fac.fill(d);
     const double *ac = d.acoef + kAcoef * c;
-    const double u1 = uni(ac[1]), u2 = uni(ac[2]), th = uni(ac[3]), itau = uni(ac[4]);
-    const double gcoef = ac[5];
-    const double dt0 = ac[6], dt1 = ac[7], dt2 = ac[8], dt3 = ac[9];
-    const double Vv = d.vol[c];
+    sm.fill(d, ac, lane);
+    const double rho = uni(ac[0]), th = uni(ac[3]), itau = uni(ac[4]), Vv = uni(d.vol[c]);
+    const double M = adjoint_jacobian(ac, lane);
     const double *aw = d.aW[par] + 8 * c;
-    const double rt = aw[4];
-    // source phi_eq / tau + phi_tau = C0 + C1 v1 + C2 v2 + C3 |v|^2/2 (first), C3 (second)
-    const double C0 = aw[0] * itau - rt * dt0, C1 = aw[1] * itau - rt * dt1;
-    const double C2 = aw[2] * itau - rt * dt2, C3 = aw[3] * itau - rt * dt3;
-    patch_tables<T, XCH>(d, sm, w, lane, u1, u2, 0.5 / th);
+    const double rt = uni(aw[4]);
+    // source V (phi_eq / tau + phi_tau) = V (C0 + C1 v1 + C2 v2 + C3 |v|^2/2)
+    // (first), V C3 (second): in FP64 with V folded in, as a part in v1 and a
+    // part in v2 (qb); in FP32 qb = C2 v2
+    constexpr bool kFold = sizeof(T) == 8;
+    double C[4];
+#pragma unroll
+    for (int m = 0; m < 4; m++) C[m] = uni(aw[m]) * itau - rt * uni(ac[6 + m]);
+    const T VT = uni((T)Vv), Ct1 = uni((T)C[1]), Ct2 = uni((T)C[2]), Ct3 = uni((T)C[3]);
+    for (int i = lane; i < d.lm.n2p; i += kWave) {
+        const double v2 = i < d.n2 ? d.vy[i] : 1.0;
+        sm.qb[i] = kFold ? (T)(Vv * v2 * fma(0.5 * C[3], v2, C[2])) : Ct2 * (T)v2;
+    }
 
-    const size_t row = (size_t)c * nv;
-    int nb[4], slot[4];
+    const int nv = d.nv, rowb = nv * 2 * (int)sizeof(T);
+    const char *pin = static_cast<const char *>(d.phi[par]);
+    int nb[4];
     T Sx[4], Sy[4];
+    __amdgpu_buffer_rsrc_t src[4];
 #pragma unroll
     for (int q = 0; q < 4; q++) {
         nb[q] = uni(d.nbr[4 * c + q]);
         Sx[q] = uni((T)d.S[8 * c + 2 * q]);
         Sy[q] = uni((T)d.S[8 * c + 2 * q + 1]);
-        slot[q] = XCH && nb[q] >= c0 && nb[q] < c0 + cnt ? nb[q] - c0 : -1;
+        // downstream row; nothing (zero) behind a boundary face
+        src[q] = row_rsrc(pin + (size_t)(nb[q] >= 0 ? nb[q] : c) * rowb, nb[q] >= 0 ? rowb : 0);
     }
     const int wl = nb[0] <= -2 ? -2 - nb[0] : -1;
     T Phi_w = 0;
@@ -502,356 +792,253 @@ __device__ __forceinline__ void adjoint_patch(const DevSolve &d, int p, int par)
         S0y = uni(d.S[8 * c + 1]);
     }
     const T *__restrict__ gM = static_cast<const T *>(d.gM);
-    // downstream rows of faces to cells not exchanged through LDS; every
-    // other face reads the own row (loaded anyway, an L1 hit) and ignores it
-    const T2 *dsrc[4];
-#pragma unroll
-    for (int q = 0; q < 4; q++) dsrc[q] = pin + (size_t)(nb[q] >= 0 && slot[q] < 0 ? nb[q] : c) * nv;
-    const int obj = d.objective;
-    const T VT = uni((T)Vv), den0 = uni((T)(Vv * itau));
-    const T Ct0 = uni((T)C0), Ct1 = uni((T)C1), Ct2 = uni((T)C2), Ct3 = uni((T)C3);
-    const T gc = uni((T)gcoef), th2 = uni((T)(0.5 * th));
-    const double thw2 = 0.5 * d.theta_w, hth = 0.5 * th;
+    const __amdgpu_buffer_rsrc_t own = row_rsrc(pin + (size_t)c * rowb, rowb);
+    const __amdgpu_buffer_rsrc_t fst = row_rsrc(static_cast<const char *>(d.fstar) + (size_t)c * rowb, rowb);
+    const __amdgpu_buffer_rsrc_t erow =
+        row_rsrc(SO ? static_cast<const char *>(d.corr) + (size_t)c * rowb : nullptr, SO ? rowb : 0);
+    const __amdgpu_buffer_rsrc_t dst = row_rsrc(static_cast<char *>(d.phi[par ^ 1]) + (size_t)c * rowb, act ? rowb : 0);
+    const T den0 = uni((T)(Vv * itau)), src2 = VT * Ct3;
+    const AdjCell cq = {uni(ac[1]), 0.5 * uni(ac[3]), 0.5 * d.theta_w, S0x, S0y, wl, d.objective};
+    const int bstep = d.lm.brow * d.n1 * 2 * (int)sizeof(T);
     __syncthreads();
 
-    double A0 = 0, A1 = 0, A2 = 0, A3 = 0, A4 = 0, R = 0, Pw = 0, dn = 0, dd = 0;
-    // one velocity (1-D indices a, b): the point-implicit update from the
-    // downstream values of the four faces, and the new value's share of the
-    // FP64 adjoint moments, the wall multiplier and the residual
-    auto update = [&](int a, int b, const T2 (&dwn)[4], T2 e) {
-        const double v1d = sm.vx[a], v2d = sm.vy[b];
-        const T v1 = (T)v1d, v2 = (T)v2d;
-        const T mj = (T)mJ_of(obj, v1d, v2d);
-        T out = 0, a1 = 0, a2 = 0;
+    AdjMoments<V> mom;
+    mom.init();
+    double dn = 0, dd = 0;
+    for (int i = 0; i < d.lm.isteps; i++) {
+        const Walk wk = make_walk<T, V>(d, lane, i);
+        const int a = wk.a, steps = d.lm.tq + (i < d.lm.tr ? 1 : 0);
+        const ColFactor *col = sm.fac.col + a;
+        T sx[4][V], s1[V], v1h[V];
+        double dnb[V], ddb[V];
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const T s = v1 * Sx[q] + v2 * Sy[q];
-            if (s > 0) {
-                out += s;
-                if (nb[q] >= 0) {
-                    a1 += s * dwn[q].x;
-                    a2 += s * dwn[q].y;
-                } else if (nb[q] <= -2) {
-                    a1 += s * (Phi_w - mj);
+        for (int v = 0; v < V; v++) {
+            const double v1 = col[v].v;
+            s1[v] = kFold ? (T)(Vv * fma(fma(0.5 * C[3], v1, C[1]), v1, C[0])) : (T)C[0] + Ct1 * (T)v1;
+            keep(s1[v]);
+            v1h[v] = (T)v1 * (T)v1;
+            if (!kFold) keep(v1h[v]);
+            dnb[v] = ddb[v] = 0;
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                sx[q][v] = (T)v1 * Sx[q];
+                keep(sx[q][v]);
+            }
+        }
+        int off = wk.off, b = wk.b;
+        for (int t = 0; t < steps; t++, b += d.lm.brow, off += bstep) {
+            const T v2 = (T)sm.fac.row[b].v;
+            T s[4][V];
+            Vals<T, V> dwn[4], old, fs, e;
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                const T sy = v2 * Sy[q];
+                bool in = true;
+#pragma unroll
+                for (int v = 0; v < V; v++) {
+                    s[q][v] = sx[q][v] + sy;
+                    in = in && !(s[q][v] > 0);
                 }
+                dwn[q] = row_load<T, V, false>(src[q], in ? kOutside : off);
             }
-        }
-        if constexpr (SO) {
-            a1 -= e.x;
-            a2 -= e.y;
-        }
-        const T vv2 = (T)0.5 * (v1 * v1 + v2 * v2);
-        const T s1 = Ct0 + Ct1 * v1 + Ct2 * v2 + Ct3 * vv2;
-        const T rden = recip(out + den0);
-        T2 r;
-        r.x = (a1 + VT * s1) * rden;
-        r.y = (a2 + VT * Ct3) * rden;
-        return r;
-    };
-    const AdjCell cq = {u1, u2, hth, thw2, S0x, S0y, wl, obj};
-    auto accumulate = [&](int a, int b, int k, T2 r, T2 fs, T2 old) {
-        const double v1d = sm.vx[a], v2d = sm.vy[b];
-        const double wt = sm.wx[a] * sm.wy[b];
-        const double p1 = (double)r.x, p2 = (double)r.y;
-        const double g1 = (double)(gc * sm.ex[w][a] * sm.ey[w][b]);
-        const double g2 = (double)(th2 * (T)g1);
-        adjoint_terms(A0, A1, A2, A3, A4, R, Pw, cq, v1d, v2d, wt, g1, g2, p1, p2, (double)fs.x, (double)fs.y, gM, k);
-        const double e1 = p1 - (double)old.x, e2 = p2 - (double)old.y;
-        dn = fma(wt, fma(e1, e1, e2 * e2), dn);
-        dd = fma(wt, fma(p1, p1, p2 * p2), dd);
-    };
-    if constexpr (XCH) {
-        int a = lane % n1, b = lane / n1;
-        const int da = kWave % n1, db = kWave / n1;
-        const int nstep = (nv + kWave - 1) / kWave;
-        T2 own_n = {0, 0}, fs_n = {0, 0}, e_n = {0, 0}, dwn_n[4] = {};
-        if (act) {
-            const int k = min(lane, nv - 1);
-            own_n = pin[row + k];
-            fs_n = ntload2(&fst[row + k]);
-            if constexpr (SO) e_n = ntload2(&eterm[row + k]);
+            fs = row_load<T, V, NT>(fst, off);
+            if constexpr (RES) old = row_load<T, V, false>(own, off);
+            if constexpr (SO) e = row_load<T, V, NT>(erow, off);
+            loads_first();
+            const T qb = sm.qb[b], v2h = v2 * v2;
+            Vals<T, V> r;
 #pragma unroll
-            for (int q = 0; q < 4; q++) dwn_n[q] = dsrc[q][k];
-        }
-        for (int t = 0; t < nstep; t++) {
-            const int buf = t & 1;
-            const int k = t * kWave + lane;
-            // every wave publishes its own values of this step, then the
-            // next step's loads go out before this step's arithmetic
-            sm.xch[buf][w][lane] = own_n;
-            const T2 old = own_n, fs = fs_n, e = e_n;
-            T2 dwn[4];
-#pragma unroll
-            for (int q = 0; q < 4; q++) dwn[q] = dwn_n[q];
-            __syncthreads();
-            if (act && t + 1 < nstep) {
-                const int kn = min(k + kWave, nv - 1);
-                own_n = pin[row + kn];
-                fs_n = ntload2(&fst[row + kn]);
-                if constexpr (SO) e_n = ntload2(&eterm[row + kn]);
-#pragma unroll
-                for (int q = 0; q < 4; q++) dwn_n[q] = dsrc[q][kn];
-            }
-#pragma unroll
-            for (int q = 0; q < 4; q++)
-                if (slot[q] >= 0) dwn[q] = sm.xch[buf][slot[q]][lane];
-            if (act && k < nv) {
-                const T2 r = update(a, b, dwn, e);
-                __builtin_nontemporal_store(r.x, &pout[row + k].x);
-                __builtin_nontemporal_store(r.y, &pout[row + k].y);
-                accumulate(a, b, k, r, fs, old);
-            }
-            a += da;
-            b += db;
-            if (a >= n1) {
-                a -= n1;
-                b++;
-            }
-        }
-    } else if (pair_velocities<T>(n1)) {
-        int a = (2 * lane) % n1, b = (2 * lane) / n1;
-        const int da = (2 * kWave) % n1, db = (2 * kWave) / n1;
-        const int nstep = (nv + 2 * kWave - 1) / (2 * kWave);
-        for (int t = 0; t < nstep; t++) {
-            const int k = 2 * (t * kWave + lane);
-            if (act && k < nv) {
-                const f4 o4 = *reinterpret_cast<const f4 *>(pin + row + k);
-                const f4 s4 = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(fst + row + k));
-                f4 d4[4];
-#pragma unroll
-                for (int q = 0; q < 4; q++) d4[q] = *reinterpret_cast<const f4 *>(dsrc[q] + k);
-                T2 d0[4], d1[4], e0 = {0, 0}, e1 = {0, 0};
+            for (int v = 0; v < V; v++) {
+                T out = 0, a1 = 0, a2 = 0;
 #pragma unroll
                 for (int q = 0; q < 4; q++) {
-                    d0[q].x = d4[q].x;
-                    d0[q].y = d4[q].y;
-                    d1[q].x = d4[q].z;
-                    d1[q].y = d4[q].w;
+                    const T m = max0(s[q][v]);
+                    out += m;
+                    T d1 = dwn[q].x[v];
+                    if (q == 0 && wl >= 0) d1 = Phi_w - (T)mJ_of(cq.obj, col[v].v, sm.fac.row[b].v);
+                    a1 = madd(m, d1, a1);
+                    a2 = madd(m, dwn[q].y[v], a2);
                 }
                 if constexpr (SO) {
-                    const f4 e4 = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(eterm + row + k));
-                    e0.x = e4.x;
-                    e0.y = e4.y;
-                    e1.x = e4.z;
-                    e1.y = e4.w;
+                    a1 -= e.x[v];
+                    a2 -= e.y[v];
                 }
-                const T2 r0 = update(a, b, d0, e0), r1 = update(a + 1, b, d1, e1);
-                const f4 r4 = {(float)r0.x, (float)r0.y, (float)r1.x, (float)r1.y};
-                __builtin_nontemporal_store(r4, reinterpret_cast<f4 *>(pout + row + k));
-                T2 fs0, fs1, old0, old1;
-                fs0.x = s4.x;
-                fs0.y = s4.y;
-                fs1.x = s4.z;
-                fs1.y = s4.w;
-                old0.x = o4.x;
-                old0.y = o4.y;
-                old1.x = o4.z;
-                old1.y = o4.w;
-                accumulate(a, b, k, r0, fs0, old0);
-                accumulate(a + 1, b, k + 1, r1, fs1, old1);
+                T src1;
+                if constexpr (sizeof(T) == 8)
+                    src1 = s1[v] + qb;                  // V included
+                else
+                    src1 = VT * ((s1[v] + qb) + Ct3 * (0.5f * (v1h[v] + v2h)));
+                const T rden = recip(out + den0);
+                r.x[v] = (a1 + src1) * rden;
+                r.y[v] = (a2 + src2) * rden;
             }
-            a += da;
-            b += db;
-            if (a >= n1) {
-                a -= n1;
-                b++;
-            }
-        }
-    } else {
-        int a = lane % n1, b = lane / n1;
-        const int da = kWave % n1, db = kWave / n1;
-        const int nstep = (nv + kWave - 1) / kWave;
-        for (int t = 0; t < nstep; t++) {
-            const int k = t * kWave + lane;
-            if (act && k < nv) {
-                const T2 old = pin[row + k], fs = ntload2(&fst[row + k]);
-                T2 dwn[4], e = {0, 0};
+            row_store<T, V, NT>(dst, off, r);
+            const double w = sm.fac.row[b].w;
+            mom.add(cq, sm.adj[b], w, r, fs);
+            if (wl >= 0) mom.add_wall(cq, sm.fac.row[b], col, r, gM + b * d.n1 + a, wk.in && b < d.n2);
+            if constexpr (RES) {
 #pragma unroll
-                for (int q = 0; q < 4; q++) dwn[q] = dsrc[q][k];
-                if constexpr (SO) e = ntload2(&eterm[row + k]);
-                const T2 r = update(a, b, dwn, e);
-                __builtin_nontemporal_store(r.x, &pout[row + k].x);
-                __builtin_nontemporal_store(r.y, &pout[row + k].y);
-                accumulate(a, b, k, r, fs, old);
+                for (int v = 0; v < V; v++) {
+                    const double p1 = (double)r.x[v], p2 = (double)r.y[v];
+                    const double e1 = p1 - (double)old.x[v], e2 = p2 - (double)old.y[v];
+                    dnb[v] = fma(w, fma(e1, e1, e2 * e2), dnb[v]);
+                    ddb[v] = fma(w, fma(p1, p1, p2 * p2), ddb[v]);
+                }
             }
-            a += da;
-            b += db;
-            if (a >= n1) {
-                a -= n1;
-                b++;
+        }
+        mom.fold(cq, col, sm.gx + a);
+        if constexpr (RES) {
+#pragma unroll
+            for (int v = 0; v < V; v++) {
+                dn = fma(col[v].w, dnb[v], dn);
+                dd = fma(col[v].w, ddb[v], dd);
             }
         }
     }
-    double acc[9] = {A0, A1, A2, A3, A4, R, Pw, dn, dd};
-    wave_sum<9>(acc);
-    if (act && lane == 0) {
-        adjoint_store(d, ac, wl, acc, d.aW[par ^ 1] + 8 * c, d.Phi[par ^ 1]);
-        d.red[2 * c] = acc[7];
-        d.red[2 * c + 1] = acc[8];
+    double acc[7];
+    mom.total(acc);
+    if constexpr (RES) {
+        double rs[2] = {dn, dd};
+        wave_sum<2>(rs);
+        if (act && lane == 0) {
+            d.red[2 * c] = rs[0];
+            d.red[2 * c + 1] = rs[1];
+        }
     }
+    adjoint_store(d, rho, th, itau, M, act, lane, wl, acc, d.aW[par ^ 1] + 8 * c, d.Phi[par ^ 1]);
+}
+
+template <typename T, bool SO, bool NT, bool RES>
+__device__ __forceinline__ void adjoint_patch(const DevSolve &d, int p, int par)
+{
+    int w;
+    bool act;
+    const int c = patch_wave(d, p, w, act), lane = threadIdx.x % kWave;
+    if (sizeof(T) == 4 && pair_velocities<T>(d.n1))
+        adjoint_cell<T, sizeof(T) == 4 ? 2 : 1, SO, NT, RES>(d, par, c, act, w, lane);
+    else
+        adjoint_cell<T, 1, SO, NT, RES>(d, par, c, act, w, lane);
 }
 
 // Adjoint moments What, rho_tau and wall multipliers Phi_l of phi[par] with
-// no update (a loaded phi): the lane <-> velocity map, expressions and
-// summation order of the adjoint sweep's epilogue, so the next sweep sees
-// what a sweep that had produced this phi would have left.  CORR: phi is
-// first corrected in place by the collision invariant -(z . Psi, z_3) of the
-// adjoint prediction (z [nc][4]), and the moments are those of the result.
-template <typename T, bool CORR = false>
-__device__ __forceinline__ void adjoint_moments_patch(const DevSolve &d, int p, int par, const double *z = nullptr)
+// no update (a loaded phi): the walk, expressions and summation order of the
+// adjoint sweep's epilogue, so the next sweep sees what a sweep that had
+// produced this phi would have left.  CORR: phi is first corrected in place
+// by the collision invariant -(z . Psi, z_3) of the adjoint prediction
+// (z [nc][4]), and the moments are those of the result.
+template <typename T, int V, bool CORR>
+__device__ __forceinline__ void adjoint_moments_cell(const DevSolve &d, int par, const double *z, int c, bool act, int w,
+                                                     int lane)
 {
-    using T2 = typename Vec2<T>::type;
-    __shared__ PatchLds<T, false> sm;
-    const int w = uni((int)(threadIdx.x / kWave)), lane = threadIdx.x % kWave;
-    const int c0 = uni(d.patch[p]), cnt = uni(d.patch[p + 1]) - c0;
-    const bool act = w < cnt;
-    const int c = c0 + (act ? w : 0);
-    const int nv = d.nv, n1 = d.n1;
-    // read and (CORR) written in place: no restrict
-    const T2 *pin = static_cast<const T2 *>(d.phi[par]);
-    const T2 *__restrict__ fst = static_cast<const T2 *>(d.fstar);
-    const T *__restrict__ gM = static_cast<const T *>(d.gM);
+    const AdjLds<T> sm(d, w);
+    sm.fac.fill(d);
     const double *ac = d.acoef + kAcoef * c;
-    const double u1 = uni(ac[1]), u2 = uni(ac[2]), th = uni(ac[3]);
-    patch_tables<T, false>(d, sm, w, lane, u1, u2, 0.5 / th);
+    sm.fill(d, ac, lane);
+    const double rho = uni(ac[0]), th = uni(ac[3]), itau = uni(ac[4]);
+    const double M = adjoint_jacobian(ac, lane);
+    const T *__restrict__ gM = static_cast<const T *>(d.gM);
     const int l0 = uni(d.nbr[4 * c]);
     const int wl = l0 <= -2 ? -2 - l0 : -1;
-    double S0x = 0, S0y = 0;
-    if (wl >= 0) {
-        S0x = uni(d.S[8 * c]);
-        S0y = uni(d.S[8 * c + 1]);
-    }
-    const T gc = uni((T)ac[5]), th2 = uni((T)(0.5 * th));
-    const AdjCell cq = {u1, u2, 0.5 * th, 0.5 * d.theta_w, S0x, S0y, wl, d.objective};
-    const size_t row = (size_t)c * nv;
-    __syncthreads();
-    double A0 = 0, A1 = 0, A2 = 0, A3 = 0, A4 = 0, R = 0, Pw = 0;
-    T2 *pio = static_cast<T2 *>(d.phi[par]);
+    const int rowb = d.nv * 2 * (int)sizeof(T);
+    const AdjCell cq = {uni(ac[1]), 0.5 * uni(ac[3]), 0.5 * d.theta_w, uni(d.S[8 * c]), uni(d.S[8 * c + 1]), wl, d.objective};
+    const __amdgpu_buffer_rsrc_t prow = row_rsrc(static_cast<const char *>(d.phi[par]) + (size_t)c * rowb, rowb);
+    const __amdgpu_buffer_rsrc_t dst = row_rsrc(static_cast<char *>(d.phi[par]) + (size_t)c * rowb, act ? rowb : 0);
+    const __amdgpu_buffer_rsrc_t fst = row_rsrc(static_cast<const char *>(d.fstar) + (size_t)c * rowb, rowb);
+    const int bstep = d.lm.brow * d.n1 * 2 * (int)sizeof(T);
     double zc[4] = {0, 0, 0, 0};
-    if (CORR) {
+    if constexpr (CORR) {
 #pragma unroll
         for (int i = 0; i < 4; i++) zc[i] = uni(z[4 * c + i]);
     }
-    // one velocity: (CORR) the corrected value, returned for the store, and
-    // its share of the sums
-    auto accumulate = [&](int a, int b, int k, T2 r, T2 fs) {
-        const double v1d = sm.vx[a], v2d = sm.vy[b];
-        if (CORR) {
-            const double s1 = ((zc[0] + zc[1] * v1d) + zc[2] * v2d) + zc[3] * (0.5 * (v1d * v1d + v2d * v2d));
-            r.x = (T)((double)r.x - s1);
-            r.y = (T)((double)r.y - zc[3]);
-        }
-        const double wt = sm.wx[a] * sm.wy[b];
-        const double g1 = (double)(gc * sm.ex[w][a] * sm.ey[w][b]);
-        const double g2 = (double)(th2 * (T)g1);
-        adjoint_terms(A0, A1, A2, A3, A4, R, Pw, cq, v1d, v2d, wt, g1, g2, (double)r.x, (double)r.y, (double)fs.x,
-                      (double)fs.y, gM, k);
-        return r;
-    };
-    // streaming access as in the sweeps: the frozen f and the corrected row
-    // are not read again here (non-temporal), FP32 pairs move 16 bytes
-    if (act) {
-        if (pair_velocities<T>(n1)) {
-            int a = (2 * lane) % n1, b = (2 * lane) / n1;
-            const int da = (2 * kWave) % n1, db = (2 * kWave) / n1;
-            for (int k = 2 * lane; k < nv; k += 2 * kWave) {
-                const f4 p4 = *reinterpret_cast<const f4 *>(pin + row + k);
-                const f4 s4 = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(fst + row + k));
-                T2 r0, r1, fs0, fs1;
-                r0.x = p4.x;
-                r0.y = p4.y;
-                r1.x = p4.z;
-                r1.y = p4.w;
-                fs0.x = s4.x;
-                fs0.y = s4.y;
-                fs1.x = s4.z;
-                fs1.y = s4.w;
-                r0 = accumulate(a, b, k, r0, fs0);
-                r1 = accumulate(a + 1, b, k + 1, r1, fs1);
-                if (CORR) {
-                    const f4 o4 = {(float)r0.x, (float)r0.y, (float)r1.x, (float)r1.y};
-                    __builtin_nontemporal_store(o4, reinterpret_cast<f4 *>(pio + row + k));
+    __syncthreads();
+    AdjMoments<V> mom;
+    mom.init();
+    for (int i = 0; i < d.lm.isteps; i++) {
+        const Walk wk = make_walk<T, V>(d, lane, i);
+        const int a = wk.a, steps = d.lm.tq + (i < d.lm.tr ? 1 : 0);
+        const ColFactor *col = sm.fac.col + a;
+        double z1[V];
+#pragma unroll
+        for (int v = 0; v < V; v++) z1[v] = fma(fma(0.5 * zc[3], col[v].v, zc[1]), col[v].v, zc[0]);
+        int off = wk.off, b = wk.b;
+        for (int t = 0; t < steps; t++, b += d.lm.brow, off += bstep) {
+            const RowFactor rf = sm.fac.row[b];
+            Vals<T, V> r = row_load<T, V, false>(prow, off);
+            const Vals<T, V> fs = row_load<T, V, true>(fst, off);
+            if constexpr (CORR) {
+                const double z2 = rf.v * fma(0.5 * zc[3], rf.v, zc[2]);
+#pragma unroll
+                for (int v = 0; v < V; v++) {
+                    r.x[v] = (T)((double)r.x[v] - (z1[v] + z2));
+                    r.y[v] = (T)((double)r.y[v] - zc[3]);
                 }
-                a += da;
-                b += db;
-                if (a >= n1) {
-                    a -= n1;
-                    b++;
-                }
+                row_store<T, V, true>(dst, off, r);
             }
-        } else {
-            int a = lane % n1, b = lane / n1;
-            const int da = kWave % n1, db = kWave / n1;
-            for (int k = lane; k < nv; k += kWave) {
-                const T2 r = accumulate(a, b, k, pin[row + k], ntload2(&fst[row + k]));
-                if (CORR) {
-                    __builtin_nontemporal_store(r.x, &pio[row + k].x);
-                    __builtin_nontemporal_store(r.y, &pio[row + k].y);
-                }
-                a += da;
-                b += db;
-                if (a >= n1) {
-                    a -= n1;
-                    b++;
-                }
-            }
+            mom.add(cq, sm.adj[b], rf.w, r, fs);
+            if (wl >= 0) mom.add_wall(cq, rf, col, r, gM + b * d.n1 + a, wk.in && b < d.n2);
         }
+        mom.fold(cq, col, sm.gx + a);
     }
-    double acc[7] = {A0, A1, A2, A3, A4, R, Pw};
-    wave_sum<7>(acc);
-    if (act && lane == 0) adjoint_store(d, ac, wl, acc, d.aW[par] + 8 * c, d.Phi[par]);
+    double acc[7];
+    mom.total(acc);
+    adjoint_store(d, rho, th, itau, M, act, lane, wl, acc, d.aW[par] + 8 * c, d.Phi[par]);
 }
 
 // ---------------------------------------------------------------------------
 // kernels
 // ---------------------------------------------------------------------------
 constexpr int kPatchBlock = kPatchCells * kWave;   // threads of a patch workgroup
-static_assert(kPatchCells >= 4, "the velocity tables are loaded by the first 256 threads");
 
-template <typename T, bool SO>
+template <typename T, bool SO, bool NT>
 __global__ __launch_bounds__(kPatchBlock) void k_primal_sweep(DevSolve d, int par)
 {
     const int p = xcd_item(d.np, blockIdx.x);
     if (p < 0) return;
-    primal_patch<T, SO>(d, p, par);
+    primal_patch<T, SO, NT>(d, p, par);
 }
 
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_moments(DevSolve d, int par)
+__global__ __launch_bounds__(kPatchBlock) void k_moments(DevSolve d, int par)
 {
-    const int c = blockIdx.x * (kBlock / kWave) + (int)(threadIdx.x / kWave);
-    if (c < d.nc) moments_wave<T>(d, c, par);
+    const int p = xcd_item(d.np, blockIdx.x);
+    if (p < 0) return;
+    int w;
+    bool act;
+    const int c = patch_wave(d, p, w, act), lane = threadIdx.x % kWave;
+    if (sizeof(T) == 4 && pair_velocities<T>(d.n1))
+        moments_cell<T, sizeof(T) == 4 ? 2 : 1>(d, par, c, act, lane);
+    else
+        moments_cell<T, 1>(d, par, c, act, lane);
 }
 
-template <typename T, bool SO>
+template <typename T, bool SO, bool NT, bool RES>
 __global__ __launch_bounds__(kPatchBlock) void k_adjoint_sweep(DevSolve d, int par)
 {
     const int p = xcd_item(d.np, blockIdx.x);
     if (p < 0) return;
-    adjoint_patch<T, kAdjointExchange<T>, SO>(d, p, par);
+    adjoint_patch<T, SO, NT, RES>(d, p, par);
 }
 
-template <typename T>
-__global__ __launch_bounds__(kPatchBlock) void k_adjoint_moments(DevSolve d, int par)
+// adjoint moments of phi[par]; CORR: corrected by z first
+template <typename T, bool CORR>
+__global__ __launch_bounds__(kPatchBlock) void k_adjoint_moments(DevSolve d, int par, const double *z)
 {
     const int p = xcd_item(d.np, blockIdx.x);
     if (p < 0) return;
-    adjoint_moments_patch<T>(d, p, par);
-}
-
-template <typename T>
-__global__ __launch_bounds__(kPatchBlock) void k_adjoint_correct_moments(DevSolve d, int par, const double *z)
-{
-    const int p = xcd_item(d.np, blockIdx.x);
-    if (p < 0) return;
-    adjoint_moments_patch<T, true>(d, p, par, z);
+    int w;
+    bool act;
+    const int c = patch_wave(d, p, w, act), lane = threadIdx.x % kWave;
+    if (sizeof(T) == 4 && pair_velocities<T>(d.n1))
+        adjoint_moments_cell<T, sizeof(T) == 4 ? 2 : 1, CORR>(d, par, z, c, act, w, lane);
+    else
+        adjoint_moments_cell<T, 1, CORR>(d, par, z, c, act, w, lane);
 }
 
 // one sweep of the primal-phase (or adjoint-phase) members of a batch that
 // run one scheme (SO: second order, the held corrections evaluated before
 // the launch); a workgroup owns one (solve, patch).  Phases and schemes are
 // separate kernels so that each gets the occupancy of its own registers.
-template <typename T, bool SO>
+template <typename T, bool SO, bool NT>
 __global__ __launch_bounds__(kPatchBlock) void k_batch_primal(const DevSolve *__restrict__ tab,
                                                               const int32_t *__restrict__ blk_solve,
                                                               const int32_t *__restrict__ blk_patch,
@@ -859,10 +1046,10 @@ __global__ __launch_bounds__(kPatchBlock) void k_batch_primal(const DevSolve *__
 {
     const int s = blk_solve[blockIdx.x];
     if (s < 0) return;
-    primal_patch<T, SO>(tab[s], blk_patch[blockIdx.x], (par0[s] + step) & 1);
+    primal_patch<T, SO, NT>(tab[s], blk_patch[blockIdx.x], (par0[s] + step) & 1);
 }
 
-template <typename T, bool SO>
+template <typename T, bool SO, bool NT, bool RES>
 __global__ __launch_bounds__(kPatchBlock) void k_batch_adjoint(const DevSolve *__restrict__ tab,
                                                                const int32_t *__restrict__ blk_solve,
                                                                const int32_t *__restrict__ blk_patch,
@@ -870,7 +1057,7 @@ __global__ __launch_bounds__(kPatchBlock) void k_batch_adjoint(const DevSolve *_
 {
     const int s = blk_solve[blockIdx.x];
     if (s < 0) return;
-    adjoint_patch<T, kAdjointExchange<T>, SO>(tab[s], blk_patch[blockIdx.x], (par0[s] + step) & 1);
+    adjoint_patch<T, SO, NT, RES>(tab[s], blk_patch[blockIdx.x], (par0[s] + step) & 1);
 }
 
 // Block tables of a batch on the device (the allocation-free batch): block
@@ -1105,20 +1292,15 @@ hipError_t launch_primal_init(const DevSolve &d, hipStream_t st)
 
 hipError_t launch_moments(const DevSolve &d, int par, hipStream_t st)
 {
-    constexpr int per_block = kBlock / kWave;
-    DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(k_moments<T>, dim3((d.nc + per_block - 1) / per_block), dim3(kBlock), 0,
-                                             st, d, par));
+    DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(k_moments<T>, dim3(xcd_grid(d.np)), dim3(kPatchBlock), factor_lds(d.lm), st,
+                                             d, par));
     return hipGetLastError();
 }
 
 hipError_t launch_primal_sweep(const DevSolve &d, int par, hipStream_t st)
 {
-    if (d.order == 2)
-        DVM_DISPATCH(d.mixed, hipLaunchKernelGGL((k_primal_sweep<T, true>), dim3(xcd_grid(d.np)), dim3(kPatchBlock), 0,
-                                                 st, d, par));
-    else
-        DVM_DISPATCH(d.mixed, hipLaunchKernelGGL((k_primal_sweep<T, false>), dim3(xcd_grid(d.np)), dim3(kPatchBlock), 0,
-                                                 st, d, par));
+    DVM_FLAG(d.order == 2, SO, DVM_FLAG(d.nt[0], NT, DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(
+        (k_primal_sweep<T, SO, NT>), dim3(xcd_grid(d.np)), dim3(kPatchBlock), primal_lds(d), st, d, par))));
     return hipGetLastError();
 }
 
@@ -1224,45 +1406,37 @@ hipError_t launch_eq_params_group(const DevSolve *tab, const MacroGroup &g, int 
 
 hipError_t launch_adjoint_correct_moments(const DevSolve &d, int par, const double *z, hipStream_t st)
 {
-    DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(k_adjoint_correct_moments<T>, dim3(xcd_grid(d.np)), dim3(kPatchBlock), 0,
-                                             st, d, par, z));
+    DVM_DISPATCH(d.mixed, hipLaunchKernelGGL((k_adjoint_moments<T, true>), dim3(xcd_grid(d.np)), dim3(kPatchBlock),
+                                             adjoint_lds(d), st, d, par, z));
     return hipGetLastError();
 }
 
 hipError_t launch_adjoint_moments(const DevSolve &d, int par, hipStream_t st)
 {
-    DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(k_adjoint_moments<T>, dim3(xcd_grid(d.np)), dim3(kPatchBlock), 0, st, d,
-                                             par));
+    DVM_DISPATCH(d.mixed, hipLaunchKernelGGL((k_adjoint_moments<T, false>), dim3(xcd_grid(d.np)), dim3(kPatchBlock),
+                                             adjoint_lds(d), st, d, par, nullptr));
     return hipGetLastError();
 }
 
-hipError_t launch_adjoint_sweep(const DevSolve &d, int par, hipStream_t st)
+hipError_t launch_adjoint_sweep(const DevSolve &d, int par, int res, hipStream_t st)
 {
-    if (d.order == 2)
-        DVM_DISPATCH(d.mixed, hipLaunchKernelGGL((k_adjoint_sweep<T, true>), dim3(xcd_grid(d.np)), dim3(kPatchBlock), 0,
-                                                 st, d, par));
-    else
-        DVM_DISPATCH(d.mixed, hipLaunchKernelGGL((k_adjoint_sweep<T, false>), dim3(xcd_grid(d.np)), dim3(kPatchBlock), 0,
-                                                 st, d, par));
+    DVM_FLAG(d.order == 2, SO, DVM_FLAG(d.nt[1], NT, DVM_FLAG(res, RES, DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(
+        (k_adjoint_sweep<T, SO, NT, RES>), dim3(xcd_grid(d.np)), dim3(kPatchBlock), adjoint_lds(d), st, d, par)))));
     return hipGetLastError();
 }
 
 hipError_t launch_batch(const DevSolve *tab, const int32_t *blk_solve, const int32_t *blk_patch,
-                        const int32_t *par0, int step, int nblocks, int mixed, int adjoint, int so, hipStream_t st)
+                        const int32_t *par0, int step, const BatchLaunch &g, int res, hipStream_t st)
 {
-    if (nblocks <= 0) return hipSuccess;
-    if (adjoint && so)
-        DVM_DISPATCH(mixed, hipLaunchKernelGGL((k_batch_adjoint<T, true>), dim3(nblocks), dim3(kPatchBlock), 0, st,
-                                               tab, blk_solve, blk_patch, par0, step));
-    else if (adjoint)
-        DVM_DISPATCH(mixed, hipLaunchKernelGGL((k_batch_adjoint<T, false>), dim3(nblocks), dim3(kPatchBlock), 0, st,
-                                               tab, blk_solve, blk_patch, par0, step));
-    else if (so)
-        DVM_DISPATCH(mixed, hipLaunchKernelGGL((k_batch_primal<T, true>), dim3(nblocks), dim3(kPatchBlock), 0, st,
-                                               tab, blk_solve, blk_patch, par0, step));
+    if (g.blocks <= 0) return hipSuccess;
+    if (g.adjoint)
+        DVM_FLAG(g.so, SO, DVM_FLAG(g.nt, NT, DVM_FLAG(res, RES, DVM_DISPATCH(g.mixed, hipLaunchKernelGGL(
+            (k_batch_adjoint<T, SO, NT, RES>), dim3(g.blocks), dim3(kPatchBlock), g.lds, st, tab, blk_solve, blk_patch,
+            par0, step)))));
     else
-        DVM_DISPATCH(mixed, hipLaunchKernelGGL((k_batch_primal<T, false>), dim3(nblocks), dim3(kPatchBlock), 0, st,
-                                               tab, blk_solve, blk_patch, par0, step));
+        DVM_FLAG(g.so, SO, DVM_FLAG(g.nt, NT, DVM_DISPATCH(g.mixed, hipLaunchKernelGGL(
+            (k_batch_primal<T, SO, NT>), dim3(g.blocks), dim3(kPatchBlock), g.lds, st, tab, blk_solve, blk_patch, par0,
+            step))));
     return hipGetLastError();
 }
 

@@ -35,33 +35,6 @@ namespace dvm {
 
 constexpr double kMacroCFL = 1000.0;
 
-// derivatives of (g1, g2) with respect to the equilibrium parameters
-// (rho, u1, u2, theta) at velocity (v1, v2), with g1 = kap X Y from the tables
-// (ir = 1/rho, it = 1/theta, ih = 1/(2 theta^2) of the cell, computed once)
-struct DgCell {
-    double kap, u1, u2, hth, ir, it, ih;
-};
-
-__device__ __forceinline__ DgCell dg_cell(const double *P)
-{
-    return {P[0] / (2.0 * kPi * P[3]), P[1], P[2], 0.5 * P[3], 1.0 / P[0], 1.0 / P[3], 1.0 / (2.0 * P[3] * P[3])};
-}
-
-__device__ __forceinline__ void dg_dP(const DgCell &q, double X, double Y, double v1, double v2, double &g1,
-                                      double &g2, double (&d1)[4], double (&d2)[4])
-{
-    const double c1 = v1 - q.u1, c2 = v2 - q.u2;
-    g1 = q.kap * X * Y;
-    g2 = q.hth * g1;
-    d1[0] = g1 * q.ir;
-    d1[1] = g1 * c1 * q.it;
-    d1[2] = g1 * c2 * q.it;
-    d1[3] = g1 * ((c1 * c1 + c2 * c2) * q.ih - q.it);
-#pragma unroll
-    for (int p = 0; p < 4; p++) d2[p] = q.hth * d1[p];
-    d2[3] += 0.5 * g1;
-}
-
 // this wave's 1-D factor tables X(v1), Y(v2) of the Maxwellian of state P
 __device__ __forceinline__ void macro_tables(const DevSolve &d, const double *P, double *X, double *Y)
 {
@@ -191,8 +164,8 @@ __global__ __launch_bounds__(kPatchCells * kWave) void k_macro_resid(DevSolve d,
 }
 
 // ---------------------------------------------------------------------------
-// the macroscopic blocks of each cell, two waves per cell (faces 0-1 and
-// 2-3), no distribution read: each face q gets its outflow block
+// the macroscopic blocks of each cell, one wave per cell, no distribution
+// read: each face q gets its outflow block
 //   B_cq = sum_{k: v.S_q > 0} w (v.S_q) Psi_k dg_c,k/dW,
 // and the cell's own block is D_c = sum_q B_cq + wall1 dF + lam I (wall1 dF:
 // the diffuse wall's re-emission of the outgoing flux; lam the pseudo-time
@@ -201,176 +174,217 @@ __global__ __launch_bounds__(kPatchCells * kWave) void k_macro_resid(DevSolve d,
 // through q' is c's inflow half-space through q and the sums agree term by
 // term).  The Gauss-Seidel steps read the neighbours' B instead of a
 // separate off-diagonal table.
+//
+// The sums factor on the tensor grid.  With g = kap X(v1) Y(v2), e = v - u and
+// ascending nodes, the velocities of a grid row b with v.S_q > 0 are the
+// columns from some a* on (S_x > 0) or before it, so a sum over the half
+// space of e1^p e2^r g is sum_b Y e2^r R_p(a*_b) with R_p the sums of X e1^p
+// from either end, tabulated once per cell.  B needs p + r <= 5 (s Psi dg:
+// degrees 1 + 2 + 2): 21 sums of n2 terms per face instead of 20 of n1 n2.
+// a* is found by bisection on the same rounded v.S_q > 0 as the sweeps'.
+// Vector instructions bound it: 256x128 cells with 64x64 velocities 1190 us
+// (one term per velocity) -> 148 us, 128x64 with 32x32 186 -> 36 us.
 // ---------------------------------------------------------------------------
-constexpr int kBlkCells = kBlock / (2 * kWave);
+constexpr int kBlkCells = kBlock / kWave;
+constexpr int kHalfMoments = 6;               // R_p, p = 0 .. 5
+
+inline unsigned blocks_lds(const DevSolve &d)
+{
+    return 8u * (d.n1 + kBlkCells * (2 * kHalfMoments * (d.n1 + 1) + 2 * d.n2));
+}
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_shift(double x)      // 0 where the lane has no source
+{
+    const long long u = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(u & 0xffffffffLL), CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, ROWS, 0xf, false);
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
+// inclusive scan over the wave
+__device__ __forceinline__ double wave_scan(double x)
+{
+    x += dpp_shift<0x111, 0xf>(x);             // row_shr 1, 2, 4, 8
+    x += dpp_shift<0x112, 0xf>(x);
+    x += dpp_shift<0x114, 0xf>(x);
+    x += dpp_shift<0x118, 0xf>(x);
+    x += dpp_shift<0x142, 0xa>(x);             // last lane of rows 0, 2 to rows 1, 3
+    x += dpp_shift<0x143, 0xc>(x);             // lane 31 to rows 2, 3
+    return x;
+}
+
+// sum over the 16 lanes of a row, in every one of them
+__device__ __forceinline__ double row_sum(double x)
+{
+    x += dpp_shift<0x128, 0xf>(x);             // lane ^ 8
+    x += dpp_shift<0x141, 0xf>(x);             // lane ^ 7
+    x += dpp_shift<0x4e, 0xf>(x);              // lane ^ 2
+    x += dpp_shift<0xb1, 0xf>(x);              // lane ^ 1
+    return x;
+}
+
+extern __shared__ __align__(16) double blocks_smem[];
 
 __global__ __launch_bounds__(kBlock) void k_macro_blocks(DevSolve d, int par)
 {
-    __shared__ double tabX[kBlkCells][kMaxN1D], tabY[kBlkCells][kMaxN1D];
-    __shared__ double vx[kMaxN1D], vy[kMaxN1D], wx[kMaxN1D], wy[kMaxN1D];
-    __shared__ double Dpart[kBlkCells][2][16];
-    const int wv = (int)(threadIdx.x / kWave), lane = threadIdx.x % kWave;
-    const int cl = wv >> 1, h = wv & 1;          // cell of the workgroup, half (faces 2h, 2h+1)
-    const int c0 = blockIdx.x * kBlkCells + cl;
-    const bool act = c0 < d.nc;                 // idle waves of the last workgroup only join the barriers
+    const int w = uni((int)(threadIdx.x / kWave)), lane = threadIdx.x % kWave;
+    const int n1 = d.n1, n2 = d.n2;
+    double *vx = blocks_smem;
+    double *half = vx + n1 + w * (2 * kHalfMoments * (n1 + 1) + 2 * n2);     // [from below, from above][a][p]
+    double *wY = half + 2 * kHalfMoments * (n1 + 1), *e2 = wY + n2;
+    const int c0 = uni((int)blockIdx.x * kBlkCells + w);
+    const bool act = c0 < d.nc;                 // idle waves of the last workgroup only join the barrier
     const int c = act ? c0 : d.nc - 1;
-    const int nv = d.nv, n1 = d.n1, n2 = d.n2;
     const double *ms = d.mstate + kEqState * c;
-    const double P[4] = {ms[0], ms[1], ms[2], ms[3]};
-    const DgCell qc = dg_cell(P);
-    const double hh = 0.5 / P[3];
-    for (int i = threadIdx.x; i < n1; i += kBlock) {
-        vx[i] = d.vx[i];
-        wx[i] = d.wx[i];
+    const double rhoP = uni(ms[0]), u1 = uni(ms[1]), u2 = uni(ms[2]), th = uni(ms[3]);
+    const double hh = 0.5 / th;
+    for (int i = threadIdx.x; i < n1; i += kBlock) vx[i] = d.vx[i];
+    for (int i = lane; i < n2; i += kWave) {
+        const double e = d.vy[i] - u2;
+        e2[i] = e;
+        wY[i] = d.wy[i] * exp(-e * e * hh);
     }
-    for (int i = threadIdx.x; i < n2; i += kBlock) {
-        vy[i] = d.vy[i];
-        wy[i] = d.wy[i];
-    }
-    // the cell's 1-D factor tables: X by the first wave of the cell, Y by the second
-    if (h == 0)
-        for (int i = lane; i < n1; i += kWave) {
-            const double e = d.vx[i] - P[1];
-            tabX[cl][i] = exp(-e * e * hh);
-        }
-    else
-        for (int i = lane; i < n2; i += kWave) {
-            const double e = d.vy[i] - P[2];
-            tabY[cl][i] = exp(-e * e * hh);
-        }
-    double Sx[2], Sy[2];
+    // R_p from below (columns < a) and from above (columns >= a), 64 columns
+    // at a time, the totals so far carried along
+    for (int dir = 0; dir < 2; dir++) {
+        double *tab = half + dir * kHalfMoments * (n1 + 1);
+        double carry[kHalfMoments];
 #pragma unroll
-    for (int t = 0; t < 2; t++) {
-        Sx[t] = d.S[8 * c + 2 * (2 * h + t)];
-        Sy[t] = d.S[8 * c + 2 * (2 * h + t) + 1];
-    }
-    const int nb0 = d.nbr[4 * c];
-    const int wl = (h == 0 && nb0 <= -2) ? -2 - nb0 : -1;     // the wall face is face 0
-    const double Dw = wl >= 0 ? d.D[wl] : 1.0;
-    const double n1w = wl >= 0 ? d.wall_n[2 * wl] : 0.0, n2w = wl >= 0 ? d.wall_n[2 * wl + 1] : 0.0;
-    const double thw2 = 0.5 * d.theta_w;
-    const double *gMd = static_cast<const double *>(d.gM);
-    const float *gMf = static_cast<const float *>(d.gM);
-    __syncthreads();
-    // Bp: B of the two faces in dg/dP form (2 x 16)
-    double Bp[32];
+        for (int p = 0; p < kHalfMoments; p++) carry[p] = 0;
+        if (lane < kHalfMoments) tab[(dir ? n1 : 0) * kHalfMoments + lane] = 0;
+        for (int i0 = 0; i0 < n1; i0 += kWave) {
+            const int i = i0 + lane, a = dir ? n1 - 1 - i : i;
+            const bool in = i < n1;
+            const double e = in ? d.vx[a] - u1 : 0.0;
+            double t = in ? d.wx[a] * exp(-e * e * hh) : 0.0;
 #pragma unroll
-    for (int i = 0; i < 32; i++) Bp[i] = 0.0;
-    for (int k = lane; k < nv; k += kWave) {
-        const int a = k % n1, b = k / n1;
-        const double v1 = vx[a], v2 = vy[b], wt = wx[a] * wy[b];
-        const double psi[4] = {1.0, v1, v2, 0.5 * (v1 * v1 + v2 * v2)};
-        double g1, g2, d1[4], d2[4];
-        dg_dP(qc, tabX[cl][a], tabY[cl][b], v1, v2, g1, g2, d1, d2);
-        const double s0 = v1 * Sx[0] + v2 * Sy[0], s1 = v1 * Sx[1] + v2 * Sy[1];
-        // B_q[x][p] += w s Psi_x dg1/dP_p (+ w s dg2/dP_p in row x = 3) for
-        // each outflow face, as fused multiply-adds on (w s Psi_x)
-#pragma unroll
-        for (int t = 0; t < 2; t++) {
-            const double st = t == 0 ? s0 : s1;
-            if (st > 0) {
-                const double ws = wt * st;
-                double *Bq = Bp + 16 * t;
-#pragma unroll
-                for (int x = 0; x < 4; x++) {
-                    const double wsp = ws * psi[x];
-#pragma unroll
-                    for (int p = 0; p < 4; p++) Bq[4 * x + p] = fma(wsp, d1[p], Bq[4 * x + p]);
-                }
-#pragma unroll
-                for (int p = 0; p < 4; p++) Bq[12 + p] = fma(ws, d2[p], Bq[12 + p]);
+            for (int p = 0; p < kHalfMoments; p++) {
+                const double sum = wave_scan(t) + carry[p];
+                if (in) tab[(dir ? a : a + 1) * kHalfMoments + p] = sum;
+                carry[p] = __shfl(sum, kWave - 1, kWave);
+                t *= e;
             }
         }
     }
-    wave_sum<32>(Bp);
-    const double *M = ms + 4;
-    if (act && lane == 0) {
-        // this half's faces: B_q = Bp_q M into the table, and their share of D
-        double Dm[16];
+    // lanes 16 q + i: face q, grid rows i, i + 16, ...
+    const int q = lane >> 4;
+    const double Sx = d.S[8 * c + 2 * q], Sy = d.S[8 * c + 2 * q + 1];
+    __syncthreads();
+    double M[21];                               // sums of e1^p e2^r over the face's outflow half-space
 #pragma unroll
-        for (int i = 0; i < 16; i++) Dm[i] = 0.0;
-#pragma unroll
-        for (int t = 0; t < 2; t++) {
-            const double *Bq = Bp + 16 * t;
-            double *Bo = d.mO + 64 * c + 16 * (2 * h + t);
-#pragma unroll
-            for (int x = 0; x < 4; x++)
-#pragma unroll
-                for (int m = 0; m < 4; m++) {
-                    const double v = ((Bq[4 * x] * M[m] + Bq[4 * x + 1] * M[4 + m]) + Bq[4 * x + 2] * M[8 + m]) +
-                                     Bq[4 * x + 3] * M[12 + m];
-                    Bo[4 * x + m] = v;
-                    Dm[4 * x + m] += v;
-                }
+    for (int i = 0; i < 21; i++) M[i] = 0;
+    int bits = 0;
+    while ((1 << bits) <= n1) bits++;
+    for (int b = lane & 15; b < n2; b += 16) {
+        // columns [0, a) with v.S <= 0 (S_x > 0: outflow from above) or > 0 (from below)
+        const double sy = d.vy[b] * Sy;
+        int lo = 0, hi = n1;
+        for (int t = 0; t < bits; t++) {
+            const int mid = (lo + hi) >> 1;
+            const bool pos = vx[min(mid, n1 - 1)] * Sx + sy > 0;
+            if (lo < hi) {
+                if (pos == (Sx > 0))
+                    hi = mid;
+                else
+                    lo = mid + 1;
+            }
         }
+        const double *R = half + ((Sx > 0 ? n1 + 1 : 0) + lo) * kHalfMoments;
+        double yr = wY[b];
+        const double e = e2[b];
+        int k = 0;
 #pragma unroll
-        for (int i = 0; i < 16; i++) Dpart[cl][h][i] = Dm[i];
+        for (int r = 0; r < kHalfMoments; r++) {
+#pragma unroll
+            for (int p = 0; p + r < kHalfMoments; p++) {
+                M[k] = fma(yr, R[p], M[k]);
+                k++;
+            }
+            yr *= e;
+        }
     }
-    // the wall face (face 0, first wave of a wall cell), in a loop of its
-    // own so that the face sums above need not stay live beside its sums:
-    // where the face is inflow, the diffuse value's response wall1; the
-    // outgoing flux's response dF (dg/dP form)
-    if (wl >= 0) {
-        double wacc[8];
 #pragma unroll
-        for (int i = 0; i < 8; i++) wacc[i] = 0.0;
-        double *wall1 = wacc, *dFp = wacc + 4;
-        for (int k = lane; k < nv; k += kWave) {
+    for (int i = 0; i < 21; i++) M[i] = row_sum(M[i]);
+    // K_ij = sum w s g phi_i phi_j with phi = (1, e1, e2, |e|^2/2), s = S.e + S.u:
+    // m(p, r) the sum of e1^p e2^r, sm that of s e1^p e2^r
+    const double kap = rhoP / (2.0 * kPi * th), su = fma(Sx, u1, Sy * u2);
+    auto m = [&](int p, int r) { return M[6 * r - r * (r - 1) / 2 + p]; };
+    auto sm = [&](int p, int r) { return kap * fma(Sx, m(p + 1, r), fma(Sy, m(p, r + 1), su * m(p, r))); };
+    double K[4][4];
+    K[0][0] = sm(0, 0);
+    K[0][1] = K[1][0] = sm(1, 0);
+    K[0][2] = K[2][0] = sm(0, 1);
+    K[1][1] = sm(2, 0);
+    K[1][2] = K[2][1] = sm(1, 1);
+    K[2][2] = sm(0, 2);
+    K[0][3] = K[3][0] = 0.5 * (K[1][1] + K[2][2]);
+    K[1][3] = K[3][1] = 0.5 * (sm(3, 0) + sm(1, 2));
+    K[2][3] = K[3][2] = 0.5 * (sm(2, 1) + sm(0, 3));
+    K[3][3] = 0.25 * (sm(4, 0) + 2.0 * sm(2, 2) + sm(0, 4));
+    // entry (x, mm) of B_cq in lane 16 q + 4 x + mm:
+    // B = T K D dP/dW, Psi = T phi, dg1/dP = g phi D, and dg2/dP = th/2 dg1/dP + (0, 0, 0, g/2)
+    // in the energy row
+    const int x = (lane >> 2) & 3, mm = lane & 3;
+    const double uu = 0.5 * (u1 * u1 + u2 * u2);
+    const double t0 = x == 0 ? 1.0 : x == 1 ? u1 : x == 2 ? u2 : uu + 0.5 * th;
+    const double t1 = x == 1 ? 1.0 : x == 3 ? u1 : 0.0, t2 = x == 2 ? 1.0 : x == 3 ? u2 : 0.0, t3 = x == 3 ? 1.0 : 0.0;
+    double TK[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) TK[j] = fma(t0, K[0][j], fma(t1, K[1][j], fma(t2, K[2][j], t3 * K[3][j])));
+    const double ith = 1.0 / th;
+    const double Bp[4] = {TK[0] / rhoP, TK[1] * ith, TK[2] * ith,
+                          (TK[3] * ith - TK[0]) * ith + 0.5 * t3 * K[0][0]};
+    double Be = 0;
+#pragma unroll
+    for (int p = 0; p < 4; p++) Be = fma(Bp[p], ms[4 + 4 * p + mm], Be);
+    if (act) d.mO[64 * c + lane] = Be;
+    // own block: the faces' sum, the wall's response and the pseudo-time term V/dt
+    double De = Be + __shfl_xor(Be, 16, kWave);
+    De += __shfl_xor(De, 32, kWave);
+    const int nb0 = uni(d.nbr[4 * c]);
+    if (nb0 <= -2) {
+        // wall cell: where the wall face is inflow, the diffuse value's
+        // response; the outgoing flux's response is row 0 of B_c0 over A
+        const int wl = -2 - nb0;
+        const double S0x = uni(d.S[8 * c]), S0y = uni(d.S[8 * c + 1]), thw2 = 0.5 * d.theta_w, iD = 1.0 / d.D[wl];
+        const double *gMd = static_cast<const double *>(d.gM);
+        const float *gMf = static_cast<const float *>(d.gM);
+        double wall[4] = {0, 0, 0, 0};
+        for (int k = lane; k < d.nv; k += kWave) {
             const int a = k % n1, b = k / n1;
-            const double v1 = vx[a], v2 = vy[b], wt = wx[a] * wy[b];
-            const double psi[4] = {1.0, v1, v2, 0.5 * (v1 * v1 + v2 * v2)};
-            double g1, g2, d1[4], d2[4];
-            dg_dP(qc, tabX[cl][a], tabY[cl][b], v1, v2, g1, g2, d1, d2);
-            const double s = v1 * Sx[0] + v2 * Sy[0];
+            const double v1 = vx[a], v2 = d.vy[b], s = v1 * S0x + v2 * S0y;
             if (!(s > 0)) {
-                const double gb1 = (d.mixed ? (double)gMf[k] : gMd[k]) / Dw, gb2 = thw2 * gb1;
-#pragma unroll
-                for (int x = 0; x < 4; x++) wall1[x] += wt * s * (psi[x] * gb1 + (x == 3 ? gb2 : 0.0));
-            }
-            const double vn = v1 * n1w + v2 * n2w;
-            if (vn > 0) {
-#pragma unroll
-                for (int p = 0; p < 4; p++) dFp[p] += wt * vn * d1[p];
+                const double g = d.wx[a] * d.wy[b] * s * ((d.mixed ? (double)gMf[k] : gMd[k]) * iD);
+                wall[0] += g;
+                wall[1] = fma(g, v1, wall[1]);
+                wall[2] = fma(g, v2, wall[2]);
+                wall[3] = fma(g, fma(0.5, fma(v1, v1, v2 * v2), thw2), wall[3]);
             }
         }
-        wave_sum<8>(wacc);
-        if (act && lane == 0) {
-#pragma unroll
-            for (int m = 0; m < 4; m++) {
-                const double dF = ((dFp[0] * M[m] + dFp[1] * M[4 + m]) + dFp[2] * M[8 + m]) + dFp[3] * M[12 + m];
-#pragma unroll
-                for (int x = 0; x < 4; x++) Dpart[cl][h][4 * x + m] += wall1[x] * dF;
-            }
-        }
+        wave_sum<4>(wall);
+        const double dF = __shfl(Be, mm, kWave) / d.wall_A[wl];
+        const double wx4 = x == 0 ? wall[0] : x == 1 ? wall[1] : x == 2 ? wall[2] : wall[3];
+        De = fma(wx4, dF, De);
     }
-    __syncthreads();
-    if (!act || h != 0 || lane != 0) return;
-    // D = both halves + the pseudo-time term V/dt of the cell, inverted
     const double *W = d.W[par] + 4 * c;
-    const double rho = W[0], u1 = W[1] / rho, u2 = W[2] / rho;
-    const double th = (2.0 / 3.0) * (W[3] / rho - 0.5 * (u1 * u1 + u2 * u2));
+    const double rho = W[0], w1 = W[1] / rho, w2 = W[2] / rho;
+    const double thW = (2.0 / 3.0) * (W[3] / rho - 0.5 * (w1 * w1 + w2 * w2));
     double sS = 0.0;
 #pragma unroll
-    for (int q = 0; q < 4; q++) sS += hypot(d.S[8 * c + 2 * q], d.S[8 * c + 2 * q + 1]);
-    const double lam = (sqrt(u1 * u1 + u2 * u2) + sqrt(5.0 / 3.0 * th)) * sS / kMacroCFL;
-    double Dm[4][4];
+    for (int f = 0; f < 4; f++) sS += hypot(d.S[8 * c + 2 * f], d.S[8 * c + 2 * f + 1]);
+    const double lam = (sqrt(w1 * w1 + w2 * w2) + sqrt(5.0 / 3.0 * thW)) * sS / kMacroCFL;
+    if (x == mm) De += lam;
+    // inverse: lane l solves for column l % 4
+    double A[4][4], rhs[4], col[4];
 #pragma unroll
-    for (int x = 0; x < 4; x++)
+    for (int i = 0; i < 4; i++) {
+        rhs[i] = i == mm ? 1.0 : 0.0;
 #pragma unroll
-        for (int m = 0; m < 4; m++) Dm[x][m] = Dpart[cl][0][4 * x + m] + Dpart[cl][1][4 * x + m] + (x == m ? lam : 0.0);
-    double *Di = d.mDinv + 16 * c;
-#pragma unroll
-    for (int b2 = 0; b2 < 4; b2++) {
-        double A[4][4], e[4] = {0, 0, 0, 0}, x[4];
-#pragma unroll
-        for (int i = 0; i < 4; i++)
-#pragma unroll
-            for (int j = 0; j < 4; j++) A[i][j] = Dm[i][j];
-        e[b2] = 1.0;
-        solve4(A, e, x);
-#pragma unroll
-        for (int a2 = 0; a2 < 4; a2++) Di[4 * a2 + b2] = x[a2];
+        for (int j = 0; j < 4; j++) A[i][j] = __shfl(De, 4 * i + j, kWave);
     }
+    solve4(A, rhs, col);
+    if (act && lane < 16) d.mDinv[16 * c + lane] = x == 0 ? col[0] : x == 1 ? col[1] : x == 2 ? col[2] : col[3];
 }
 
 // the face of cell n that faces cell c (n a face neighbour of c)
@@ -484,7 +498,7 @@ static hipError_t macro_system(const DevSolve &d, int par, bool with_r, hipStrea
                                                  st, d, par));
         if (hipError_t e = hipGetLastError()) return e;
     }
-    hipLaunchKernelGGL(k_macro_blocks, dim3((d.nc + kBlkCells - 1) / kBlkCells), dim3(kBlock), 0, st, d, par);
+    hipLaunchKernelGGL(k_macro_blocks, dim3((d.nc + kBlkCells - 1) / kBlkCells), dim3(kBlock), blocks_lds(d), st, d, par);
     return hipGetLastError();
 }
 

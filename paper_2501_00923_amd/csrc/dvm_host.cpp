@@ -1451,12 +1451,14 @@ int dvm_batch_create_static(dvm_solver *const *solvers, int n, void *hip_stream,
     return DVM_OK;
 }
 
-// append member m (nc cells, state buffer par) to a launch group
-static void group_add(dvm::MacroGroup &g, int m, int nc, int par)
+// append member m (solver s, state buffer par) to a launch group
+static void group_add(dvm::MacroGroup &g, int m, const dvm_solver &s, int par)
 {
     g.idx[g.n] = m;
     g.par[g.n] = par;
-    g.pre[g.n + 1] = g.pre[g.n] + nc;
+    g.ni[g.n] = s.ni;
+    g.nj[g.n] = s.nj;
+    g.pre[g.n + 1] = g.pre[g.n] + s.nc;
     g.n++;
 }
 
@@ -1499,7 +1501,7 @@ int dvm_batch_run(dvm_batch *b, int iters)
                 dvm_solver *s = b->members[m];
                 if (s->phase != 0 || s->equil != DVM_EQ_CONSERVATIVE) continue;
                 if (!s->dev.mstate) return fail(DVM_ESTATE, "no equilibrium parameter buffer");
-                group_add(g, m, s->nc, s->fpar ^ (it & 1));
+                group_add(g, m, *s, s->fpar ^ (it & 1));
                 if (g.n == dvm::kMacroGroup) {
                     HIP_OK(dvm::launch_eq_params_group(tab, g, 0, b->stream));
                     g.n = 0;
@@ -1531,8 +1533,8 @@ int dvm_batch_run(dvm_batch *b, int iters)
             for (int m : due[adj]) {
                 dvm_solver *s = b->members[m];
                 const int par = (adj ? s->ppar : s->fpar) ^ ((it + 1) & 1);
-                HIP_OK(adj ? dvm::launch_macro_adjoint_begin(s->dev, par, b->stream)
-                           : dvm::launch_macro_predict_begin(s->dev, par, b->stream));
+                HIP_OK(adj ? dvm::launch_macro_adjoint_begin(s->dev, par, s->acc_inner, b->stream)
+                           : dvm::launch_macro_predict_begin(s->dev, par, s->acc_inner, b->stream));
             }
             std::vector<int> inners;
             for (int m : due[adj])
@@ -1542,22 +1544,26 @@ int dvm_batch_run(dvm_batch *b, int iters)
                 dvm::MacroGroup g;
                 g.n = 0;
                 g.pre[0] = 0;
+                // the group's steps, then its members' finishing kernels
+                auto flush = [&]() -> int {
+                    int from = 0;
+                    HIP_OK(dvm::launch_macro_gs_group(tab, g, inner, adj, &from, b->stream));
+                    for (int a = 0; a < g.n; a++) {
+                        dvm_solver *s = b->members[g.idx[a]];
+                        HIP_OK(adj ? dvm::launch_macro_adjoint_end(s->dev, g.par[a], b->stream)
+                                   : dvm::launch_macro_predict_end(s->dev, g.par[a], from, b->stream));
+                    }
+                    g.n = 0;
+                    return DVM_OK;
+                };
                 for (int m : due[adj]) {
                     dvm_solver *s = b->members[m];
                     if (s->acc_inner != inner) continue;
-                    group_add(g, m, s->nc, 0);
-                    if (g.n == dvm::kMacroGroup) {
-                        HIP_OK(dvm::launch_macro_gs_group(tab, g, inner, adj, b->stream));
-                        g.n = 0;
-                    }
+                    group_add(g, m, *s, (adj ? s->ppar : s->fpar) ^ ((it + 1) & 1));
+                    if (g.n == dvm::kMacroGroup)
+                        if (int e = flush()) return e;
                 }
-                HIP_OK(dvm::launch_macro_gs_group(tab, g, inner, adj, b->stream));
-            }
-            for (int m : due[adj]) {
-                dvm_solver *s = b->members[m];
-                const int par = (adj ? s->ppar : s->fpar) ^ ((it + 1) & 1);
-                HIP_OK(adj ? dvm::launch_macro_adjoint_end(s->dev, par, b->stream)
-                           : dvm::launch_macro_predict_end(s->dev, par, b->stream));
+                if (int e = flush()) return e;
             }
         }
     }

@@ -16,8 +16,8 @@
 //      slow wake, a sonic region) from being amplified; stored as the
 //      inverse of each cell's own block and the outflow block of each face
 //      (the neighbours' inflow blocks);
-//   3. k_macro_rbgs: red-black block Gauss-Seidel half steps from dW = 0
-//      (colour (i + j) % 2 in mesh numbering, each half step reading one
+//   3. k_macro_prep, k_macro_gs: red-black block Gauss-Seidel half steps from
+//      dW = 0 (colour (i + j) % 2 in mesh numbering, each half step reading one
 //      array and writing the other);
 //   4. k_macro_apply: W += dW, limited so that rho and theta change by at
 //      most 20%: the next sweep relaxes towards the predicted moments.
@@ -28,6 +28,8 @@
 // lane, moment sums reduced across the wave in a fixed order.
 
 #include <math.h>
+
+#include <algorithm>
 
 #include "dvm_device.h"
 
@@ -397,65 +399,262 @@ __device__ __forceinline__ int back_face(const DevSolve &d, int n, int c)
     return qb;
 }
 
-// ---------------------------------------------------------------------------
-// one colour of a red-black block Gauss-Seidel step for cell c: on its colour
-// x_c = Dinv_c (-r_c - sum_q O_cq src_nbr), the rest copied.  The cell's four
-// components sit on four lanes (component a = lane % 4): each lane sums its
-// row of the neighbours' blocks, the lanes exchange the right-hand side and
-// each applies its row of D^-1, so a launch has four threads per cell (the
-// kernel is latency-bound: one thread per cell gives 2 waves per CU on
-// 32,768 cells).  All four lanes of a cell take the same branches; callers
-// launch whole cells.
-// ---------------------------------------------------------------------------
-static_assert(kBlock % 4 == 0, "the Gauss-Seidel launches keep a cell's four lanes in one workgroup");
-__device__ __forceinline__ void rbgs_cell(const DevSolve &d, int c, int a, int colour, const double *__restrict__ src,
-                                           double *__restrict__ dst)
+// The iteration blocks, in place of the face blocks B: 16 lanes per (cell,
+// face), lane 4 x + m its entry (x, m).
+//   primal   C_cq = Dinv_c B_nq' and r_c <- y_c = -Dinv_c r_c, so that a half
+//            step is x_c = y_c + sum_q C_cq x_n (-B_nq' is the inflow block of
+//            the neighbour n); the two blocks of a face trade places, taken
+//            by its lower-numbered cell
+//   adjoint  E_cq = (Dinv_n B_cq)^T, what cell n's update passes back to c
+// Boundary faces get zero blocks.
+template <bool ADJ>
+__global__ __launch_bounds__(kBlock) void k_macro_prep(DevSolve d)
 {
-    const int m = d.cell_of[c];
-    const int i = m % d.ni, j = m / d.ni;
-    if (((i + j) & 1) != colour) {
-        dst[4 * c + a] = src[4 * c + a];
-        return;
+    const int t = blockIdx.x * blockDim.x + threadIdx.x, item = t >> 4, e = t & 15, x = e >> 2, m = e & 3;
+    if (item >= 4 * d.nc) return;               // whole groups of 16 lanes
+    const int c = item >> 2, q = item & 3, n = d.nbr[4 * c + q];
+    double *B = d.mO + 64 * c + 16 * q;
+    if (n < 0) {
+        B[e] = 0.0;
+    } else if constexpr (ADJ) {
+        const double b = B[e], Dn = d.mDinv[16 * n + e];
+        double s = 0;
+#pragma unroll
+        for (int k = 0; k < 4; k++) s = fma(__shfl(Dn, 4 * m + k, 16), __shfl(b, 4 * k + x, 16), s);
+        B[e] = s;
+    } else if (c < n) {
+        double *Bn = d.mO + 64 * n + 16 * back_face(d, n, c);
+        const double bc = B[e], bn = Bn[e], Dc = d.mDinv[16 * c + e], Dn = d.mDinv[16 * n + e];
+        double sc = 0, sn = 0;
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            sc = fma(__shfl(Dc, 4 * x + k, 16), __shfl(bn, 4 * k + m, 16), sc);
+            sn = fma(__shfl(Dn, 4 * x + k, 16), __shfl(bc, 4 * k + m, 16), sn);
+        }
+        B[e] = sc;
+        Bn[e] = sn;
     }
-    double ba = -d.mr[4 * c + a];
-    for (int q = 0; q < 4; q++) {
-        const int n = d.nbr[4 * c + q];
-        if (n < 0) continue;
-        // the inflow block of n across face q is -B_nq'
-        const double *B = d.mO + 64 * n + 16 * back_face(d, n, c);
-#pragma unroll
-        for (int e = 0; e < 4; e++) ba += B[4 * a + e] * src[4 * n + e];
+    if (!ADJ && q == 0) {
+        const double p = d.mDinv[16 * c + e] * d.mr[4 * c + m];
+        double s = p + __shfl_xor(p, 1, 16);
+        s += __shfl_xor(s, 2, 16);
+        if (m == 0) d.mr[4 * c + x] = -s;       // all lanes of the group have read r
     }
-    double b[4];
-#pragma unroll
-    for (int e = 0; e < 4; e++) b[e] = __shfl(ba, e, 4);
-    const double *Di = d.mDinv + 16 * c;
-    double acc = 0;
-#pragma unroll
-    for (int e = 0; e < 4; e++) acc += Di[4 * a + e] * b[e];
-    dst[4 * c + a] = acc;
 }
 
-__global__ __launch_bounds__(kBlock) void k_macro_rbgs(DevSolve d, int colour, const double *__restrict__ src,
-                                                       double *__restrict__ dst)
+// device number of mesh cell (i, j) (the storage order of build_patches)
+__device__ __forceinline__ int device_cell(const DevSolve &d, int i, int j)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;     // 4 lanes per cell
-    if ((t >> 2) < d.nc) rbgs_cell(d, t >> 2, t & 3, colour, src, dst);
+    const int i0 = i - i % kTileI, j0 = j - j % kTileJ, wt = min(kTileI, d.ni - i0), ht = min(kTileJ, d.nj - j0);
+    const int ii = i - i0, jj = j - j0, pi = ii - ii % kPatchI, pj = jj - jj % kPatchJ;
+    const int wp = min(kPatchI, wt - pi), hp = min(kPatchJ, ht - pj);
+    return i0 * d.nj + wt * j0 + wt * pj + hp * pi + (jj - pj) * wp + (ii - pi);
 }
 
-// Several solves of a batch in one launch: a thread per cell of the
-// group's members in turn (member a owns cells pre[a] .. pre[a+1]-1), each
-// member's DevSolve read from the batch's table; the per-cell arithmetic
-// is the single-solve kernel's, so the results are bitwise the same.
-__global__ __launch_bounds__(kBlock) void k_macro_rbgs_group(const DevSolve *__restrict__ tab, MacroGroup g,
-                                                             int colour, int from)
+// ---------------------------------------------------------------------------
+// `steps` half steps of the red-black block Gauss-Seidel iteration in one
+// launch.  A workgroup owns a tile of the mesh and computes on a window of
+// kGsW x kGsH cells around it, `steps` cells wider on each side: after k half
+// steps the window's outer k cells are wrong, the tile is not.  A window
+// follows the mesh across the periodic seam and, mirrored, across the wake
+// cut; cells outside it or the mesh take part with nothing.  Four lanes per
+// pair of cells (one of each colour), lane a holding row a of the blocks in
+// registers, the iterates in LDS.
+//
+// Why: one half step a launch took 4.6 to 8 us, its launch and the chain
+// neighbour - back face - block, on any mesh up to 32768 cells; here a half
+// step costs two LDS reads a neighbour and a barrier, and the blocks are read
+// once per launch (measured figures at gs_steps).
+//
+// primal, colour on:  x_c = y_c + sum_q C_cq x_n
+// adjoint (the transposed half steps in reverse order), colour on:
+//   s_on += v_on, then v_m = (m off: v_m) + sum_{n on} E_mq v_n; after the
+//   last one z = -Dinv^T s.
+// Neighbours of one colour (an odd ni across the seam) read the old values.
+// ---------------------------------------------------------------------------
+constexpr int kGsW = 24, kGsH = 21, kGsBlock = 1024;
+static_assert(kGsW % 2 == 0 && 2 * kGsW * kGsH <= kGsBlock, "four lanes per pair of cells");
+
+template <bool ADJ>
+__device__ __forceinline__ void gs_tile(const DevSolve &d, int tile, const GsStep &st, const double *__restrict__ src,
+                                        double *__restrict__ dst)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;     // 4 lanes per cell
-    const int i = t >> 2;
-    if (i >= g.pre[g.n]) return;
-    const int a = group_member(g, i);
+    __shared__ __align__(16) double xs[4 * kGsW * kGsH];
+    const int g = threadIdx.x >> 2, a = threadIdx.x & 3;
+    const bool lane_in = g < kGsW * kGsH / 2;
+    const int tw = kGsW - 2 * st.steps, th = kGsH - 2 * st.steps, tiles_i = (d.ni + tw - 1) / tw;
+    const int i0 = (tile % tiles_i) * tw - st.steps, j0 = (tile / tiles_i) * th - st.steps;
+    const int wj = g / (kGsW / 2);
+    const bool odd = (d.ni & 1) != 0;           // neighbours of one colour
+    int cell[2], li[2], col[2], nl[2][4], same[2];
+    bool own[2];
+    double C[2][16], y[2], s[2] = {0, 0};
+#pragma unroll
+    for (int u = 0; u < 2; u++) {
+        const int wi = 2 * (g % (kGsW / 2)) + ((u ^ wj) & 1);
+        int i = i0 + wi, j = j0 + wj;
+        bool ok = lane_in && j < d.nj, mir = false;
+        own[u] = ok && i >= 0 && i < d.ni && j >= 0 && wi >= st.steps && wi < st.steps + tw && wj >= st.steps &&
+                 wj < st.steps + th;
+        if (d.topo == 0) {
+            ok = ok && j >= 0;
+            i %= d.ni;
+            if (i < 0) i += d.ni;
+        } else {
+            ok = ok && i >= 0 && i < d.ni;
+            if (j < 0) {
+                mir = true;
+                i = d.ni - 1 - i;
+                j = -1 - j;
+                ok = ok && j < d.nj;
+            }
+        }
+        li[u] = lane_in ? wj * kGsW + wi : 0;
+        cell[u] = ok ? device_cell(d, i, j) : -1;
+        col[u] = (i + j) & 1;
+        same[u] = 0;
+        const int sg = mir ? -1 : 1;
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const int di = sg * (q == 1 ? 1 : q == 3 ? -1 : 0), dj = sg * (q == 2 ? 1 : q == 0 ? -1 : 0);
+            const bool in = wi + di >= 0 && wi + di < kGsW && wj + dj >= 0 && wj + dj < kGsH;
+            nl[u][q] = in ? 4 * (li[u] + di + kGsW * dj) : 4 * li[u];
+        }
+        y[u] = 0;
+#pragma unroll
+        for (int k = 0; k < 16; k++) C[u][k] = 0;
+        double x0 = 0;
+        if (ok) {
+            const double *B = d.mO + 64 * (size_t)cell[u] + 4 * a;
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+#pragma unroll
+                for (int e = 0; e < 4; e++) C[u][4 * q + e] = B[16 * q + e];
+                if (odd) {
+                    const int n = d.nbr[4 * cell[u] + q];
+                    if (n >= 0) {
+                        const int mn = d.cell_of[n];
+                        if (((mn % d.ni + mn / d.ni) & 1) == col[u]) same[u] |= 1 << q;
+                    }
+                }
+            }
+            if (!ADJ) y[u] = d.mr[4 * cell[u] + a];
+            if (ADJ && own[u] && !st.first) s[u] = d.mr[4 * cell[u] + a];     // one running sum, whatever the launches
+            if (ADJ || !st.first) x0 = src[4 * cell[u] + a];
+        }
+        if (lane_in) xs[4 * li[u] + a] = x0;
+    }
+    __syncthreads();
+    for (int t = 0; t < st.steps; t++) {
+        const int on = (st.colour + t) & 1;
+        double nx[2];
+        bool set[2];
+#pragma unroll
+        for (int u = 0; u < 2; u++) {
+            const bool lit = col[u] == on;
+            // primal: cells of the colour; adjoint: the others (and, next to
+            // neighbours of their own colour, these too)
+            set[u] = cell[u] >= 0 && (ADJ || lit);
+            nx[u] = 0;
+            if (!set[u]) continue;
+            if (!ADJ) {
+                double acc = y[u];
+#pragma unroll
+                for (int q = 0; q < 4; q++)
+#pragma unroll
+                    for (int e = 0; e < 4; e++) acc = fma(C[u][4 * q + e], xs[nl[u][q] + e], acc);
+                nx[u] = acc;
+            } else {
+                const double v = xs[4 * li[u] + a];
+                double acc = lit ? 0.0 : v;
+                if (lit) s[u] += v;
+                if (!lit || same[u]) {
+#pragma unroll
+                    for (int q = 0; q < 4; q++) {
+                        if (odd && lit != (((same[u] >> q) & 1) != 0)) continue;
+#pragma unroll
+                        for (int e = 0; e < 4; e++) acc = fma(C[u][4 * q + e], xs[nl[u][q] + e], acc);
+                    }
+                }
+                nx[u] = acc;
+            }
+        }
+        if (ADJ || odd) __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 2; u++)
+            if (set[u]) xs[4 * li[u] + a] = nx[u];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int u = 0; u < 2; u++) {
+        if (!own[u]) continue;                  // whole groups of four lanes
+        const int at = 4 * cell[u] + a;
+        if (!ADJ || !st.last) dst[at] = xs[4 * li[u] + a];
+        if (ADJ) {
+            double sum = s[u];
+            if (st.last) {
+                const double *Di = d.mDinv + 16 * (size_t)cell[u];
+                double z = 0;
+#pragma unroll
+                for (int e = 0; e < 4; e++) z = fma(-Di[4 * e + a], __shfl(sum, e, 4), z);
+                sum = z;
+            }
+            d.mr[at] = sum;
+        }
+    }
+}
+
+template <bool ADJ>
+__global__ __launch_bounds__(kGsBlock) void k_macro_gs(DevSolve d, GsStep st, int tiles, int from)
+{
+    const int tile = xcd_item(tiles, blockIdx.x);
+    if (tile >= 0) gs_tile<ADJ>(d, tile, st, d.mx[from], d.mx[from ^ 1]);
+}
+
+// Several solves of a batch in one launch: member a owns tiles pre[a] ..
+// pre[a+1]-1 of the group.  The steps per launch may differ from a single
+// solve's; each cell's arithmetic does not, so the results are bitwise the
+// same.
+template <bool ADJ>
+__global__ __launch_bounds__(kGsBlock) void k_macro_gs_group(const DevSolve *__restrict__ tab, MacroGroup g, GsStep st,
+                                                             int from)
+{
+    const int item = xcd_item(g.pre[g.n], blockIdx.x);
+    if (item < 0) return;
+    const int a = group_member(g, item);
     const DevSolve &d = tab[g.idx[a]];
-    rbgs_cell(d, i - g.pre[a], t & 3, colour, d.mx[from], d.mx[from ^ 1]);
+    gs_tile<ADJ>(d, item - g.pre[a], st, d.mx[from], d.mx[from ^ 1]);
+}
+
+// Half steps per launch for meshes of ni[k] x nj[k] cells: more of them save
+// launches but leave smaller tiles of the fixed window; a launch of more
+// tiles than the chip has compute units takes another round of them (one
+// window's registers fill a unit).  The line fits launches measured at 2 to 8
+// half steps (6.1 to 8.4 us; 14.6 us in two rounds).  50 steps, primal /
+// adjoint us, with one launch a half step and here: 64x32 cells 433 / 517 ->
+// 110 / 133, 128x64 420 / 515 -> 105 / 135, 256x128 666 / 808 -> 167 / 202.
+static int gs_tiles(int ni, int nj, int steps)
+{
+    const int tw = kGsW - 2 * steps, th = kGsH - 2 * steps;
+    return ((ni + tw - 1) / tw) * ((nj + th - 1) / th);
+}
+
+static int gs_steps(const int *ni, const int *nj, int n, int total)
+{
+    int best = 1;
+    double cost = 0;
+    for (int steps = 1; steps <= kGsMaxSteps && steps <= total; steps++) {
+        int tiles = 0;
+        for (int k = 0; k < n; k++) tiles += gs_tiles(ni[k], nj[k], steps);
+        const int launches = (total + steps - 1) / steps, rounds = (tiles + 255) / 256;
+        const double c = launches * (1.5 + rounds * (3.8 + 0.45 * steps));
+        if (steps == 1 || c < cost) {
+            best = steps;
+            cost = c;
+        }
+    }
+    const int launches = (total + best - 1) / best;
+    return (total + launches - 1) / launches;
 }
 
 __global__ __launch_bounds__(kBlock) void k_macro_zero(double *x, int n)
@@ -502,29 +701,68 @@ static hipError_t macro_system(const DevSolve &d, int par, bool with_r, hipStrea
     return hipGetLastError();
 }
 
-hipError_t launch_macro_predict_begin(const DevSolve &d, int par, hipStream_t st)
+template <bool ADJ>
+static hipError_t macro_prep(const DevSolve &d, hipStream_t st)
+{
+    const int64_t threads = (int64_t)64 * d.nc;
+    hipLaunchKernelGGL(k_macro_prep<ADJ>, dim3((unsigned)((threads + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, d);
+    return hipGetLastError();
+}
+
+hipError_t launch_macro_predict_begin(const DevSolve &d, int par, int inner, hipStream_t st)
 {
     if (hipError_t e = macro_system(d, par, true, st)) return e;
+    if (hipError_t e = macro_prep<false>(d, st)) return e;
+    if (inner > 0) return hipSuccess;
     hipLaunchKernelGGL(k_macro_zero, dim3((4 * d.nc + kBlock - 1) / kBlock), dim3(kBlock), 0, st, d.mx[0], 4 * d.nc);
     return hipGetLastError();
 }
 
-hipError_t launch_macro_predict_end(const DevSolve &d, int par, hipStream_t st)
+hipError_t launch_macro_predict_end(const DevSolve &d, int par, int from, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_macro_apply, dim3((d.nc + kBlock - 1) / kBlock), dim3(kBlock), 0, st, d, par, d.mx[0]);
+    hipLaunchKernelGGL(k_macro_apply, dim3((d.nc + kBlock - 1) / kBlock), dim3(kBlock), 0, st, d, par, d.mx[from]);
     return hipGetLastError();
+}
+
+// the launches of `inner` steps; `go` launches one; the result is in buffer
+// (launches & 1)
+template <typename F>
+static hipError_t gs_launches(int total, int steps, int colour0, F go, int *from)
+{
+    int k = 0;
+    for (int done = 0; done < total; done += steps, k++) {
+        GsStep st;
+        st.steps = std::min(steps, total - done);
+        st.colour = (colour0 + done) & 1;
+        st.first = done == 0;
+        st.last = done + st.steps == total;
+        go(st, k & 1);
+        if (hipError_t e = hipGetLastError()) return e;
+    }
+    *from = k & 1;
+    return hipSuccess;
+}
+
+// The forward steps run colour 0 then 1 in each of `inner`; the transposed
+// ones the reverse, colour 1 first.
+static hipError_t gs_single(const DevSolve &d, int inner, int adjoint, int *from, hipStream_t st)
+{
+    *from = 0;
+    if (inner <= 0) return hipSuccess;
+    const int steps = gs_steps(&d.ni, &d.nj, 1, 2 * inner);
+    return gs_launches(2 * inner, steps, adjoint, [&](const GsStep &gs, int k) {
+        const int tiles = gs_tiles(d.ni, d.nj, gs.steps);
+        DVM_FLAG(adjoint, ADJ, hipLaunchKernelGGL(k_macro_gs<ADJ>, dim3(xcd_grid(tiles)), dim3(kGsBlock), 0, st, d, gs,
+                                                  tiles, k));
+    }, from);
 }
 
 hipError_t launch_macro_predict(const DevSolve &d, int par, int inner, hipStream_t st)
 {
-    const int gt = (4 * d.nc + kBlock - 1) / kBlock;          // k_macro_rbgs: 4 lanes per cell
-    if (hipError_t e = launch_macro_predict_begin(d, par, st)) return e;
-    for (int it = 0; it < inner; it++) {
-        hipLaunchKernelGGL(k_macro_rbgs, dim3(gt), dim3(kBlock), 0, st, d, 0, d.mx[0], d.mx[1]);
-        hipLaunchKernelGGL(k_macro_rbgs, dim3(gt), dim3(kBlock), 0, st, d, 1, d.mx[1], d.mx[0]);
-        if (hipError_t e = hipGetLastError()) return e;
-    }
-    return launch_macro_predict_end(d, par, st);
+    int from = 0;
+    if (hipError_t e = launch_macro_predict_begin(d, par, inner, st)) return e;
+    if (hipError_t e = gs_single(d, inner, 0, &from, st)) return e;
+    return launch_macro_predict_end(d, par, from, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -538,7 +776,7 @@ hipError_t launch_macro_predict(const DevSolve &d, int par, int inner, hipStream
 //   1. k_macro_adj_y: y = H^T (phi_s - phi) per cell, from the adjoint
 //      moments the two sweeps left (What and rho_tau are linear in phi):
 //      y = V (What_s - What) / tau - V (1/tau dtau/dW) (rho_tau,s - rho_tau);
-//   2. k_macro_rbgs_adj: z = L^T y, the Gauss-Seidel half steps transposed
+//   2. k_macro_gs<true>: z = L^T y, the Gauss-Seidel half steps transposed
 //      in reverse order;
 //   3. k_adjoint_correct_moments: phi_s -= (z . Psi, z_3) and the adjoint
 //      moments of the corrected phi, in one pass.
@@ -560,79 +798,18 @@ __global__ __launch_bounds__(kBlock) void k_macro_adj_y(DevSolve d, int pnew, do
     for (int m = 0; m < 4; m++) y[4 * c + m] = V * (itau * (an[m] - ao[m]) - ac[6 + m] * drt);
 }
 
-__device__ __forceinline__ bool macro_colour(const DevSolve &d, int c, int colour)
-{
-    const int m = d.cell_of[c];
-    return (((m % d.ni) + (m / d.ni)) & 1) == colour;
-}
-
-// one transposed half step of k_macro_rbgs (colour `colour`) for cell m: the
-// forward step set x_c = Dinv_c (-r_c - sum_q O_cq src_nbr) on its colour and
-// copied the rest; given the adjoint ob of its output, t_c = -Dinv_c^T ob_c
-// joins rbar on the colour, and the adjoint of its input is
-// ib_m = (m off the colour: ob_m) + sum_q O_nq'^T t_n over neighbours n on
-// the colour, where O_nq' (n's inflow block from m) is -B_mq.  Four lanes
-// per cell as in rbgs_cell: lane a computes component a of each t_n, the
-// lanes exchange t_n, and each accumulates its component of ib_m and rbar_m
-// (the sums in the order of one thread per cell: bitwise the same).
-__device__ __forceinline__ void rbgs_adj_cell(const DevSolve &d, int m, int a, int colour,
-                                              const double *__restrict__ ob, double *__restrict__ ib,
-                                              double *__restrict__ rbar)
-{
-    const bool on = macro_colour(d, m, colour);
-    double acc = on ? 0.0 : ob[4 * m + a];
-    for (int q = 0; q < 4; q++) {
-        const int n = d.nbr[4 * m + q];
-        if (n < 0 || !macro_colour(d, n, colour)) continue;
-        const double *Di = d.mDinv + 16 * n;
-        double s = 0;
-#pragma unroll
-        for (int e = 0; e < 4; e++) s += Di[4 * e + a] * ob[4 * n + e];
-        const double ta = -s;
-        double t[4];
-#pragma unroll
-        for (int e = 0; e < 4; e++) t[e] = __shfl(ta, e, 4);
-        const double *B = d.mO + 64 * m + 16 * q;
-#pragma unroll
-        for (int e = 0; e < 4; e++) acc -= B[4 * e + a] * t[e];
-    }
-    ib[4 * m + a] = acc;
-    if (on) {
-        const double *Di = d.mDinv + 16 * m;
-        double s = 0;
-#pragma unroll
-        for (int e = 0; e < 4; e++) s += Di[4 * e + a] * ob[4 * m + e];
-        rbar[4 * m + a] -= s;
-    }
-}
-
-__global__ __launch_bounds__(kBlock) void k_macro_rbgs_adj(DevSolve d, int colour, const double *__restrict__ ob,
-                                                           double *__restrict__ ib, double *__restrict__ rbar)
-{
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;     // 4 lanes per cell
-    if ((t >> 2) < d.nc) rbgs_adj_cell(d, t >> 2, t & 3, colour, ob, ib, rbar);
-}
-
-__global__ __launch_bounds__(kBlock) void k_macro_rbgs_adj_group(const DevSolve *__restrict__ tab, MacroGroup g,
-                                                                 int colour, int from)
-{
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;     // 4 lanes per cell
-    const int i = t >> 2;
-    if (i >= g.pre[g.n]) return;
-    const int a = group_member(g, i);
-    const DevSolve &d = tab[g.idx[a]];
-    rbgs_adj_cell(d, i - g.pre[a], t & 3, colour, d.mx[from], d.mx[from ^ 1], d.mr);
-}
-
 hipError_t launch_macro_adjoint_setup(const DevSolve &d, int fpar, hipStream_t st)
 {
-    return macro_system(d, fpar, false, st);
+    if (hipError_t e = macro_system(d, fpar, false, st)) return e;
+    return macro_prep<true>(d, st);
 }
 
-hipError_t launch_macro_adjoint_begin(const DevSolve &d, int pnew, hipStream_t st)
+hipError_t launch_macro_adjoint_begin(const DevSolve &d, int pnew, int inner, hipStream_t st)
 {
     const int gt = (d.nc + kBlock - 1) / kBlock;
     hipLaunchKernelGGL(k_macro_adj_y, dim3(gt), dim3(kBlock), 0, st, d, pnew, d.mx[0]);
+    if (hipError_t e = hipGetLastError()) return e;
+    if (inner > 0) return hipSuccess;
     hipLaunchKernelGGL(k_macro_zero, dim3((4 * d.nc + kBlock - 1) / kBlock), dim3(kBlock), 0, st, d.mr, 4 * d.nc);
     return hipGetLastError();
 }
@@ -645,35 +822,25 @@ hipError_t launch_macro_adjoint_end(const DevSolve &d, int pnew, hipStream_t st)
 
 hipError_t launch_macro_adjoint_predict(const DevSolve &d, int pnew, int inner, hipStream_t st)
 {
-    const int gt = (4 * d.nc + kBlock - 1) / kBlock;          // k_macro_rbgs_adj: 4 lanes per cell
-    if (hipError_t e = launch_macro_adjoint_begin(d, pnew, st)) return e;
-    // the forward steps ran it = 0 .. inner-1, colour 0 (x -> y) then 1
-    // (y -> x); here it = inner-1 .. 0, colour 1 (adjoint of x -> of y) then 0
-    for (int it = 0; it < inner; it++) {
-        hipLaunchKernelGGL(k_macro_rbgs_adj, dim3(gt), dim3(kBlock), 0, st, d, 1, d.mx[0], d.mx[1], d.mr);
-        hipLaunchKernelGGL(k_macro_rbgs_adj, dim3(gt), dim3(kBlock), 0, st, d, 0, d.mx[1], d.mx[0], d.mr);
-        if (hipError_t e = hipGetLastError()) return e;
-    }
+    int from = 0;
+    if (hipError_t e = launch_macro_adjoint_begin(d, pnew, inner, st)) return e;
+    if (hipError_t e = gs_single(d, inner, 1, &from, st)) return e;
     return launch_macro_adjoint_end(d, pnew, st);
 }
 
 // the Gauss-Seidel steps of a group of batch members with the same inner
-// count, one launch per half step for the whole group
-hipError_t launch_macro_gs_group(const DevSolve *tab, const MacroGroup &g, int inner, int adjoint, hipStream_t st)
+// count, in shared launches (g.ni, g.nj: the members' meshes)
+hipError_t launch_macro_gs_group(const DevSolve *tab, MacroGroup g, int inner, int adjoint, int *from, hipStream_t st)
 {
-    if (g.n <= 0) return hipSuccess;
-    const int gt4 = (4 * g.pre[g.n] + kBlock - 1) / kBlock;  // 4 lanes per cell
-    for (int it = 0; it < inner; it++) {
-        if (adjoint) {
-            hipLaunchKernelGGL(k_macro_rbgs_adj_group, dim3(gt4), dim3(kBlock), 0, st, tab, g, 1, 0);
-            hipLaunchKernelGGL(k_macro_rbgs_adj_group, dim3(gt4), dim3(kBlock), 0, st, tab, g, 0, 1);
-        } else {
-            hipLaunchKernelGGL(k_macro_rbgs_group, dim3(gt4), dim3(kBlock), 0, st, tab, g, 0, 0);
-            hipLaunchKernelGGL(k_macro_rbgs_group, dim3(gt4), dim3(kBlock), 0, st, tab, g, 1, 1);
-        }
-        if (hipError_t e = hipGetLastError()) return e;
-    }
-    return hipSuccess;
+    *from = 0;
+    if (g.n <= 0 || inner <= 0) return hipSuccess;
+    const int steps = gs_steps(g.ni, g.nj, g.n, 2 * inner);
+    return gs_launches(2 * inner, steps, adjoint, [&](const GsStep &gs, int k) {
+        g.pre[0] = 0;
+        for (int a = 0; a < g.n; a++) g.pre[a + 1] = g.pre[a] + gs_tiles(g.ni[a], g.nj[a], gs.steps);
+        DVM_FLAG(adjoint, ADJ, hipLaunchKernelGGL(k_macro_gs_group<ADJ>, dim3(xcd_grid(g.pre[g.n])), dim3(kGsBlock), 0,
+                                                  st, tab, g, gs, k));
+    }, from);
 }
 
 }  // namespace dvm

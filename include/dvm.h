@@ -156,7 +156,7 @@ int dvm_solver_set_scheme(dvm_solver *s, int order, int limiter, int correction_
  * discrete collision term does not conserve exactly.  DVM_EQ_CONSERVATIVE:
  * the reduced Maxwellian whose grid moments equal W exactly (its
  * parameters rho', u', theta' found by Newton's method from the primitive
- * variables, a fixed six steps, per cell and sweep); tau keeps the cell's
+ * variables, up to six steps, per cell and sweep); tau keeps the cell's
  * own rho and theta; the adjoint differentiates through the parameters
  * (dP'/dW = (dm/dP')^{-1}).  On grids whose quadrature of the Maxwellian
  * is off (Newton-Cotes, sinh-stretched) the pointwise iteration can diverge

@@ -1135,14 +1135,16 @@ __global__ void k_zero(T *p, size_t n)
         p[i] = (T)0;
 }
 
-// per-cell adjoint coefficients from the frozen moments, one wave per cell:
+// per-cell adjoint coefficients from the frozen moments, one thread per cell
+// (the conservative equilibrium's parameters and dP'/dW from mstate, where
+// k_eq_params has left them):
 // ac[0..3] the equilibrium's (rho, u1, u2, theta), ac[4] 1/tau (the cell's
 // own rho, theta), ac[5] rho/(2 pi theta) of the equilibrium, ac[6..9]
 // (1/tau) dtau/dW, ac[16..31] dP/dW (row = parameter, column = moment)
-__global__ __launch_bounds__(kBlock) void k_adjoint_coef(DevSolve d, const double *Wst)
+__global__ __launch_bounds__(kWave) void k_adjoint_coef(DevSolve d, const double *Wst)
 {
-    const int c = blockIdx.x * (kBlock / kWave) + (int)(threadIdx.x / kWave);
-    if (c >= d.nc) return;                      // whole waves; the kernel has no block barrier
+    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= d.nc) return;
     const double *W = Wst + 4 * c;
     const double rho = W[0], u1 = W[1] / rho, u2 = W[2] / rho, E = W[3] / rho;
     const double th = (2.0 / 3.0) * (E - 0.5 * (u1 * u1 + u2 * u2));
@@ -1153,15 +1155,17 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_coef(DevSolve d, const doubl
                  dth3 = k23 * ir;
     double P[4] = {rho, u1, u2, th}, M[16];
     if (d.equil) {
-        const double Wv[4] = {W[0], W[1], W[2], W[3]};
-        eq_conservative(d, Wv, P, M);
+        const double *ms = d.mstate + kEqState * c;
+#pragma unroll
+        for (int q = 0; q < 4; q++) P[q] = ms[q];
+#pragma unroll
+        for (int q = 0; q < 16; q++) M[q] = ms[4 + q];
     } else {
         const double J[16] = {1.0, 0.0, 0.0, 0.0, -u1 * ir, ir, 0.0, 0.0, -u2 * ir, 0.0, ir, 0.0,
                               dth0, dth1, dth2, dth3};
 #pragma unroll
         for (int q = 0; q < 16; q++) M[q] = J[q];
     }
-    if (threadIdx.x % kWave != 0) return;
     double *ac = d.acoef + kAcoef * c;
     ac[0] = P[0];
     ac[1] = P[1];
@@ -1333,8 +1337,9 @@ hipError_t launch_objective(const DevSolve &d, int par, hipStream_t st)
 
 hipError_t launch_adjoint_init(const DevSolve &d, int fpar, hipStream_t st)
 {
-    constexpr int per_block = kBlock / kWave;
-    hipLaunchKernelGGL(k_adjoint_coef, dim3((d.nc + per_block - 1) / per_block), dim3(kBlock), 0, st, d, d.W[fpar]);
+    if (d.equil)
+        if (hipError_t e = launch_eq_params(d, fpar, 1, st)) return e;
+    hipLaunchKernelGGL(k_adjoint_coef, dim3((d.nc + kWave - 1) / kWave), dim3(kWave), 0, st, d, d.W[fpar]);
     if (hipError_t e = hipGetLastError()) return e;
     const size_t n = (size_t)d.nc * d.nv * 2;
     if (d.mixed)

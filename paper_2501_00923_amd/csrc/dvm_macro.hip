@@ -688,11 +688,12 @@ __global__ __launch_bounds__(kBlock) void k_macro_apply(DevSolve d, int par, con
     for (int a = 0; a < 4; a++) W[a] += fac * x[4 * c + a];
 }
 
-// P' and dP'/dW of W[par], then the blocks; with_r: also the residual's moments
-static hipError_t macro_system(const DevSolve &d, int par, bool with_r, hipStream_t st)
+// primal: P' and dP'/dW of W[par], the residual's moments and the blocks;
+// adjoint: the blocks (the adjoint's start has left P' and dP'/dW)
+static hipError_t macro_system(const DevSolve &d, int par, bool primal, hipStream_t st)
 {
-    if (hipError_t e = launch_eq_params(d, par, 1, st)) return e;
-    if (with_r) {
+    if (primal) {
+        if (hipError_t e = launch_eq_params(d, par, 1, st)) return e;
         DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(k_macro_resid<T>, dim3(xcd_grid(d.np)), dim3(kPatchCells * kWave), 0,
                                                  st, d, par));
         if (hipError_t e = hipGetLastError()) return e;

@@ -32,7 +32,8 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0     # MI355X HBM3E, vendor figure
 # the sweep and second-order kernels, their layout constants and the host-built sweep order
 KERNEL_SRCS = [os.path.join(ROOT, "paper_2501_00923_amd", "csrc", f)
-               for f in ("dvm_kernels.hip", "dvm_so.hip", "dvm_device.h", "dvm_internal.h", "dvm_host.cpp")]
+               for f in ("dvm_kernels.hip", "dvm_walk.h", "dvm_so.hip", "dvm_device.h", "dvm_internal.h",
+                         "dvm_host.cpp")]
 # scaled FETCH_SIZE + WRITE_SIZE per launch of the sweeps, from the counter
 # runs of each workload (bench.py --workload c2 | c3)
 TRAFFIC_FILES = {"c2": os.path.join(ROOT, "profiles", "sweeps_naca0012_c256x128_v48_traffic.json"),

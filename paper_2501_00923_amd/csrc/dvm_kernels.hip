@@ -32,259 +32,9 @@
 #include <algorithm>
 #include <mutex>
 
-#include "dvm_device.h"
+#include "dvm_walk.h"
 
 namespace dvm {
-
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef unsigned u4 __attribute__((ext_vector_type(4)));
-typedef unsigned u2 __attribute__((ext_vector_type(2)));
-
-// Velocities per lane and step: two adjacent ones of a velocity-grid row in
-// FP32 with an even n1, so that a lane moves 16 bytes as in FP64.
-template <typename T>
-__device__ __forceinline__ bool pair_velocities(int n1)
-{
-    return sizeof(T) == 4 && (n1 & 1) == 0;
-}
-
-// ---------------------------------------------------------------------------
-// a wave's walk over one cell's velocities
-//
-// A lane stays on one column of the velocity grid (V adjacent ones) for a
-// whole walk down its rows (LaneMap of dvm_internal.h), so every factor of
-// v1 is a per-lane constant of the inner loop, and the sums over the rows
-// carry only the v2 factors (from LDS); the v1 factors join once per walk.
-// Compared with a column that changes every step this takes the vector
-// instructions per velocity from 100 to 72 (FP64 primal), 105 to 70 (FP32
-// primal), 168 to 88 (FP64 adjoint) and 142 to 85 (FP32 adjoint).
-// Lanes outside the grid run along on padded table entries (v = 1, weight 0)
-// and buffer accesses that the row's range check drops.
-// ---------------------------------------------------------------------------
-constexpr int kOutside = 0x40000000;            // byte offset past any row (rows have at most 256 KB)
-
-struct Walk {
-    int a, b, off;           // column, first row, byte offset there
-    bool in;                 // in the grid's columns
-};
-
-template <typename T, int V>
-__device__ __forceinline__ Walk make_walk(const DevSolve &d, int lane, int i)
-{
-    Walk w;
-    const int k = i * d.lm.ks + lane;
-    const int r = (int)(((float)k + 0.5f) * d.lm.inv_width), m = k - r * d.lm.width;
-    const bool idle = r >= d.lm.rows;
-    w.a = idle ? d.lm.n1p - V : V * (m + i * d.lm.as);
-    w.b = idle ? 0 : r;
-    w.in = !idle && w.a < d.n1;
-    w.off = w.in ? (r * d.n1 + w.a) * 2 * (int)sizeof(T) : kOutside;
-    return w;
-}
-
-// V velocities' two components
-template <typename T, int V>
-struct Vals {
-    T x[V], y[V];
-};
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void *p, int bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00027000);
-}
-
-// NT: non-temporal
-template <typename T, int V, bool NT>
-__device__ __forceinline__ Vals<T, V> row_load(__amdgpu_buffer_rsrc_t r, int off)
-{
-    Vals<T, V> o;
-    if constexpr (V * sizeof(T) == 8) {
-        const u4 v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, NT ? 2 : 0);
-        if constexpr (sizeof(T) == 8) {
-            o.x[0] = __longlong_as_double(((unsigned long long)v.y << 32) | v.x);
-            o.y[0] = __longlong_as_double(((unsigned long long)v.w << 32) | v.z);
-        } else {
-            o.x[0] = __uint_as_float(v.x);
-            o.y[0] = __uint_as_float(v.y);
-            o.x[1] = __uint_as_float(v.z);
-            o.y[1] = __uint_as_float(v.w);
-        }
-    } else {
-        const u2 v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, NT ? 2 : 0);
-        o.x[0] = __uint_as_float(v.x);
-        o.y[0] = __uint_as_float(v.y);
-    }
-    return o;
-}
-
-template <typename T, int V, bool NT>
-__device__ __forceinline__ void row_store(__amdgpu_buffer_rsrc_t r, int off, const Vals<T, V> &o)
-{
-    if constexpr (V * sizeof(T) == 8) {
-        u4 v;
-        if constexpr (sizeof(T) == 8) {
-            const unsigned long long a = __double_as_longlong(o.x[0]), b = __double_as_longlong(o.y[0]);
-            v = u4{(unsigned)a, (unsigned)(a >> 32), (unsigned)b, (unsigned)(b >> 32)};
-        } else {
-            v = u4{__float_as_uint(o.x[0]), __float_as_uint(o.y[0]), __float_as_uint(o.x[1]), __float_as_uint(o.y[1])};
-        }
-        __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, NT ? 2 : 0);
-    } else {
-        __builtin_amdgcn_raw_buffer_store_b64(u2{__float_as_uint(o.x[0]), __float_as_uint(o.y[0])}, r, off, 0, NT ? 2 : 0);
-    }
-}
-
-// Reciprocal: hardware estimate and Newton steps, two in FP64 (error about
-// one ulp) and one in FP32, where it is the correctly rounded 1 / x (checked
-// for every mantissa) at a third of the division's instructions.
-__device__ __forceinline__ double recip(double x)
-{
-    double r = __builtin_amdgcn_rcp(x);
-    double e = fma(-x, r, 1.0);
-    r = fma(r, e, r);
-    e = fma(-x, r, 1.0);
-    return fma(r, e, r);
-}
-__device__ __forceinline__ float recip(float x)
-{
-    const float r = __builtin_amdgcn_rcpf(x);
-    return fmaf(r, fmaf(-x, r, 1.0f), r);
-}
-
-// c + a b: fused in FP64, rounded twice in FP32, where the stored values
-// carry the rounding: FP32 results stay those of the plain expressions to the
-// last bit, so that a derivative's FP32 noise does not depend on the kernel
-__device__ __forceinline__ double madd(double a, double b, double c) { return fma(a, b, c); }
-__device__ __forceinline__ float madd(float a, float b, float c) { return c + a * b; }
-// keeps a per-lane constant in its register (the compiler would recompute the
-// product in every step)
-__device__ __forceinline__ void keep(double &x) { asm("" : "+v"(x)); }
-__device__ __forceinline__ void keep(float &x) { asm("" : "+v"(x)); }
-// the loads above are issued before any LDS read below (table entries read
-// late do not hold registers while the loads are in flight)
-__device__ __forceinline__ void loads_first() { asm volatile("" ::: "memory"); }
-__device__ __forceinline__ double min0(double x) { return fmin(x, 0.0); }
-__device__ __forceinline__ float min0(float x) { return fminf(x, 0.0f); }
-__device__ __forceinline__ double max0(double x) { return fmax(x, 0.0); }
-__device__ __forceinline__ float max0(float x) { return fmaxf(x, 0.0f); }
-
-// v2 factors of a grid row b, shared by a workgroup's cells: v2, w, w v2, w v2^2 / 2
-struct alignas(16) RowFactor {
-    double v, w, wv, wh;
-};
-// v1 factors of a column a: v1, w
-struct alignas(16) ColFactor {
-    double v, w;
-};
-// weighted Maxwellian factors of a grid row in one cell (adjoint moments):
-// e = w Y, e c2, e c2^2
-struct alignas(16) AdjRow {
-    double e, ec, ecc, pad;
-};
-
-// the workgroup's dynamic LDS (launch bytes: sweep_lds of dvm_internal.h)
-extern __shared__ __align__(16) unsigned char sweep_smem[];
-
-// The adjoint's sums of a thread over the walks before the current one, parked
-// in LDS so that the inner loop does not hold 12 registers for them (sum k of
-// a thread is a block's stride from the next: no bank conflicts).  256x128
-// cells with 256 velocities, FP64 / FP32: 108 / 70 -> 99 / 60 us.  The primal
-// keeps its four in registers: with fewer, more waves run at once and push
-// each other's neighbour rows out of L2 (128x64 cells with 4096 velocities in
-// FP64 234 -> 244 us).
-struct WalkSums {
-    double *p;
-    __device__ __forceinline__ WalkSums() : p(reinterpret_cast<double *>(sweep_smem) + threadIdx.x) {}
-    __device__ __forceinline__ double &operator[](int k) const { return p[k * kPatchCells * kWave]; }
-};
-
-// The workgroup's shared tables from byte `at` of its LDS.
-struct Factors {
-    RowFactor *row;
-    ColFactor *col;
-    void *end;
-    __device__ __forceinline__ Factors(const DevSolve &d, int at)
-    {
-        row = reinterpret_cast<RowFactor *>(sweep_smem + at);
-        col = reinterpret_cast<ColFactor *>(row + d.lm.n2p);
-        end = col + d.lm.n1p;
-    }
-    // padded past the grid with v = 1 and weight 0; all threads of the
-    // workgroup, no barrier
-    __device__ __forceinline__ void fill(const DevSolve &d) const
-    {
-        for (int i = threadIdx.x; i < d.lm.n2p + d.lm.n1p; i += kPatchCells * kWave) {
-            const bool first = i < d.lm.n2p;
-            const int k = first ? i : i - d.lm.n2p;
-            double v = 1.0, w = 0.0;
-            if (k < (first ? d.n2 : d.n1)) {
-                v = (first ? d.vy : d.vx)[k];
-                w = (first ? d.wy : d.wx)[k];
-            }
-            if (first) {
-                const double wv = w * v;
-                row[k] = {v, w, wv, 0.5 * (wv * v)};
-            } else {
-                col[k] = {v, w};
-            }
-        }
-    }
-};
-
-// ---------------------------------------------------------------------------
-// sums over the wave: lane l ends with the total of v[l / 8], by pairwise
-// exchanges that halve the number of values carried (34 vector instructions
-// for 8 values; a butterfly of each value takes 12 LDS exchanges per value).
-// The order is fixed and the same in every kernel that sums moments.
-// ---------------------------------------------------------------------------
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double x)
-{
-    const unsigned long long u = __double_as_longlong(x);
-    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, 0xf, 0xf, true);
-    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, true);
-    return __longlong_as_double(((unsigned long long)hi << 32) | lo);
-}
-
-template <int HALF>
-__device__ __forceinline__ double swap_add(double a, double b)
-{
-    const unsigned long long ua = __double_as_longlong(a), ub = __double_as_longlong(b);
-    u2 lo, hi;
-    if constexpr (HALF == 32) {
-        lo = __builtin_amdgcn_permlane32_swap((unsigned)ua, (unsigned)ub, false, false);
-        hi = __builtin_amdgcn_permlane32_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
-    } else {
-        lo = __builtin_amdgcn_permlane16_swap((unsigned)ua, (unsigned)ub, false, false);
-        hi = __builtin_amdgcn_permlane16_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
-    }
-    return __longlong_as_double(((unsigned long long)hi.x << 32) | lo.x) +
-           __longlong_as_double(((unsigned long long)hi.y << 32) | lo.y);
-}
-
-__device__ __forceinline__ double wave_scatter8(const double (&v)[8])
-{
-    double q[4], p[2];
-#pragma unroll
-    for (int i = 0; i < 4; i++) q[i] = swap_add<32>(v[i], v[i + 4]);
-#pragma unroll
-    for (int i = 0; i < 2; i++) p[i] = swap_add<16>(q[i], q[i + 2]);
-    const bool up = (threadIdx.x & 8) != 0;
-    double s = (up ? p[1] : p[0]) + dpp_move<0x128>(up ? p[0] : p[1]);     // lane ^ 8
-    s += dpp_move<0x141>(s);                                               // lane ^ 7
-    s += dpp_move<0x4e>(s);                                                // lane ^ 2
-    s += dpp_move<0xb1>(s);                                                // lane ^ 1
-    return s;
-}
-
-// value of a lane, the same in every lane
-__device__ __forceinline__ double lane_value(double x, int lane)
-{
-    const unsigned long long u = __double_as_longlong(x);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, lane);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), lane);
-    return __longlong_as_double(((unsigned long long)hi << 32) | lo);
-}
 
 // ---------------------------------------------------------------------------
 // FP64 moments of one cell: W (4) and the wall flux sum.  Per walk the
@@ -517,16 +267,6 @@ __device__ __forceinline__ void primal_cell(const DevSolve &d, int par, int c, b
         d.red[2 * c] = e0 * e0 + e1 * e1 + e2 * e2 + e3 * e3;
         d.red[2 * c + 1] = W0 * W0 + W1 * W1 + W2 * W2 + W3 * W3;
     }
-}
-
-// the wave's cell of patch p: its number, whether it exists (idle waves of a
-// partial patch run along on the first cell without storing)
-__device__ __forceinline__ int patch_wave(const DevSolve &d, int p, int &w, bool &act)
-{
-    w = uni((int)(threadIdx.x / kWave));
-    const int c0 = uni(d.patch[p]), cnt = uni(d.patch[p + 1]) - c0;
-    act = w < cnt;
-    return c0 + (act ? w : 0);
 }
 
 template <typename T, bool SO, bool NT>

@@ -445,42 +445,6 @@ __device__ __forceinline__ void adjoint_store(const DevSolve &d, double rho, dou
     if (act && wl >= 0 && lane == 0) Phi[wl] = -acc[6] / (d.wall_A[wl] * d.D[wl]);
 }
 
-// LDS tables of the adjoint kernels: the shared factors, then per cell the
-// weighted Maxwellian factors (adj, gx) and the source's v2 part (qb)
-template <typename T>
-struct AdjLds {
-    Factors fac;
-    AdjRow *adj;
-    double *gx;
-    T *qb;
-    __device__ __forceinline__ AdjLds(const DevSolve &d, int w) : fac(d, kWalkSums * (int)sizeof(double) * kPatchCells * kWave)
-    {
-        AdjRow *a0 = static_cast<AdjRow *>(fac.end);
-        double *g0 = reinterpret_cast<double *>(a0 + kPatchCells * d.lm.n2p);
-        T *q0 = reinterpret_cast<T *>(g0 + kPatchCells * d.lm.n1p);
-        adj = a0 + w * d.lm.n2p;
-        gx = g0 + w * d.lm.n1p;
-        qb = q0 + w * d.lm.n2p;
-    }
-    // this wave's Maxwellian factors of the frozen state; no barrier
-    __device__ __forceinline__ void fill(const DevSolve &d, const double *ac, int lane) const
-    {
-        const double u1 = uni(ac[1]), u2 = uni(ac[2]), h = 0.5 * recip(uni(ac[3])), gc = uni(ac[5]);
-        for (int i = lane; i < d.lm.n1p + d.lm.n2p; i += kWave) {
-            const bool first = i < d.lm.n1p;
-            const int k = first ? i : i - d.lm.n1p;
-            const bool in = k < (first ? d.n1 : d.n2);
-            const double c = in ? (first ? d.vx[k] - u1 : d.vy[k] - u2) : 0.0;
-            const double w = in ? (first ? d.wx[k] : d.wy[k]) : 0.0;
-            const double g = w * exp(-c * c * h);
-            if (first)
-                gx[k] = gc * g;
-            else
-                adj[k] = {g, g * c, g * c * c, 0.0};
-        }
-    }
-};
-
 // ---------------------------------------------------------------------------
 // adjoint sweep of one patch: eq. (numerad_gov) with the wall and far-field
 // conditions of eq. (formula_adjointbgk), Jacobi point-implicit:

@@ -52,6 +52,8 @@ def test_walk(n1, n2, precision, order):
         check_resid(ra, rao, "adjoint")
         assert _rel(s.state_array(dvm.STATE_PHI), o.phi) <= 1e-11
         check_sens(s.wall_sensitivity(), o.wall_sensitivity(), 1e-10)
+        if order == 1:
+            assert _rel(s.mesh_sensitivity(), o.mesh_sensitivity()) <= 1e-10
 
 
 @pytest.mark.parametrize("n1,n2", [(16, 5), (33, 10), (96, 10)])

@@ -80,11 +80,11 @@ __device__ __forceinline__ double uni(double x)
 // contiguous stretch of the sweep order (n items: cells or patches) so that
 // the neighbour rows a workgroup reads were fetched moments before by a
 // workgroup of the same XCD and are still in its L2.  Returns -1 for the
-// padding workgroups of the last stretch.
-__device__ __forceinline__ int xcd_item(int n, int b)
+// padding workgroups of the last stretch.  rev: each stretch from its end.
+__device__ __forceinline__ int xcd_item(int n, int b, int rev = 0)
 {
     const int per = (n + 7) >> 3;
-    const int idx = (b & 7) * per + (b >> 3);
+    const int idx = (b & 7) * per + (rev ? per - 1 - (b >> 3) : b >> 3);
     return idx < n ? idx : -1;
 }
 static inline int xcd_grid(int n) { return ((n + 7) >> 3) << 3; }

@@ -399,7 +399,7 @@ void fill_dev(dvm_solver &s)
     d.limiter = s.limiter;
     d.equil = s.equil;
     d.lm = dvm::lane_map(s.n1, s.n2, s.mixed);
-    for (int adj = 0; adj < 2; adj++) d.nt[adj] = sweep_bytes(s, adj) > dvm::kMallBytes;
+    for (int adj = 0; adj < 2; adj++) d.mem[adj] = dvm::sweep_memory(sweep_bytes(s, adj));
     d.nbr = at<int32_t>(s, s.off.nbr);
     d.patch = at<int32_t>(s, s.off.patch);
     d.cell_of = at<int32_t>(s, s.off.cell_of);
@@ -1307,7 +1307,7 @@ static void batch_groups(dvm_solver *const *solvers, int n, int mixed, const int
         bytes[g] += sweep_bytes(*s, g >> 1);
         group[g].lds = std::max(group[g].lds, g >> 1 ? dvm::adjoint_lds(s->dev) : dvm::primal_lds(s->dev));
     }
-    for (int g = 0; g < 4; g++) group[g].nt = bytes[g] > dvm::kMallBytes;
+    for (int g = 0; g < 4; g++) group[g].mem = dvm::sweep_memory(bytes[g]);
 }
 
 int dvm_batch_create(dvm_solver *const *solvers, int n, void *work_dev, size_t work_bytes, void *hip_stream,

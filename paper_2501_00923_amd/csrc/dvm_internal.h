@@ -90,15 +90,27 @@ inline LaneMap lane_map(int n1, int n2, int mixed)
     return best;
 }
 
-// A sweep whose rows (those of one cell-velocity array times the arrays it
-// touches) fit the 256 MiB memory-side cache (MALL) uses plain loads and
-// stores, a larger one non-temporal ones: copies of up to 128 MB per buffer
-// run at 8.2 TB/s with plain and 4.7 TB/s with non-temporal stores (which
-// bypass the MALL), larger ones at 5.1 TB/s either way, and there the sweeps
-// keep neighbour rows longer in L2 with non-temporal ones (FP64 primal and
-// adjoint of the 256x128 C-grid with 2304 velocities 496 and 733 against 507
-// and 762 us; of 128x64 cells with 1024 velocities 86 against 63 us).
-constexpr size_t kMallBytes = size_t(256) << 20;
+// How the rows of a sweep (of all arrays it touches) meet the 256 MiB
+// memory-side cache (MALL), which non-temporal stores bypass:
+//   keep    they fit: plain loads and stores (copies of up to 128 MB per
+//           buffer run at 8.2 TB/s with plain and 4.7 TB/s with non-temporal
+//           stores; 128x64 cells with 1024 velocities in FP64, primal: 57
+//           against 76 us)
+//   turn    they nearly fit: plain, and every other sweep runs backwards, so
+//           that it starts with the rows the last one ended with (256x128
+//           cells with 256 velocities in FP64, 268 and 403 MB: primal 67 ->
+//           58 us, adjoint 98 non-temporal -> 94 us)
+//   stream  non-temporal, so that neighbour rows stay longer in L2 (128x64
+//           cells with 4096 velocities in FP32, 537 MB: primal 136 against
+//           145 us; the 256x128 C-grid with 2304 velocities in FP64, 2.4 and
+//           3.6 GB: 489 and 695 against 501 and 717 us; running backwards
+//           every other time 491 and 700)
+enum { kMemKeep = 0, kMemTurn = 1, kMemStream = 2 };
+inline int sweep_memory(size_t bytes)
+{
+    constexpr size_t mib = size_t(1) << 20;
+    return bytes <= 224 * mib ? kMemKeep : bytes <= 448 * mib ? kMemTurn : kMemStream;
+}
 
 // Everything a kernel needs about one solve, passed by value (single solve)
 // or read from a device table (batched).  Pointers are device pointers into
@@ -114,7 +126,7 @@ struct DevSolve {
     int order;               // spatial order of the scheme: 1, or 2 (reconstructed face values)
     int equil;               // equilibrium: 0 pointwise Maxwellian, 1 discrete-conservative
     int limiter;             // order 2: 0 none, 1 Venkatakrishnan
-    int nt[2];               // primal, adjoint sweeps with non-temporal rows
+    int mem[2];              // sweep_memory of the primal and the adjoint
     LaneMap lm;
     // mesh
     const int32_t *nbr;      // [nc][4] (device cell numbering)
@@ -248,7 +260,7 @@ hipError_t launch_so_objective_elem(const DevSolve &d, int par, hipStream_t st);
 // creation; adjoint selects the kernel of that phase, so the scheme (the
 // blocks of one launch are members of one phase and one scheme)
 struct BatchLaunch {
-    int blocks = 0, mixed = 0, adjoint = 0, so = 0, nt = 0;
+    int blocks = 0, mixed = 0, adjoint = 0, so = 0, mem = 0;
     unsigned lds = 0;        // the largest member's
 };
 hipError_t launch_batch(const DevSolve *tab, const int32_t *blk_solve, const int32_t *blk_patch,

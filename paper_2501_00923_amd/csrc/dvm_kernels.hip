@@ -699,9 +699,9 @@ __device__ __forceinline__ void adjoint_moments_cell(const DevSolve &d, int par,
 constexpr int kPatchBlock = kPatchCells * kWave;   // threads of a patch workgroup
 
 template <typename T, bool SO, bool NT>
-__global__ __launch_bounds__(kPatchBlock) void k_primal_sweep(DevSolve d, int par)
+__global__ __launch_bounds__(kPatchBlock) void k_primal_sweep(DevSolve d, int par, int rev)
 {
-    const int p = xcd_item(d.np, blockIdx.x);
+    const int p = xcd_item(d.np, blockIdx.x, rev);
     if (p < 0) return;
     primal_patch<T, SO, NT>(d, p, par);
 }
@@ -721,9 +721,9 @@ __global__ __launch_bounds__(kPatchBlock) void k_moments(DevSolve d, int par)
 }
 
 template <typename T, bool SO, bool NT, bool RES>
-__global__ __launch_bounds__(kPatchBlock) void k_adjoint_sweep(DevSolve d, int par)
+__global__ __launch_bounds__(kPatchBlock) void k_adjoint_sweep(DevSolve d, int par, int rev)
 {
-    const int p = xcd_item(d.np, blockIdx.x);
+    const int p = xcd_item(d.np, blockIdx.x, rev);
     if (p < 0) return;
     adjoint_patch<T, SO, NT, RES>(d, p, par);
 }
@@ -751,22 +751,26 @@ template <typename T, bool SO, bool NT>
 __global__ __launch_bounds__(kPatchBlock) void k_batch_primal(const DevSolve *__restrict__ tab,
                                                               const int32_t *__restrict__ blk_solve,
                                                               const int32_t *__restrict__ blk_patch,
-                                                              const int32_t *__restrict__ par0, int step)
+                                                              const int32_t *__restrict__ par0, int step, int rev)
 {
-    const int s = blk_solve[blockIdx.x];
+    // rev: each XCD's column from its end
+    const int b = rev ? (int)(gridDim.x - 8 - blockIdx.x) + 2 * (int)(blockIdx.x & 7) : (int)blockIdx.x;
+    const int s = blk_solve[b];
     if (s < 0) return;
-    primal_patch<T, SO, NT>(tab[s], blk_patch[blockIdx.x], (par0[s] + step) & 1);
+    primal_patch<T, SO, NT>(tab[s], blk_patch[b], (par0[s] + step) & 1);
 }
 
 template <typename T, bool SO, bool NT, bool RES>
 __global__ __launch_bounds__(kPatchBlock) void k_batch_adjoint(const DevSolve *__restrict__ tab,
                                                                const int32_t *__restrict__ blk_solve,
                                                                const int32_t *__restrict__ blk_patch,
-                                                               const int32_t *__restrict__ par0, int step)
+                                                               const int32_t *__restrict__ par0, int step, int rev)
 {
-    const int s = blk_solve[blockIdx.x];
+    // rev: each XCD's column from its end
+    const int b = rev ? (int)(gridDim.x - 8 - blockIdx.x) + 2 * (int)(blockIdx.x & 7) : (int)blockIdx.x;
+    const int s = blk_solve[b];
     if (s < 0) return;
-    adjoint_patch<T, SO, NT, RES>(tab[s], blk_patch[blockIdx.x], (par0[s] + step) & 1);
+    adjoint_patch<T, SO, NT, RES>(tab[s], blk_patch[b], (par0[s] + step) & 1);
 }
 
 // Block tables of a batch on the device (the allocation-free batch): block
@@ -1002,7 +1006,7 @@ static inline int ew_grid(size_t n) { return (int)std::min<size_t>((n + kBlock -
 // f = far-field Maxwellian in every cell, with its moments and wall fluxes
 hipError_t launch_primal_init(const DevSolve &d, hipStream_t st)
 {
-    DVM_FLAG(d.nt[0], NT, DVM_DISPATCH(d.mixed, hipLaunchKernelGGL((k_moments<T, true, NT>), dim3(xcd_grid(d.np)),
+    DVM_FLAG(d.mem[0] == kMemStream, NT, DVM_DISPATCH(d.mixed, hipLaunchKernelGGL((k_moments<T, true, NT>), dim3(xcd_grid(d.np)),
                                                                    dim3(kPatchBlock), factor_lds(d.lm), st, d, 0)));
     return hipGetLastError();
 }
@@ -1016,8 +1020,9 @@ hipError_t launch_moments(const DevSolve &d, int par, hipStream_t st)
 
 hipError_t launch_primal_sweep(const DevSolve &d, int par, hipStream_t st)
 {
-    DVM_FLAG(d.order == 2, SO, DVM_FLAG(d.nt[0], NT, DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(
-        (k_primal_sweep<T, SO, NT>), dim3(xcd_grid(d.np)), dim3(kPatchBlock), primal_lds(d), st, d, par))));
+    const int rev = d.mem[0] == kMemTurn ? par & 1 : 0;
+    DVM_FLAG(d.order == 2, SO, DVM_FLAG(d.mem[0] == kMemStream, NT, DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(
+        (k_primal_sweep<T, SO, NT>), dim3(xcd_grid(d.np)), dim3(kPatchBlock), primal_lds(d), st, d, par, rev))));
     return hipGetLastError();
 }
 
@@ -1138,8 +1143,9 @@ hipError_t launch_adjoint_moments(const DevSolve &d, int par, hipStream_t st)
 
 hipError_t launch_adjoint_sweep(const DevSolve &d, int par, int res, hipStream_t st)
 {
-    DVM_FLAG(d.order == 2, SO, DVM_FLAG(d.nt[1], NT, DVM_FLAG(res, RES, DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(
-        (k_adjoint_sweep<T, SO, NT, RES>), dim3(xcd_grid(d.np)), dim3(kPatchBlock), adjoint_lds(d), st, d, par)))));
+    const int rev = d.mem[1] == kMemTurn ? par & 1 : 0;
+    DVM_FLAG(d.order == 2, SO, DVM_FLAG(d.mem[1] == kMemStream, NT, DVM_FLAG(res, RES, DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(
+        (k_adjoint_sweep<T, SO, NT, RES>), dim3(xcd_grid(d.np)), dim3(kPatchBlock), adjoint_lds(d), st, d, par, rev)))));
     return hipGetLastError();
 }
 
@@ -1147,14 +1153,15 @@ hipError_t launch_batch(const DevSolve *tab, const int32_t *blk_solve, const int
                         const int32_t *par0, int step, const BatchLaunch &g, int res, hipStream_t st)
 {
     if (g.blocks <= 0) return hipSuccess;
+    const int rev = g.mem == kMemTurn ? step & 1 : 0;
     if (g.adjoint)
-        DVM_FLAG(g.so, SO, DVM_FLAG(g.nt, NT, DVM_FLAG(res, RES, DVM_DISPATCH(g.mixed, hipLaunchKernelGGL(
+        DVM_FLAG(g.so, SO, DVM_FLAG(g.mem == kMemStream, NT, DVM_FLAG(res, RES, DVM_DISPATCH(g.mixed, hipLaunchKernelGGL(
             (k_batch_adjoint<T, SO, NT, RES>), dim3(g.blocks), dim3(kPatchBlock), g.lds, st, tab, blk_solve, blk_patch,
-            par0, step)))));
+            par0, step, rev)))));
     else
-        DVM_FLAG(g.so, SO, DVM_FLAG(g.nt, NT, DVM_DISPATCH(g.mixed, hipLaunchKernelGGL(
+        DVM_FLAG(g.so, SO, DVM_FLAG(g.mem == kMemStream, NT, DVM_DISPATCH(g.mixed, hipLaunchKernelGGL(
             (k_batch_primal<T, SO, NT>), dim3(g.blocks), dim3(kPatchBlock), g.lds, st, tab, blk_solve, blk_patch, par0,
-            step))));
+            step, rev))));
     return hipGetLastError();
 }
 

@@ -77,19 +77,25 @@ def test_reloaded_state_continues_bitwise(n1, n2, precision):
     assert np.array_equal(s.state_save(dvm.STATE_PHI), want)
 
 
-@pytest.mark.parametrize("ni,nj,n", [(128, 64, 32), (128, 128, 32)])
-def test_both_sides_of_the_cache_rule_agree_with_a_batch(ni, nj, n):
-    """A solve whose rows fit the memory-side cache alone but not in a batch
-    of many takes another store policy there: the bits stay the same."""
+@pytest.mark.parametrize("adjoint", [False, True])
+@pytest.mark.parametrize("ni,nj,n", [(64, 64, 32), (128, 64, 32), (128, 128, 32), (200, 129, 33)])
+def test_cache_rule_does_not_change_results(ni, nj, n, adjoint):
+    """Solves whose rows fit the memory-side cache, nearly fit it (every other
+    sweep backwards) and do not, alone and in a batch of four with another
+    rule: the bits stay the same."""
     wl = I.circle_case(ni, nj, n, 5.0, 0.8, 0.6)
-    one = dvm.Solver.from_workload(wl, want_adjoint=False)
-    many = [dvm.Solver.from_workload(wl, want_adjoint=False) for _ in range(4)]
+    one = dvm.Solver.from_workload(wl, want_adjoint=adjoint)
+    many = [dvm.Solver.from_workload(wl, want_adjoint=adjoint) for _ in range(4)]
+    which = dvm.STATE_PHI if adjoint else dvm.STATE_F
     for s in [one] + many:
         s.primal_init()
-    one.primal_sweeps(3)
+        if adjoint:
+            s.primal_sweeps(2)
+            s.adjoint_init()
+    (one.adjoint_sweeps if adjoint else one.primal_sweeps)(3)
     b = dvm.Batch(many)
     b.run(3)
     b.close()
-    want = one.state_save(dvm.STATE_F)
+    want = one.state_save(which)
     for s in many:
-        assert np.array_equal(s.state_save(dvm.STATE_F), want)
+        assert np.array_equal(s.state_save(which), want)

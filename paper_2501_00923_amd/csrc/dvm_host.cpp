@@ -399,7 +399,10 @@ void fill_dev(dvm_solver &s)
     d.limiter = s.limiter;
     d.equil = s.equil;
     d.lm = dvm::lane_map(s.n1, s.n2, s.mixed);
-    for (int adj = 0; adj < 2; adj++) d.mem[adj] = dvm::sweep_memory(sweep_bytes(s, adj));
+    for (int adj = 0; adj < 2; adj++) {
+        d.mem[adj] = dvm::sweep_memory(sweep_bytes(s, adj));
+        dvm::sweep_parts(s.nc, (s.np + 7) / 8, d.lm.total, s.mixed, d.mem[adj], d.parts[adj], d.tail[adj]);
+    }
     d.nbr = at<int32_t>(s, s.off.nbr);
     d.patch = at<int32_t>(s, s.off.patch);
     d.cell_of = at<int32_t>(s, s.off.cell_of);
@@ -1305,6 +1308,7 @@ static void batch_groups(dvm_solver *const *solvers, int n, int mixed, const int
         const dvm_solver *s = solvers[i];
         const int g = batch_group(s);
         bytes[g] += sweep_bytes(*s, g >> 1);
+        group[g].parts |= s->dev.parts[g >> 1] > 1;
         group[g].lds = std::max(group[g].lds, g >> 1 ? dvm::adjoint_lds(s->dev) : dvm::primal_lds(s->dev));
     }
     for (int g = 0; g < 4; g++) group[g].mem = dvm::sweep_memory(bytes[g]);

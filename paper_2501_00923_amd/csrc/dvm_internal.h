@@ -34,6 +34,7 @@ struct LaneMap {
     float inv_width;
     int isteps, tq, tr, brow;
     int n1p, n2p;            // LDS table sizes: columns and rows that some lane visits
+    int total;               // steps of a row
 };
 
 // Two shapes of walk.  "phase": the units in storage order, 64 a step; the
@@ -87,6 +88,7 @@ inline LaneMap lane_map(int n1, int n2, int mixed)
         best.n2p = bsteps * nb;
     }
     best.inv_width = 1.0f / best.width;
+    best.total = best.tq * best.isteps + best.tr;
     return best;
 }
 
@@ -112,6 +114,40 @@ inline int sweep_memory(size_t bytes)
     return bytes <= 224 * mib ? kMemKeep : bytes <= 448 * mib ? kMemTurn : kMemStream;
 }
 
+// Into how many parts a cell's row of `steps` steps is summed (SweepUnit in
+// dvm_walk.h), and how many of an XCD's `per` patches, the last ones, are
+// swept by one wave a part instead of one a cell.  Measured us, primal /
+// adjoint, one wave a cell against this:
+//  - few cells (a wave or two per SIMD of the chip): shorter chains of steps.
+//    FP64 32x16 cells with 24x24 velocities 9.7 / 11.6 -> 7.4 / 8.4, 64x32
+//    with 32x32 15.8 / 22.9 -> 15.4 / 20.1 (with 16x16 7.6 / 8.6 against 8.1
+//    / 9.0 in two parts: not worth it).
+//  - FP64 rows from memory: a quarter as many cells in flight, so more of
+//    their neighbours' rows are still in L2, and a shorter tail of last
+//    workgroups.  256x128 with 48x48 488 / 692 -> 468 / 660, with 64x64 sinh
+//    857 / 1219 -> 840 / 1145; 128x64 with 64x64 235 / 337 -> 230 / 309, with
+//    32x32 in two parts 57 / 95 -> 52 / 86.
+//  - FP32 rows from memory: the added set-up costs more than that (256x128
+//    with 64x64, all in parts 427 / 602 -> 478 / 634), but a launch of few
+//    long rows ends sooner with only its last patches in parts: 128x64 with
+//    64x64 136 / 200 -> 126 / 185.
+inline void sweep_parts(int nc, int per, int steps, int mixed, int mem, int &parts, int &tail)
+{
+    parts = 1;
+    tail = per;
+    if (nc <= 1024 && steps >= 8)
+        parts = 4;
+    else if ((nc <= 2048 && steps >= 8) || (nc <= 1024 && steps >= 4))
+        parts = 2;
+    else if (!mixed && (mem == kMemStream || (mem == kMemTurn && nc >= 8192)) && steps >= 14)
+        parts = steps >= 32 ? 4 : 2;
+    else if (mixed && mem == kMemStream && per <= 512 && steps >= 28) {
+        parts = 4;
+        tail = per < 96 ? per : 96;
+    }
+    if (parts == 1) tail = 0;
+}
+
 // Everything a kernel needs about one solve, passed by value (single solve)
 // or read from a device table (batched).  Pointers are device pointers into
 // the solver's workspace.  Storage type of f / phi / fd / gM is float in
@@ -127,6 +163,7 @@ struct DevSolve {
     int equil;               // equilibrium: 0 pointwise Maxwellian, 1 discrete-conservative
     int limiter;             // order 2: 0 none, 1 Venkatakrishnan
     int mem[2];              // sweep_memory of the primal and the adjoint
+    int parts[2], tail[2];   // sweep_parts of the primal and the adjoint
     LaneMap lm;
     // mesh
     const int32_t *nbr;      // [nc][4] (device cell numbering)
@@ -188,7 +225,9 @@ constexpr int kWalkSums = 6;
 inline unsigned factor_lds(const LaneMap &m) { return 32u * m.n2p + 16u * m.n1p; }
 inline unsigned primal_lds(const DevSolve &d)
 {
-    return factor_lds(d.lm) + kPatchCells * (d.lm.n1p + d.lm.n2p) * (d.mixed ? 4u : 8u);
+    const unsigned tables = factor_lds(d.lm) + kPatchCells * (d.lm.n1p + d.lm.n2p) * (d.mixed ? 4u : 8u);
+    const unsigned sums = d.parts[0] > 1 ? kPatchCells * kWave * 8u : 0u;   // join_parts
+    return tables > sums ? tables : sums;
 }
 inline unsigned adjoint_lds(const DevSolve &d)
 {
@@ -261,6 +300,7 @@ hipError_t launch_so_objective_elem(const DevSolve &d, int par, hipStream_t st);
 // blocks of one launch are members of one phase and one scheme)
 struct BatchLaunch {
     int blocks = 0, mixed = 0, adjoint = 0, so = 0, mem = 0;
+    int parts = 0;           // some member's rows are summed in parts
     unsigned lds = 0;        // the largest member's
 };
 hipError_t launch_batch(const DevSolve *tab, const int32_t *blk_solve, const int32_t *blk_patch,

@@ -45,14 +45,23 @@ namespace dvm {
 template <int V>
 struct Moments {
     double A[V], B[V], C[V], F; // of this walk; wall flux sum
-    double m[4];                // of the walks before
+    double m[4];                // of the part's walks before
+    double s;                   // wave totals of the parts before, moment lane / 8
 
     __device__ __forceinline__ void init()
     {
 #pragma unroll
         for (int i = 0; i < 4; i++) m[i] = 0;
-        F = 0;
+        F = s = 0;
         clear();
+    }
+    __device__ __forceinline__ void end_part()
+    {
+        const double in[8] = {m[0], m[1], m[2], m[3], F, 0, 0, 0};
+        s += wave_scatter8(in);
+#pragma unroll
+        for (int i = 0; i < 4; i++) m[i] = 0;
+        F = 0;
     }
     __device__ __forceinline__ void clear()
     {
@@ -98,12 +107,23 @@ struct Moments {
     // totals over the wave, in every lane
     __device__ __forceinline__ void total(double (&o)[5])
     {
-        const double in[8] = {m[0], m[1], m[2], m[3], F, 0, 0, 0};
-        const double s = wave_scatter8(in);
 #pragma unroll
         for (int i = 0; i < 5; i++) o[i] = lane_value(s, 8 * i);
     }
 };
+
+// Part sums s of the waves that share a cell, added in part order: s of the
+// first one (true) becomes the cell's.  All waves of the workgroup.
+__device__ __forceinline__ bool join_parts(const DevSolve &d, const SweepUnit &u, int lane, double &s)
+{
+    double *x = reinterpret_cast<double *>(sweep_smem) + u.slot * u.parts * kWave + lane;
+    __syncthreads();                            // the tables are done with
+    x[u.p0 * kWave] = s;
+    __syncthreads();
+    if (u.p0 == 0)
+        for (int p = 1; p < u.parts; p++) s += x[p * kWave];
+    return u.p0 == 0;
+}
 
 // ---------------------------------------------------------------------------
 // primal sweep of one patch: eq. (numerpr_gov), first-order upwind, Jacobi
@@ -112,12 +132,14 @@ struct Moments {
 // subtracted from the numerator and the wall flux is F + dF.
 // NT: rows are stored (and the held correction loaded) non-temporally.
 // ---------------------------------------------------------------------------
-template <typename T, int V, bool SO, bool NT>
-__device__ __forceinline__ void primal_cell(const DevSolve &d, int par, int c, bool act, int w, int lane)
+template <typename T, int V, bool SO, bool NT, bool PARTS>
+__device__ __forceinline__ void primal_cell(const DevSolve &d, int par, const SweepUnit &u, bool split, int lane)
 {
+    const int c = u.c;
+    const bool act = u.act;
     const Factors fac(d, 0);
     fac.fill(d);
-    T *ex = static_cast<T *>(fac.end) + w * (d.lm.n1p + d.lm.n2p), *ey = ex + d.lm.n1p;
+    T *ex = static_cast<T *>(fac.end) + u.slot * (d.lm.n1p + d.lm.n2p), *ey = ex + d.lm.n1p;
 
     const double *Win = d.W[par] + 4 * c;
     const double W0 = uni(Win[0]), W1 = uni(Win[1]), W2 = uni(Win[2]), W3 = uni(Win[3]);
@@ -136,7 +158,7 @@ __device__ __forceinline__ void primal_cell(const DevSolve &d, int par, int c, b
     }
     const double ith = recip(Pe[3]), h = 0.5 * ith;
     // Maxwellian factors: g1 = gc ex[a] ey[b]
-    for (int i = lane; i < d.lm.n1p + d.lm.n2p; i += kWave) {
+    for (int i = u.fill0; i < d.lm.n1p + d.lm.n2p; i += u.fill_step) {
         const bool first = i < d.lm.n1p;
         const int k = first ? i : i - d.lm.n1p;
         double g = 0;
@@ -184,9 +206,9 @@ __device__ __forceinline__ void primal_cell(const DevSolve &d, int par, int c, b
 
     Moments<V> mom;
     mom.init();
-    for (int i = 0; i < d.lm.isteps; i++) {
+    walk_parts<PARTS>(d.lm, u.p0, u.p1, u.parts, [&](int i, int t0, int steps) {
         const Walk wk = make_walk<T, V>(d, lane, i);
-        const int a = wk.a, steps = d.lm.tq + (i < d.lm.tr ? 1 : 0);
+        const int a = wk.a;
         const ColFactor *col = fac.col + a;
         T sx[4][V], e1[V];
 #pragma unroll
@@ -200,7 +222,7 @@ __device__ __forceinline__ void primal_cell(const DevSolve &d, int par, int c, b
                 keep(sx[q][v]);
             }
         }
-        int off = wk.off, b = wk.b;
+        int off = wk.off + t0 * bstep, b = wk.b + t0 * d.lm.brow;
         for (int t = 0; t < steps; t++, b += d.lm.brow, off += bstep) {
             const T v2 = (T)fac.row[b].v;
             T s[4][V];
@@ -253,7 +275,8 @@ __device__ __forceinline__ void primal_cell(const DevSolve &d, int par, int c, b
             if (wl >= 0) mom.add_wall(rf, col, S0x, S0y, r);
         }
         mom.fold(col);
-    }
+    }, [&] { mom.end_part(); });
+    if (PARTS && split && !join_parts(d, u, lane, mom.s)) return;
     double acc[5];
     mom.total(acc);
     if (act && lane == 0) {
@@ -269,16 +292,14 @@ __device__ __forceinline__ void primal_cell(const DevSolve &d, int par, int c, b
     }
 }
 
-template <typename T, bool SO, bool NT>
-__device__ __forceinline__ void primal_patch(const DevSolve &d, int p, int par)
+template <typename T, bool SO, bool NT, bool PARTS>
+__device__ __forceinline__ void primal_unit(const DevSolve &d, int par, const SweepUnit &u, bool split)
 {
-    int w;
-    bool act;
-    const int c = patch_wave(d, p, w, act), lane = threadIdx.x % kWave;
+    const int lane = threadIdx.x % kWave;
     if (sizeof(T) == 4 && pair_velocities<T>(d.n1))
-        primal_cell<T, sizeof(T) == 4 ? 2 : 1, SO, NT>(d, par, c, act, w, lane);
+        primal_cell<T, sizeof(T) == 4 ? 2 : 1, SO, NT, PARTS>(d, par, u, split, lane);
     else
-        primal_cell<T, 1, SO, NT>(d, par, c, act, w, lane);
+        primal_cell<T, 1, SO, NT, PARTS>(d, par, u, split, lane);
 }
 
 // moments W and wall flux F of f[par] of a cell (no update): the walk,
@@ -301,11 +322,11 @@ __device__ __forceinline__ void moments_cell(const DevSolve &d, int par, int c, 
     __syncthreads();
     Moments<V> mom;
     mom.init();
-    for (int i = 0; i < d.lm.isteps; i++) {
+    walk_parts<true>(d.lm, 0, d.parts[0], d.parts[0], [&](int i, int t0, int steps) {
         const Walk wk = make_walk<T, V>(d, lane, i);
-        const int a = wk.a, steps = d.lm.tq + (i < d.lm.tr ? 1 : 0);
+        const int a = wk.a;
         const ColFactor *col = fac.col + a;
-        int off = wk.off, b = wk.b;
+        int off = wk.off + t0 * bstep, b = wk.b + t0 * d.lm.brow;
         for (int t = 0; t < steps; t++, b += d.lm.brow, off += bstep) {
             const RowFactor rf = fac.row[b];
             const Vals<T, V> r = row_load<T, V, false>(src, off);
@@ -314,7 +335,7 @@ __device__ __forceinline__ void moments_cell(const DevSolve &d, int par, int c, 
             if (wl >= 0) mom.add_wall(rf, col, S0x, S0y, r);
         }
         mom.fold(col);
-    }
+    }, [&] { mom.end_part(); });
     double acc[5];
     mom.total(acc);
     if (act && lane == 0) {
@@ -348,14 +369,23 @@ struct AdjCell {
 template <int V>
 struct AdjMoments {
     double Q[V], Qc[V], Qcc[V], E[V], R[V], Pw; // of this walk; wall multiplier sum
-    WalkSums m;                                 // of the walks before (6)
+    WalkSums m;                                 // of the part's walks before (6)
+    double s;                                   // wave totals of the parts before, sum lane / 8
 
     __device__ __forceinline__ void init()
     {
 #pragma unroll
         for (int i = 0; i < 6; i++) m[i] = 0;
-        Pw = 0;
+        Pw = s = 0;
         clear();
+    }
+    __device__ __forceinline__ void end_part()
+    {
+        const double in[8] = {m[0], m[1], m[2], m[3], m[4], m[5], Pw, 0};
+        s += wave_scatter8(in);
+#pragma unroll
+        for (int i = 0; i < 6; i++) m[i] = 0;
+        Pw = 0;
     }
     __device__ __forceinline__ void clear()
     {
@@ -414,8 +444,6 @@ struct AdjMoments {
     // totals: A0..A4, R, Pw
     __device__ __forceinline__ void total(double (&o)[7])
     {
-        const double in[8] = {m[0], m[1], m[2], m[3], m[4], m[5], Pw, 0};
-        const double s = wave_scatter8(in);
 #pragma unroll
         for (int i = 0; i < 7; i++) o[i] = lane_value(s, 8 * i);
     }
@@ -455,13 +483,15 @@ __device__ __forceinline__ void adjoint_store(const DevSolve &d, double rho, dou
 // subtracted from the numerator.  NT: rows only this cell touches are loaded
 // and stored non-temporally.
 // ---------------------------------------------------------------------------
-template <typename T, int V, bool SO, bool NT, bool RES>
-__device__ __forceinline__ void adjoint_cell(const DevSolve &d, int par, int c, bool act, int w, int lane)
+template <typename T, int V, bool SO, bool NT, bool RES, bool PARTS>
+__device__ __forceinline__ void adjoint_cell(const DevSolve &d, int par, const SweepUnit &u, bool split, int lane)
 {
-    const AdjLds<T> sm(d, w);
+    const int c = u.c;
+    const bool act = u.act;
+    const AdjLds<T> sm(d, u.slot);
     sm.fac.fill(d);
     const double *ac = d.acoef + kAcoef * c;
-    sm.fill(d, ac, lane);
+    sm.fill(d, ac, u.fill0, u.fill_step);
     const double rho = uni(ac[0]), th = uni(ac[3]), itau = uni(ac[4]), Vv = uni(d.vol[c]);
     const double M = adjoint_jacobian(ac, lane);
     const double *aw = d.aW[par] + 8 * c;
@@ -474,7 +504,7 @@ __device__ __forceinline__ void adjoint_cell(const DevSolve &d, int par, int c, 
 #pragma unroll
     for (int m = 0; m < 4; m++) C[m] = uni(aw[m]) * itau - rt * uni(ac[6 + m]);
     const T VT = uni((T)Vv), Ct1 = uni((T)C[1]), Ct2 = uni((T)C[2]), Ct3 = uni((T)C[3]);
-    for (int i = lane; i < d.lm.n2p; i += kWave) {
+    for (int i = u.fill0; i < d.lm.n2p; i += u.fill_step) {
         const double v2 = i < d.n2 ? d.vy[i] : 1.0;
         sm.qb[i] = kFold ? (T)(Vv * v2 * fma(0.5 * C[3], v2, C[2])) : Ct2 * (T)v2;
     }
@@ -513,10 +543,10 @@ __device__ __forceinline__ void adjoint_cell(const DevSolve &d, int par, int c, 
 
     AdjMoments<V> mom;
     mom.init();
-    double dn = 0, dd = 0;
-    for (int i = 0; i < d.lm.isteps; i++) {
+    double dn = 0, dd = 0, rs[2] = {0, 0};
+    walk_parts<PARTS>(d.lm, u.p0, u.p1, u.parts, [&](int i, int t0, int steps) {
         const Walk wk = make_walk<T, V>(d, lane, i);
-        const int a = wk.a, steps = d.lm.tq + (i < d.lm.tr ? 1 : 0);
+        const int a = wk.a;
         const ColFactor *col = sm.fac.col + a;
         T sx[4][V], s1[V], v1h[V];
         double dnb[V], ddb[V];
@@ -534,7 +564,7 @@ __device__ __forceinline__ void adjoint_cell(const DevSolve &d, int par, int c, 
                 keep(sx[q][v]);
             }
         }
-        int off = wk.off, b = wk.b;
+        int off = wk.off + t0 * bstep, b = wk.b + t0 * d.lm.brow;
         for (int t = 0; t < steps; t++, b += d.lm.brow, off += bstep) {
             const T v2 = (T)sm.fac.row[b].v;
             T s[4][V];
@@ -603,12 +633,26 @@ __device__ __forceinline__ void adjoint_cell(const DevSolve &d, int par, int c, 
                 dd = fma(col[v].w, ddb[v], dd);
             }
         }
+    }, [&] {
+        mom.end_part();
+        if constexpr (RES) {
+            double x[2] = {dn, dd};
+            wave_sum<2>(x);
+            rs[0] += x[0];
+            rs[1] += x[1];
+            dn = dd = 0;
+        }
+    });
+    if (PARTS && split) {
+        if constexpr (RES) {
+            join_parts(d, u, lane, rs[0]);
+            join_parts(d, u, lane, rs[1]);
+        }
+        if (!join_parts(d, u, lane, mom.s)) return;
     }
     double acc[7];
     mom.total(acc);
     if constexpr (RES) {
-        double rs[2] = {dn, dd};
-        wave_sum<2>(rs);
         if (act && lane == 0) {
             d.red[2 * c] = rs[0];
             d.red[2 * c + 1] = rs[1];
@@ -617,16 +661,14 @@ __device__ __forceinline__ void adjoint_cell(const DevSolve &d, int par, int c, 
     adjoint_store(d, rho, th, itau, M, act, lane, wl, acc, d.aW[par ^ 1] + 8 * c, d.Phi[par ^ 1]);
 }
 
-template <typename T, bool SO, bool NT, bool RES>
-__device__ __forceinline__ void adjoint_patch(const DevSolve &d, int p, int par)
+template <typename T, bool SO, bool NT, bool RES, bool PARTS>
+__device__ __forceinline__ void adjoint_unit(const DevSolve &d, int par, const SweepUnit &u, bool split)
 {
-    int w;
-    bool act;
-    const int c = patch_wave(d, p, w, act), lane = threadIdx.x % kWave;
+    const int lane = threadIdx.x % kWave;
     if (sizeof(T) == 4 && pair_velocities<T>(d.n1))
-        adjoint_cell<T, sizeof(T) == 4 ? 2 : 1, SO, NT, RES>(d, par, c, act, w, lane);
+        adjoint_cell<T, sizeof(T) == 4 ? 2 : 1, SO, NT, RES, PARTS>(d, par, u, split, lane);
     else
-        adjoint_cell<T, 1, SO, NT, RES>(d, par, c, act, w, lane);
+        adjoint_cell<T, 1, SO, NT, RES, PARTS>(d, par, u, split, lane);
 }
 
 // Adjoint moments What, rho_tau and wall multipliers Phi_l of phi[par] with
@@ -642,7 +684,7 @@ __device__ __forceinline__ void adjoint_moments_cell(const DevSolve &d, int par,
     const AdjLds<T> sm(d, w);
     sm.fac.fill(d);
     const double *ac = d.acoef + kAcoef * c;
-    sm.fill(d, ac, lane);
+    sm.fill(d, ac, lane, kWave);
     const double rho = uni(ac[0]), th = uni(ac[3]), itau = uni(ac[4]);
     const double M = adjoint_jacobian(ac, lane);
     const T *__restrict__ gM = static_cast<const T *>(d.gM);
@@ -662,14 +704,14 @@ __device__ __forceinline__ void adjoint_moments_cell(const DevSolve &d, int par,
     __syncthreads();
     AdjMoments<V> mom;
     mom.init();
-    for (int i = 0; i < d.lm.isteps; i++) {
+    walk_parts<true>(d.lm, 0, d.parts[1], d.parts[1], [&](int i, int t0, int steps) {
         const Walk wk = make_walk<T, V>(d, lane, i);
-        const int a = wk.a, steps = d.lm.tq + (i < d.lm.tr ? 1 : 0);
+        const int a = wk.a;
         const ColFactor *col = sm.fac.col + a;
         double z1[V];
 #pragma unroll
         for (int v = 0; v < V; v++) z1[v] = fma(fma(0.5 * zc[3], col[v].v, zc[1]), col[v].v, zc[0]);
-        int off = wk.off, b = wk.b;
+        int off = wk.off + t0 * bstep, b = wk.b + t0 * d.lm.brow;
         for (int t = 0; t < steps; t++, b += d.lm.brow, off += bstep) {
             const RowFactor rf = sm.fac.row[b];
             Vals<T, V> r = row_load<T, V, false>(prow, off);
@@ -687,7 +729,7 @@ __device__ __forceinline__ void adjoint_moments_cell(const DevSolve &d, int par,
             if (wl >= 0) mom.add_wall(cq, rf, col, r, gM + b * d.n1 + a, wk.in && b < d.n2);
         }
         mom.fold(cq, col, sm.gx + a);
-    }
+    }, [&] { mom.end_part(); });
     double acc[7];
     mom.total(acc);
     adjoint_store(d, rho, th, itau, M, act, lane, wl, acc, d.aW[par] + 8 * c, d.Phi[par]);
@@ -698,12 +740,41 @@ __device__ __forceinline__ void adjoint_moments_cell(const DevSolve &d, int par,
 // ---------------------------------------------------------------------------
 constexpr int kPatchBlock = kPatchCells * kWave;   // threads of a patch workgroup
 
-template <typename T, bool SO, bool NT>
+// Workgroup b of a sweep (phase 0 primal, 1 adjoint): each XCD takes its
+// stretch of patches (from its end: rev), the last `tail` of them in parts.
+// Returns the patch, -1 for padding; k: which of the patch's workgroups, -1 for
+// the only one.
+template <bool PARTS>
+__device__ __forceinline__ int sweep_patch(const DevSolve &d, int phase, int b, int rev, int &k)
+{
+    k = -1;
+    if constexpr (!PARTS) return xcd_item(d.np, b, rev);
+    const int per = (d.np + 7) >> 3, parts = d.parts[phase], whole = per - d.tail[phase];
+    int j = b >> 3;
+    if (j >= whole) {
+        k = (j - whole) & (parts - 1);
+        j = whole + ((j - whole) >> (parts >> 1));   // parts: 2 or 4
+    }
+    const int p = (b & 7) * per + (rev ? per - 1 - j : j);
+    return p < d.np ? p : -1;
+}
+template <bool PARTS>
+__device__ __forceinline__ SweepUnit sweep_unit(const DevSolve &d, int phase, int p, int k)
+{
+    return !PARTS || k < 0 ? patch_unit(d, p, d.parts[phase]) : part_unit(d, p, k, d.parts[phase]);
+}
+static inline int sweep_grid(const DevSolve &d, int phase)
+{
+    return 8 * ((d.np + 7) / 8 + d.tail[phase] * (d.parts[phase] - 1));
+}
+
+template <typename T, bool SO, bool NT, bool PARTS>
 __global__ __launch_bounds__(kPatchBlock) void k_primal_sweep(DevSolve d, int par, int rev)
 {
-    const int p = xcd_item(d.np, blockIdx.x, rev);
+    int k;
+    const int p = sweep_patch<PARTS>(d, 0, blockIdx.x, rev, k);
     if (p < 0) return;
-    primal_patch<T, SO, NT>(d, p, par);
+    primal_unit<T, SO, NT, PARTS>(d, par, sweep_unit<PARTS>(d, 0, p, k), k >= 0);
 }
 
 template <typename T, bool FILL, bool NT>
@@ -720,12 +791,13 @@ __global__ __launch_bounds__(kPatchBlock) void k_moments(DevSolve d, int par)
         moments_cell<T, 1, FILL, NT>(d, par, c, act, lane);
 }
 
-template <typename T, bool SO, bool NT, bool RES>
+template <typename T, bool SO, bool NT, bool RES, bool PARTS>
 __global__ __launch_bounds__(kPatchBlock) void k_adjoint_sweep(DevSolve d, int par, int rev)
 {
-    const int p = xcd_item(d.np, blockIdx.x, rev);
+    int k;
+    const int p = sweep_patch<PARTS>(d, 1, blockIdx.x, rev, k);
     if (p < 0) return;
-    adjoint_patch<T, SO, NT, RES>(d, p, par);
+    adjoint_unit<T, SO, NT, RES, PARTS>(d, par, sweep_unit<PARTS>(d, 1, p, k), k >= 0);
 }
 
 // adjoint moments of phi[par]; CORR: corrected by z first
@@ -747,7 +819,7 @@ __global__ __launch_bounds__(kPatchBlock) void k_adjoint_moments(DevSolve d, int
 // run one scheme (SO: second order, the held corrections evaluated before
 // the launch); a workgroup owns one (solve, patch).  Phases and schemes are
 // separate kernels so that each gets the occupancy of its own registers.
-template <typename T, bool SO, bool NT>
+template <typename T, bool SO, bool NT, bool PARTS>
 __global__ __launch_bounds__(kPatchBlock) void k_batch_primal(const DevSolve *__restrict__ tab,
                                                               const int32_t *__restrict__ blk_solve,
                                                               const int32_t *__restrict__ blk_patch,
@@ -757,10 +829,10 @@ __global__ __launch_bounds__(kPatchBlock) void k_batch_primal(const DevSolve *__
     const int b = rev ? (int)(gridDim.x - 8 - blockIdx.x) + 2 * (int)(blockIdx.x & 7) : (int)blockIdx.x;
     const int s = blk_solve[b];
     if (s < 0) return;
-    primal_patch<T, SO, NT>(tab[s], blk_patch[b], (par0[s] + step) & 1);
+    primal_unit<T, SO, NT, PARTS>(tab[s], (par0[s] + step) & 1, patch_unit(tab[s], blk_patch[b], tab[s].parts[0]), false);
 }
 
-template <typename T, bool SO, bool NT, bool RES>
+template <typename T, bool SO, bool NT, bool RES, bool PARTS>
 __global__ __launch_bounds__(kPatchBlock) void k_batch_adjoint(const DevSolve *__restrict__ tab,
                                                                const int32_t *__restrict__ blk_solve,
                                                                const int32_t *__restrict__ blk_patch,
@@ -770,7 +842,7 @@ __global__ __launch_bounds__(kPatchBlock) void k_batch_adjoint(const DevSolve *_
     const int b = rev ? (int)(gridDim.x - 8 - blockIdx.x) + 2 * (int)(blockIdx.x & 7) : (int)blockIdx.x;
     const int s = blk_solve[b];
     if (s < 0) return;
-    adjoint_patch<T, SO, NT, RES>(tab[s], blk_patch[b], (par0[s] + step) & 1);
+    adjoint_unit<T, SO, NT, RES, PARTS>(tab[s], (par0[s] + step) & 1, patch_unit(tab[s], blk_patch[b], tab[s].parts[1]), false);
 }
 
 // Block tables of a batch on the device (the allocation-free batch): block
@@ -1021,8 +1093,8 @@ hipError_t launch_moments(const DevSolve &d, int par, hipStream_t st)
 hipError_t launch_primal_sweep(const DevSolve &d, int par, hipStream_t st)
 {
     const int rev = d.mem[0] == kMemTurn ? par & 1 : 0;
-    DVM_FLAG(d.order == 2, SO, DVM_FLAG(d.mem[0] == kMemStream, NT, DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(
-        (k_primal_sweep<T, SO, NT>), dim3(xcd_grid(d.np)), dim3(kPatchBlock), primal_lds(d), st, d, par, rev))));
+    DVM_FLAG(d.order == 2, SO, DVM_FLAG(d.mem[0] == kMemStream, NT, DVM_FLAG(d.parts[0] > 1, PARTS, DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(
+        (k_primal_sweep<T, SO, NT, PARTS>), dim3(sweep_grid(d, 0)), dim3(kPatchBlock), primal_lds(d), st, d, par, rev)))));
     return hipGetLastError();
 }
 
@@ -1144,8 +1216,8 @@ hipError_t launch_adjoint_moments(const DevSolve &d, int par, hipStream_t st)
 hipError_t launch_adjoint_sweep(const DevSolve &d, int par, int res, hipStream_t st)
 {
     const int rev = d.mem[1] == kMemTurn ? par & 1 : 0;
-    DVM_FLAG(d.order == 2, SO, DVM_FLAG(d.mem[1] == kMemStream, NT, DVM_FLAG(res, RES, DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(
-        (k_adjoint_sweep<T, SO, NT, RES>), dim3(xcd_grid(d.np)), dim3(kPatchBlock), adjoint_lds(d), st, d, par, rev)))));
+    DVM_FLAG(d.order == 2, SO, DVM_FLAG(d.mem[1] == kMemStream, NT, DVM_FLAG(res, RES, DVM_FLAG(d.parts[1] > 1, PARTS, DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(
+        (k_adjoint_sweep<T, SO, NT, RES, PARTS>), dim3(sweep_grid(d, 1)), dim3(kPatchBlock), adjoint_lds(d), st, d, par, rev))))));
     return hipGetLastError();
 }
 
@@ -1155,13 +1227,13 @@ hipError_t launch_batch(const DevSolve *tab, const int32_t *blk_solve, const int
     if (g.blocks <= 0) return hipSuccess;
     const int rev = g.mem == kMemTurn ? step & 1 : 0;
     if (g.adjoint)
-        DVM_FLAG(g.so, SO, DVM_FLAG(g.mem == kMemStream, NT, DVM_FLAG(res, RES, DVM_DISPATCH(g.mixed, hipLaunchKernelGGL(
-            (k_batch_adjoint<T, SO, NT, RES>), dim3(g.blocks), dim3(kPatchBlock), g.lds, st, tab, blk_solve, blk_patch,
-            par0, step, rev)))));
+        DVM_FLAG(g.so, SO, DVM_FLAG(g.mem == kMemStream, NT, DVM_FLAG(res, RES, DVM_FLAG(g.parts, PARTS, DVM_DISPATCH(g.mixed, hipLaunchKernelGGL(
+            (k_batch_adjoint<T, SO, NT, RES, PARTS>), dim3(g.blocks), dim3(kPatchBlock), g.lds, st, tab, blk_solve, blk_patch,
+            par0, step, rev))))));
     else
-        DVM_FLAG(g.so, SO, DVM_FLAG(g.mem == kMemStream, NT, DVM_DISPATCH(g.mixed, hipLaunchKernelGGL(
-            (k_batch_primal<T, SO, NT>), dim3(g.blocks), dim3(kPatchBlock), g.lds, st, tab, blk_solve, blk_patch, par0,
-            step, rev))));
+        DVM_FLAG(g.so, SO, DVM_FLAG(g.mem == kMemStream, NT, DVM_FLAG(g.parts, PARTS, DVM_DISPATCH(g.mixed, hipLaunchKernelGGL(
+            (k_batch_primal<T, SO, NT, PARTS>), dim3(g.blocks), dim3(kPatchBlock), g.lds, st, tab, blk_solve, blk_patch, par0,
+            step, rev)))));
     return hipGetLastError();
 }
 

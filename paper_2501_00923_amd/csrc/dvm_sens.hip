@@ -195,7 +195,7 @@ __device__ __forceinline__ void mesh_sens_cell(const DevSolve &d, int fpar, int 
     // the frozen state's equilibrium (parameters and 1/tau from the adjoint
     // coefficients)
     const double *ac = d.acoef + kAcoef * c;
-    sm.fill(d, ac, lane);
+    sm.fill(d, ac, lane, kWave);
     const double hth = 0.5 * uni(ac[3]), itau = uni(ac[4]);
     const int rowb = d.nv * 2 * (int)sizeof(T), bstep = d.lm.brow * d.n1 * 2 * (int)sizeof(T);
     const char *f = static_cast<const char *>(d.f[fpar]);

@@ -273,10 +273,10 @@ struct AdjLds {
         qb = q0 + w * d.lm.n2p;
     }
     // this wave's Maxwellian factors of the frozen state; no barrier
-    __device__ __forceinline__ void fill(const DevSolve &d, const double *ac, int lane) const
+    __device__ __forceinline__ void fill(const DevSolve &d, const double *ac, int fill0, int fill_step) const
     {
         const double u1 = uni(ac[1]), u2 = uni(ac[2]), h = 0.5 * recip(uni(ac[3])), gc = uni(ac[5]);
-        for (int i = lane; i < d.lm.n1p + d.lm.n2p; i += kWave) {
+        for (int i = fill0; i < d.lm.n1p + d.lm.n2p; i += fill_step) {
             const bool first = i < d.lm.n1p;
             const int k = first ? i : i - d.lm.n1p;
             const bool in = k < (first ? d.n1 : d.n2);
@@ -290,6 +290,83 @@ struct AdjLds {
         }
     }
 };
+
+// What a wave of a sweep works on.  A row's steps are summed in `parts` equal
+// parts (sweep_parts), each reduced over the wave and added in order, so that a
+// cell's sums do not depend on whether one wave walks all parts or `parts`
+// waves one each.
+struct SweepUnit {
+    int c;                   // cell
+    bool act;                // exists (idle waves of a partial patch run along on the first cell without storing)
+    int slot;                // the cell's LDS tables
+    int fill0, fill_step;    // table entries this lane fills
+    int p0, p1, parts;       // parts p0 .. p1 - 1 of parts
+};
+
+// wave w of a workgroup that takes patch p, one cell a wave
+__device__ __forceinline__ SweepUnit patch_unit(const DevSolve &d, int p, int parts)
+{
+    const int w = uni((int)(threadIdx.x / kWave));
+    const int c0 = uni(d.patch[p]), cnt = uni(d.patch[p + 1]) - c0;
+    SweepUnit u;
+    u.act = w < cnt;
+    u.c = c0 + (u.act ? w : 0);
+    u.slot = w;
+    u.fill0 = threadIdx.x % kWave;
+    u.fill_step = kWave;
+    u.p0 = 0;
+    u.p1 = u.parts = parts;
+    return u;
+}
+
+// wave w of the k-th of `parts` (2 or 4) workgroups that share patch p, `parts`
+// waves a cell
+__device__ __forceinline__ SweepUnit part_unit(const DevSolve &d, int p, int k, int parts)
+{
+    const int w = uni((int)(threadIdx.x / kWave)), cells = kPatchCells >> (parts >> 1);
+    const int c0 = uni(d.patch[p]), cnt = uni(d.patch[p + 1]) - c0;
+    SweepUnit u;
+    u.slot = w >> (parts >> 1);
+    const int i = k * cells + u.slot;
+    u.act = i < cnt;
+    u.c = c0 + (u.act ? i : 0);
+    u.fill0 = (w & (parts - 1)) * kWave + threadIdx.x % kWave;
+    u.fill_step = parts * kWave;
+    u.p0 = w & (parts - 1);
+    u.p1 = u.p0 + 1;
+    u.parts = parts;
+    return u;
+}
+
+// The pieces of parts p0 .. p1 - 1 in walk order: go(i, t0, n) takes steps t0 ..
+// t0 + n - 1 of walk i, done() ends a part.  PARTS: there is more than one (the
+// plain walk costs a launch of few short rows up to 9 % less).
+template <bool PARTS, typename Go, typename Done>
+__device__ __forceinline__ void walk_parts(const LaneMap &m, int p0, int p1, int parts, Go go, Done done)
+{
+    if constexpr (!PARTS) {
+        for (int i = 0; i < m.isteps; i++) go(i, 0, m.tq + (i < m.tr ? 1 : 0));
+        done();
+        return;
+    }
+    int i = 0, start = 0;
+    for (int p = p0; p < p1; p++) {
+        int g = m.total * p >> (parts >> 1);
+        const int ge = m.total * (p + 1) >> (parts >> 1);
+        while (g < ge) {
+            int steps = m.tq + (i < m.tr ? 1 : 0);
+            while (g >= start + steps) {
+                start += steps;
+                i++;
+                steps = m.tq + (i < m.tr ? 1 : 0);
+            }
+            const int n = min(start + steps, ge) - g;
+            go(i, g - start, n);
+            g += n;
+        }
+        done();
+    }
+}
 
 // the wave's cell of patch p: its number, whether it exists (idle waves of a
 // partial patch run along on the first cell without storing)

@@ -99,3 +99,46 @@ def test_cache_rule_does_not_change_results(ni, nj, n, adjoint):
     want = one.state_save(which)
     for s in many:
         assert np.array_equal(s.state_save(which), want)
+
+
+# (cells, velocities, precision): rows in 4 and in 2 parts for few cells, FP64
+# rows from memory in 4 parts, FP32 ones with only the last patches in parts
+@pytest.mark.parametrize("ni,nj,n1,n2,precision", [
+    (17, 9, 24, 24, dvm.FP64), (30, 21, 17, 20, dvm.MIXED), (45, 33, 24, 24, dvm.FP64), (40, 30, 33, 31, dvm.MIXED),
+    (120, 50, 47, 49, dvm.FP64), (130, 63, 64, 66, dvm.MIXED)])
+def test_rows_in_parts(ni, nj, n1, n2, precision):
+    """Sweeps whose rows several waves share, against the oracle, and bit for
+    bit the batch's, where one wave takes all parts."""
+    g = I.ogrid(ni, nj, 6.0, 1.05, np.array([0.0, 0.02, 0.01, 0.0]), np.zeros(4))
+    wl = I.Workload("parts", g, I.VGridSpec(I.VG_MIDPOINT, n1, n2, 4.0), I.FlowSpec(0.8, 0.4, 1.1), 0)
+    s, m = [dvm.Solver.from_workload(wl, precision=precision) for _ in range(2)]
+    o = oracle.Problem.from_workload(wl, nthreads=16)
+    o.primal_init()
+    ro = o.primal_iterate(3)
+    for x in (s, m):
+        x.primal_init()
+    _, r = s.primal_iterate(3)
+    b = dvm.Batch([m])
+    b.run(3)
+    assert abs(b.residuals()[0] - r) <= 1e-12 * r
+    b.close()
+    assert np.array_equal(s.state_save(dvm.STATE_F), m.state_save(dvm.STATE_F))
+    assert np.array_equal(s.moments(), m.moments())
+    tol = 1e-11 if precision == dvm.FP64 else 2e-5
+    assert _rel(s.moments(), o.W) <= tol
+    W = s.moments()
+    s.state_load(dvm.STATE_F, s.state_save(dvm.STATE_F))
+    assert np.array_equal(s.moments(), W)
+    for x in (s, m):
+        x.adjoint_init()
+    _, ra = s.adjoint_iterate(2)
+    b = dvm.Batch([m])
+    b.run(2)
+    assert abs(b.residuals()[0] - ra) <= 1e-12 * ra
+    b.close()
+    assert np.array_equal(s.state_save(dvm.STATE_PHI), m.state_save(dvm.STATE_PHI))
+    o.adjoint_init()
+    o.adjoint_iterate(2)
+    if precision == dvm.FP64:
+        check_resid(r, ro, "primal")
+        assert _rel(s.state_array(dvm.STATE_PHI), o.phi) <= 1e-11

@@ -75,6 +75,16 @@ __device__ __forceinline__ double uni(double x)
     const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(v >> 32));
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
+// a pointer into global memory (the address space, lost on the way through
+// registers, is given back: generic loads would wait with the scalar ones)
+using GlobalDoubles = const __attribute__((address_space(1))) double *;
+__device__ __forceinline__ GlobalDoubles uni(const double *x)
+{
+    const unsigned long long v = reinterpret_cast<unsigned long long>(x);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(v & 0xffffffffULL));
+    const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(v >> 32));
+    return reinterpret_cast<GlobalDoubles>(((unsigned long long)hi << 32) | lo);
+}
 
 // Workgroups are handed to the 8 XCDs round-robin; give each XCD a
 // contiguous stretch of the sweep order (n items: cells or patches) so that

@@ -138,9 +138,18 @@ __device__ __forceinline__ void primal_cell(const DevSolve &d, int par, const Sw
     const int c = u.c;
     const bool act = u.act;
     const Factors fac(d, 0);
-    fac.fill(d);
+    const GridTables gt(d);
+    const GridEntry ge = gt.at(threadIdx.x), ge0 = gt.at(u.fill0);
     T *ex = static_cast<T *>(fac.end) + u.slot * (d.lm.n1p + d.lm.n2p), *ey = ex + d.lm.n1p;
 
+    int nb[4];
+    T Sx[4], Sy[4];
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        nb[q] = uni(d.nbr[4 * c + q]);
+        Sx[q] = uni((T)d.S[8 * c + 2 * q]);
+        Sy[q] = uni((T)d.S[8 * c + 2 * q + 1]);
+    }
     const double *Win = d.W[par] + 4 * c;
     const double W0 = uni(Win[0]), W1 = uni(Win[1]), W2 = uni(Win[2]), W3 = uni(Win[3]);
     const double ir = recip(W0), u1 = W1 * ir, u2 = W2 * ir;
@@ -157,29 +166,16 @@ __device__ __forceinline__ void primal_cell(const DevSolve &d, int par, const Sw
         for (int a = 0; a < 4; a++) Pe[a] = uni(pe[a]);
     }
     const double ith = recip(Pe[3]), h = 0.5 * ith;
+    fac.fill(gt, ge);
     // Maxwellian factors: g1 = gc ex[a] ey[b]
-    for (int i = u.fill0; i < d.lm.n1p + d.lm.n2p; i += u.fill_step) {
-        const bool first = i < d.lm.n1p;
-        const int k = first ? i : i - d.lm.n1p;
-        double g = 0;
-        if (k < (first ? d.n1 : d.n2)) {
-            const double e = first ? d.vx[k] - Pe[1] : d.vy[k] - Pe[2];
-            g = exp(-e * e * h);
-        }
-        ex[i] = (T)g;
-    }
+    gt.each(u.fill0, u.fill_step, ge0, [&](int i, const GridEntry &e) {
+        const double x = e.v - (e.col ? Pe[1] : Pe[2]);
+        ex[i] = e.in ? (T)exp(-x * x * h) : (T)0;
+    });
 
     const int nv = d.nv, rowb = nv * 2 * (int)sizeof(T);
     const char *fin = static_cast<const char *>(d.f[par]);
     char *fout = static_cast<char *>(d.f[par ^ 1]);
-    int nb[4];
-    T Sx[4], Sy[4];
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-        nb[q] = uni(d.nbr[4 * c + q]);
-        Sx[q] = uni((T)d.S[8 * c + 2 * q]);
-        Sy[q] = uni((T)d.S[8 * c + 2 * q + 1]);
-    }
     const int wl = nb[0] <= -2 ? -2 - nb[0] : -1;
     T wcoef = 1;
     double S0x = 0, S0y = 0;
@@ -311,7 +307,8 @@ template <typename T, int V, bool FILL, bool NT>
 __device__ __forceinline__ void moments_cell(const DevSolve &d, int par, int c, bool act, int lane)
 {
     const Factors fac(d, 0);
-    fac.fill(d);
+    const GridTables gt(d);
+    fac.fill(gt, gt.at(threadIdx.x));
     const int rowb = d.nv * 2 * (int)sizeof(T);
     const int l0 = uni(d.nbr[4 * c]);
     const int wl = l0 <= -2 ? -2 - l0 : -1;
@@ -489,9 +486,17 @@ __device__ __forceinline__ void adjoint_cell(const DevSolve &d, int par, const S
     const int c = u.c;
     const bool act = u.act;
     const AdjLds<T> sm(d, u.slot);
-    sm.fac.fill(d);
+    const GridTables gt(d);
+    const GridEntry ge = gt.at(threadIdx.x), ge0 = gt.at(u.fill0);
+    int nb[4];
+    T Sx[4], Sy[4];
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        nb[q] = uni(d.nbr[4 * c + q]);
+        Sx[q] = uni((T)d.S[8 * c + 2 * q]);
+        Sy[q] = uni((T)d.S[8 * c + 2 * q + 1]);
+    }
     const double *ac = d.acoef + kAcoef * c;
-    sm.fill(d, ac, u.fill0, u.fill_step);
     const double rho = uni(ac[0]), th = uni(ac[3]), itau = uni(ac[4]), Vv = uni(d.vol[c]);
     const double M = adjoint_jacobian(ac, lane);
     const double *aw = d.aW[par] + 8 * c;
@@ -504,21 +509,16 @@ __device__ __forceinline__ void adjoint_cell(const DevSolve &d, int par, const S
 #pragma unroll
     for (int m = 0; m < 4; m++) C[m] = uni(aw[m]) * itau - rt * uni(ac[6 + m]);
     const T VT = uni((T)Vv), Ct1 = uni((T)C[1]), Ct2 = uni((T)C[2]), Ct3 = uni((T)C[3]);
-    for (int i = u.fill0; i < d.lm.n2p; i += u.fill_step) {
-        const double v2 = i < d.n2 ? d.vy[i] : 1.0;
-        sm.qb[i] = kFold ? (T)(Vv * v2 * fma(0.5 * C[3], v2, C[2])) : Ct2 * (T)v2;
-    }
+    sm.fac.fill(gt, ge);
+    sm.fill(gt, ge0, ac, u.fill0, u.fill_step, [&](int k, double v2) {
+        sm.qb[k] = kFold ? (T)(Vv * v2 * fma(0.5 * C[3], v2, C[2])) : Ct2 * (T)v2;
+    });
 
     const int nv = d.nv, rowb = nv * 2 * (int)sizeof(T);
     const char *pin = static_cast<const char *>(d.phi[par]);
-    int nb[4];
-    T Sx[4], Sy[4];
     __amdgpu_buffer_rsrc_t src[4];
 #pragma unroll
     for (int q = 0; q < 4; q++) {
-        nb[q] = uni(d.nbr[4 * c + q]);
-        Sx[q] = uni((T)d.S[8 * c + 2 * q]);
-        Sy[q] = uni((T)d.S[8 * c + 2 * q + 1]);
         // downstream row; nothing (zero) behind a boundary face
         src[q] = row_rsrc(pin + (size_t)(nb[q] >= 0 ? nb[q] : c) * rowb, nb[q] >= 0 ? rowb : 0);
     }
@@ -682,9 +682,10 @@ __device__ __forceinline__ void adjoint_moments_cell(const DevSolve &d, int par,
                                                      int lane)
 {
     const AdjLds<T> sm(d, w);
-    sm.fac.fill(d);
+    const GridTables gt(d);
+    sm.fac.fill(gt, gt.at(threadIdx.x));
     const double *ac = d.acoef + kAcoef * c;
-    sm.fill(d, ac, lane, kWave);
+    sm.fill(gt, ac, lane);
     const double rho = uni(ac[0]), th = uni(ac[3]), itau = uni(ac[4]);
     const double M = adjoint_jacobian(ac, lane);
     const T *__restrict__ gM = static_cast<const T *>(d.gM);

@@ -54,7 +54,8 @@ template <typename T, int V>
 __device__ __forceinline__ void macro_flux_cell(const DevSolve &d, int par, int c, bool act, int lane)
 {
     const Factors fac(d, 0);
-    fac.fill(d);
+    const GridTables gt(d);
+    fac.fill(gt, gt.at(threadIdx.x));
     const double *ms = d.mstate + kEqState * c;
     const double P0 = uni(ms[0]), P1 = uni(ms[1]), P2 = uni(ms[2]), P3 = uni(ms[3]), h = 0.5 / P3;
     // moments of the equilibrium: R_p = sum wx X v1^p, T_p = sum wy Y v2^p, p < 3

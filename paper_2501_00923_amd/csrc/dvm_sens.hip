@@ -191,11 +191,12 @@ template <typename T, int V>
 __device__ __forceinline__ void mesh_sens_cell(const DevSolve &d, int fpar, int ppar, int c, bool act, int w, int lane)
 {
     const AdjLds<T> sm(d, w);
-    sm.fac.fill(d);
+    const GridTables gt(d);
+    sm.fac.fill(gt, gt.at(threadIdx.x));
     // the frozen state's equilibrium (parameters and 1/tau from the adjoint
     // coefficients)
     const double *ac = d.acoef + kAcoef * c;
-    sm.fill(d, ac, lane, kWave);
+    sm.fill(gt, ac, lane);
     const double hth = 0.5 * uni(ac[3]), itau = uni(ac[4]);
     const int rowb = d.nv * 2 * (int)sizeof(T), bstep = d.lm.brow * d.n1 * 2 * (int)sizeof(T);
     const char *f = static_cast<const char *>(d.f[fpar]);

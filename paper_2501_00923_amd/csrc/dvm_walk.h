@@ -167,6 +167,53 @@ struct WalkSums {
     __device__ __forceinline__ double &operator[](int k) const { return p[k * kPatchCells * kWave]; }
 };
 
+// The velocity grid's values for the LDS tables, whose entries are numbered
+// columns (n1p) first, then rows (n2p), padded past the grid with v = 1 and
+// weight 0.  The kernels load a thread's first entries before anything else
+// (their addresses need nothing but the arguments), so that these loads, the
+// cell's and the neighbour list's wait for memory together.  Sweeps, us,
+// primal / adjoint, against loading each where it is used: 256x128 cells with
+// 16x16 velocities in FP64 58 / 92 -> 57 / 83, in FP32 41 / 60 -> 38 / 54,
+// 128x64 with 32x32 in FP32 27.1 / 37.5 -> 26.2 / 36.3, 256x128 with 48x48 in
+// FP64 468 / 659 -> 464 / 650.
+struct GridEntry {
+    int k;
+    bool col, in;            // a column; inside the grid
+    double v, w;
+};
+struct GridTables {
+    int n1, n2, n1p, n;
+    GlobalDoubles vx, vy, wx, wy;
+    // (in registers: a choice between two arguments would be loaded per lane)
+    __device__ __forceinline__ explicit GridTables(const DevSolve &d)
+        : n1(uni(d.n1)), n2(uni(d.n2)), n1p(d.lm.n1p), n(d.lm.n1p + d.lm.n2p), vx(uni(d.vx)), vy(uni(d.vy)), wx(uni(d.wx)),
+          wy(uni(d.wy))
+    {
+    }
+    __device__ __forceinline__ GridEntry at(int i) const
+    {
+        GridEntry e;
+        e.col = i < n1p;
+        e.k = e.col ? i : i - n1p;
+        const int m = e.col ? n1 : n2, k = min(e.k, m - 1);
+        e.in = e.k < m;
+        e.v = (e.col ? vx : vy)[k];
+        e.w = (e.col ? wx : wy)[k];
+        return e;
+    }
+    // put(i, entry i) for i = i0, i0 + step, ...; e: entry i0
+    template <typename Put>
+    __device__ __forceinline__ void each(int i0, int step, GridEntry e, Put put) const
+    {
+        for (int i = i0; i < n; i += step) {
+            GridEntry next = e;
+            if (i + step < n) next = at(i + step);
+            put(i, e);
+            e = next;
+        }
+    }
+};
+
 // The workgroup's shared tables from byte `at` of its LDS.
 struct Factors {
     RowFactor *row;
@@ -178,25 +225,20 @@ struct Factors {
         col = reinterpret_cast<ColFactor *>(row + d.lm.n2p);
         end = col + d.lm.n1p;
     }
-    // padded past the grid with v = 1 and weight 0; all threads of the
-    // workgroup, no barrier
-    __device__ __forceinline__ void fill(const DevSolve &d) const
+    __device__ __forceinline__ void put(const GridEntry &e) const
     {
-        for (int i = threadIdx.x; i < d.lm.n2p + d.lm.n1p; i += kPatchCells * kWave) {
-            const bool first = i < d.lm.n2p;
-            const int k = first ? i : i - d.lm.n2p;
-            double v = 1.0, w = 0.0;
-            if (k < (first ? d.n2 : d.n1)) {
-                v = (first ? d.vy : d.vx)[k];
-                w = (first ? d.wy : d.wx)[k];
-            }
-            if (first) {
-                const double wv = w * v;
-                row[k] = {v, w, wv, 0.5 * (wv * v)};
-            } else {
-                col[k] = {v, w};
-            }
+        const double v = e.in ? e.v : 1.0, w = e.in ? e.w : 0.0;
+        if (e.col) {
+            col[e.k] = {v, w};
+        } else {
+            const double wv = w * v;
+            row[e.k] = {v, w, wv, 0.5 * (wv * v)};
         }
+    }
+    // e: entry threadIdx.x; all threads of the workgroup, no barrier
+    __device__ __forceinline__ void fill(const GridTables &g, const GridEntry &e) const
+    {
+        g.each(threadIdx.x, kPatchCells * kWave, e, [&](int, const GridEntry &x) { put(x); });
     }
 };
 
@@ -272,22 +314,28 @@ struct AdjLds {
         gx = g0 + w * d.lm.n1p;
         qb = q0 + w * d.lm.n2p;
     }
-    // this wave's Maxwellian factors of the frozen state; no barrier
-    __device__ __forceinline__ void fill(const DevSolve &d, const double *ac, int fill0, int fill_step) const
+    // this wave's Maxwellian factors of the frozen state from entry i0 in steps
+    // of `step` (e0: entry i0); row(k, v2): anything else per row; no
+    // barrier
+    template <typename Row>
+    __device__ __forceinline__ void fill(const GridTables &g, const GridEntry &e0, const double *ac, int i0, int step,
+                                         Row row) const
     {
         const double u1 = uni(ac[1]), u2 = uni(ac[2]), h = 0.5 * recip(uni(ac[3])), gc = uni(ac[5]);
-        for (int i = fill0; i < d.lm.n1p + d.lm.n2p; i += fill_step) {
-            const bool first = i < d.lm.n1p;
-            const int k = first ? i : i - d.lm.n1p;
-            const bool in = k < (first ? d.n1 : d.n2);
-            const double c = in ? (first ? d.vx[k] - u1 : d.vy[k] - u2) : 0.0;
-            const double w = in ? (first ? d.wx[k] : d.wy[k]) : 0.0;
-            const double g = w * exp(-c * c * h);
-            if (first)
-                gx[k] = gc * g;
-            else
-                adj[k] = {g, g * c, g * c * c, 0.0};
-        }
+        g.each(i0, step, e0, [&](int, const GridEntry &e) {
+            const double c = e.in ? e.v - (e.col ? u1 : u2) : 0.0, w = e.in ? e.w : 0.0;
+            const double x = w * exp(-c * c * h);
+            if (e.col) {
+                gx[e.k] = gc * x;
+            } else {
+                adj[e.k] = {x, x * c, x * c * c, 0.0};
+                row(e.k, e.in ? e.v : 1.0);
+            }
+        });
+    }
+    __device__ __forceinline__ void fill(const GridTables &g, const double *ac, int lane) const
+    {
+        fill(g, g.at(lane), ac, lane, kWave, [](int, double) {});
     }
 };
 

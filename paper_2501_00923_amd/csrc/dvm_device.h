@@ -63,6 +63,21 @@ __device__ __forceinline__ double mJ_of(int objective, double v1, double v2)
     return objective == 0 ? v1 : 0.5 * (v1 * v1 + v2 * v2);
 }
 
+// The x and y of a velocity's two slopes (or B) in a cell's row of d.G.  FP64
+// rows hold all of the first component, then all of the second, FP32 rows both
+// together: a lane's access is 16 bytes, a wave's contiguous, either way.
+template <typename T>
+struct Slopes {
+    T x[2], y[2];
+};
+template <typename T>
+__device__ __forceinline__ Slopes<T> slopes_at(const DevSolve &d, int c, int k)
+{
+    const T *g = static_cast<const T *>(d.G) + (size_t)c * d.nv * 4;
+    const T *g1 = sizeof(T) == 8 ? g + 2 * k : g + 4 * k, *g2 = sizeof(T) == 8 ? g1 + 2 * d.nv : g1 + 2;
+    return {{g1[0], g2[0]}, {g1[1], g2[1]}};
+}
+
 // Values that are the same in every lane of a wave (per-cell constants of a
 // patch sweep), moved to scalar registers so that they do not occupy
 // vector registers through the velocity loop.

@@ -29,7 +29,6 @@ __global__ __launch_bounds__(kBlock) void k_wall_sens(DevSolve d, int fpar, int 
     const double n1 = d.wall_n[2 * l], n2 = d.wall_n[2 * l + 1], A = d.wall_A[l];
     const double iD = 1.0 / d.D[l], F = SO ? d.F[fpar][l] + d.dF[l] : d.F[fpar][l], thw2 = 0.5 * d.theta_w;
     const double iV = 1.0 / d.vol[c];
-    const T2 *G = static_cast<const T2 *>(d.G);
     int nb[4];
     double Sx[4], Sy[4], rx[4] = {}, ry[4] = {}, nx[4] = {}, ny[4] = {};
     for (int q = 0; q < 4; q++) {
@@ -54,8 +53,11 @@ __global__ __launch_bounds__(kBlock) void k_wall_sens(DevSolve d, int fpar, int 
         const double gw1 = F * (double)gM[k] * iD;
         T2 gc1 = {0, 0}, gc2 = {0, 0};
         if (SO) {
-            gc1 = G[2 * (row + k)];
-            gc2 = G[2 * (row + k) + 1];
+            const Slopes<T> gk = slopes_at<T>(d, c, k);
+            gc1.x = gk.x[0];
+            gc1.y = gk.y[0];
+            gc2.x = gk.x[1];
+            gc2.y = gk.y[1];
         }
         // the outgoing wall value: the cell value, reconstructed at order 2
         const double f1l = vn > 0 ? (double)fc.x + (SO ? (double)(gc1.x * (T)rx[0] + gc1.y * (T)ry[0]) : 0.0) : gw1;
@@ -77,9 +79,9 @@ __global__ __launch_bounds__(kBlock) void k_wall_sens(DevSolve d, int fpar, int 
                 a1 = (double)u.x;
                 a2 = (double)u.y;
                 if (SO) {
-                    const T2 h1 = G[2 * nr], h2 = G[2 * nr + 1];
-                    a1 += (double)(h1.x * (T)nx[q] + h1.y * (T)ny[q]);
-                    a2 += (double)(h2.x * (T)nx[q] + h2.y * (T)ny[q]);
+                    const Slopes<T> h = slopes_at<T>(d, nb[q], k);
+                    a1 += (double)(h.x[0] * (T)nx[q] + h.y[0] * (T)ny[q]);
+                    a2 += (double)(h.x[1] * (T)nx[q] + h.y[1] * (T)ny[q]);
                 }
             } else if (nb[q] == -1) {
                 const T2 u = fd[k];
@@ -372,7 +374,6 @@ __global__ __launch_bounds__(kBlock) void k_mesh_sens_cell_so(DevSolve d, int fp
     const T2 *ph = static_cast<const T2 *>(d.phi[ppar]);
     const T2 *fd = static_cast<const T2 *>(d.fd);
     const T *gM = static_cast<const T *>(d.gM);
-    const T *Gs = static_cast<const T *>(d.G);
     const T2 *ps = static_cast<const T2 *>(d.psi);
     // the frozen state's equilibrium (parameters and 1/tau from the adjoint
     // coefficients)
@@ -403,8 +404,8 @@ __global__ __launch_bounds__(kBlock) void k_mesh_sens_cell_so(DevSolve d, int fp
         const double mj = mJ_of(obj, v1, v2);
         const T2 fc = f[row + k], pc = ph[row + k], pk = ps[row + k];
         const double f1 = (double)fc.x, f2 = (double)fc.y, p1 = (double)pc.x, p2 = (double)pc.y;
-        const T *gk = Gs + 4 * (row + k);
-        const double g1x = (double)gk[0], g1y = (double)gk[1], g2x = (double)gk[2], g2y = (double)gk[3];
+        const Slopes<T> gk = slopes_at<T>(d, c, k);
+        const double g1x = (double)gk.x[0], g1y = (double)gk.y[0], g2x = (double)gk.x[1], g2y = (double)gk.y[1];
         double P1x = 0, P1y = 0, P2x = 0, P2y = 0, fb1[4], fb2[4];
         for (int q = 0; q < 4; q++) {
             const double s = v1 * Sx[q] + v2 * Sy[q];
@@ -442,8 +443,8 @@ __global__ __launch_bounds__(kBlock) void k_mesh_sens_cell_so(DevSolve d, int fp
                 P2x += s * e2 * rfx[q];
                 P2y += s * e2 * rfy[q];
             } else if (nb[q] >= 0) {
-                const T *gn = Gs + 4 * ((size_t)nb[q] * nv + k);
-                const double n1x = (double)gn[0], n1y = (double)gn[1], n2x = (double)gn[2], n2y = (double)gn[3];
+                const Slopes<T> gn = slopes_at<T>(d, nb[q], k);
+                const double n1x = (double)gn.x[0], n1y = (double)gn.y[0], n2x = (double)gn.x[1], n2y = (double)gn.y[1];
                 a1 = fn1 + n1x * rnx[q] + n1y * rny[q];
                 a2 = fn2 + n2x * rnx[q] + n2y * rny[q];
                 acc[8 + 2 * q] += wt * s * (p1 * n1x + p2 * n2x);
@@ -553,7 +554,6 @@ __global__ __launch_bounds__(kBlock) void k_mesh_sens_wall(DevSolve d, int fpar,
     const T *gM = static_cast<const T *>(d.gM);
     const double nx = d.wall_n[2 * l], ny = d.wall_n[2 * l + 1], A = d.wall_A[l];
     const double F = SO ? d.F[fpar][l] + d.dF[l] : d.F[fpar][l], D = d.D[l], rw = F / D, thw2 = 0.5 * d.theta_w;
-    const T *Gs = static_cast<const T *>(d.G);
     const double r0x = SO ? d.rf[8 * c] : 0.0, r0y = SO ? d.rf[8 * c + 1] : 0.0;
     // dF/dn (2), dD/dn (2), dL/drho from R (1), dJ/drho / A (1), dJ/dS_0 at fixed rho (2)
     double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -566,7 +566,10 @@ __global__ __launch_bounds__(kBlock) void k_mesh_sens_wall(DevSolve d, int fpar,
         double f1 = (double)fc.x;
         const double g = (double)gM[k];
         if constexpr (SO) {
-            if (vn > 0) f1 += (double)Gs[4 * (row + k)] * r0x + (double)Gs[4 * (row + k) + 1] * r0y;
+            if (vn > 0) {
+                const Slopes<T> gk = slopes_at<T>(d, c, k);
+                f1 += (double)gk.x[0] * r0x + (double)gk.y[0] * r0y;
+            }
         }
         if (vn > 0) {
             acc[0] += wt * v1 * f1;

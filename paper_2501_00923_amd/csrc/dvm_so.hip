@@ -22,9 +22,15 @@
 // order), one wave per cell, a lane per velocity; per-cell constants in
 // scalar registers.  Each kernel reads its cell's row and its interior
 // neighbours' rows (in L2 for the same reasons as in the sweeps) and writes
-// one row.
+// one row.  All are bound by memory; 256x128 cells with 48x48 velocities
+// in FP64, us: slopes 806 (from 1045, when the limiter took four fractions and
+// bound them), psi 611 (867), c 799 (868), B 939 (1084), E 894 (1004).  Rows
+// go through buffer accesses whose range check drops
+// what is not wanted (a boundary face's neighbour, a face that the velocity
+// does not cross that way), so a step issues its loads together without a
+// branch.  FP32 expressions keep their order and roundings.
 
-#include "dvm_device.h"
+#include "dvm_walk.h"
 
 namespace dvm {
 
@@ -38,7 +44,6 @@ constexpr int kSoBlock = kPatchCells * kWave;
 template <typename T>
 struct Cell {
     int c, nb[4];
-    size_t row, nrow[4];     // first pair of c's row; of each neighbour's (c's own for boundary faces)
     T Sx[4], Sy[4], rx[4], ry[4], nx[4], ny[4];
     T iV, iVn[4];
 };
@@ -48,12 +53,10 @@ __device__ __forceinline__ Cell<T> load_cell(const DevSolve &d, int c, bool want
 {
     Cell<T> g;
     g.c = c;
-    g.row = (size_t)c * d.nv;
     g.iV = uni((T)(1.0 / d.vol[c]));
 #pragma unroll
     for (int q = 0; q < 4; q++) {
         g.nb[q] = uni(d.nbr[4 * c + q]);
-        g.nrow[q] = g.nb[q] >= 0 ? (size_t)g.nb[q] * d.nv : g.row;
         g.Sx[q] = uni((T)d.S[8 * c + 2 * q]);
         g.Sy[q] = uni((T)d.S[8 * c + 2 * q + 1]);
         g.rx[q] = uni((T)d.rf[8 * c + 2 * q]);
@@ -72,58 +75,105 @@ __device__ __forceinline__ Cell<T> load_cell(const DevSolve &d, int c, bool want
 // Venkatakrishnan smoothing relative to the cell value: e = kVkKappa |f_c|
 constexpr double kVkKappa = 1e-3;
 
+__device__ __forceinline__ double max2(double a, double b) { return fmax(a, b); }
+__device__ __forceinline__ float max2(float a, float b) { return fmaxf(a, b); }
+__device__ __forceinline__ double min2(double a, double b) { return fmin(a, b); }
+__device__ __forceinline__ float min2(float a, float b) { return fminf(a, b); }
+
+// Row of a cell in an array of `bytes` a cell, and those of its neighbours:
+// without bytes (all loads zero) behind boundary faces.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t cell_row(const void *p, int c, int bytes)
+{
+    return row_rsrc(static_cast<const char *>(p) + (size_t)c * bytes, bytes);
+}
+template <typename T>
+__device__ __forceinline__ void neighbour_rows(const void *p, const Cell<T> &g, int bytes, __amdgpu_buffer_rsrc_t (&r)[4])
+{
+#pragma unroll
+    for (int q = 0; q < 4; q++)
+        r[q] = row_rsrc(static_cast<const char *>(p) + (size_t)(g.nb[q] >= 0 ? g.nb[q] : g.c) * bytes,
+                        g.nb[q] >= 0 ? bytes : 0);
+}
+
+// Slopes of velocity k (layout: Slopes); nothing if !want.
+template <typename T>
+__device__ __forceinline__ Slopes<T> slope_load(__amdgpu_buffer_rsrc_t r, int k, int nv, bool want)
+{
+    const int off = want ? 16 * k : kOutside;
+    if constexpr (sizeof(T) == 8) {
+        const Vals<T, 1> a = row_load<T, 1, false>(r, off), b = row_load<T, 1, false>(r, off + 16 * nv);
+        return {{a.x[0], b.x[0]}, {a.y[0], b.y[0]}};
+    } else {
+        const Vals<T, 2> a = row_load<T, 2, false>(r, off);
+        return {{a.x[0], a.x[1]}, {a.y[0], a.y[1]}};
+    }
+}
+template <typename T>
+__device__ __forceinline__ void slope_store(__amdgpu_buffer_rsrc_t r, int k, int nv, const Slopes<T> &o)
+{
+    if constexpr (sizeof(T) == 8) {
+        row_store<T, 1, true>(r, 16 * k, Vals<T, 1>{{o.x[0]}, {o.y[0]}});
+        row_store<T, 1, true>(r, 16 * (k + nv), Vals<T, 1>{{o.x[1]}, {o.y[1]}});
+    } else {
+        row_store<T, 2, true>(r, 16 * k, Vals<T, 2>{{o.x[0], o.x[1]}, {o.y[0], o.y[1]}});
+    }
+}
+
 // Limited slope of one component: Green-Gauss gradient from the cell value
-// fc and the interior neighbours' values fn, then the Venkatakrishnan factor
-// p = min(1, min_q (D^2 + e^2 + 2 d D) / (D^2 + 2 d^2 + d D + e^2)) with d
-// the face's unlimited increment grad . r_q and D the room to the
-// neighbourhood's max (d > 0) or min, each term evaluated in the order
-// written here.  The smallest of the four fractions is found by comparing
-// cross products, then divided once (IEEE).  The limiter arithmetic is FP64
-// for both storage types, on d, D and e rescaled by the power of two nearest
-// 1 / |f_c| (exact, and the fractions are homogeneous of degree 0): squares
-// of values near the Maxwellian's tail (f ~ 1e-22 and below on common grids)
-// underflow in FP32, and the adjoint uses p on its own, not only p grad f.
+// fc and the interior neighbours' values fn (fc at a boundary face), then the
+// Venkatakrishnan factor p = min(1, min_q (D^2 + e^2 + 2 d D) / (D^2 + 2 d^2 +
+// d D + e^2)) with d the face's unlimited increment grad . r_q and D the room
+// to the neighbourhood's max (d > 0) or min.  For D > 0 the fraction is at
+// least 1 up to d = D / 2 and falls from there on (the sign of its derivative
+// is that of D^3 - 4 d D (d + D) + e^2 (D - 4 d)), so the smallest one of a
+// side is that of its largest |d|, or above 1: two fractions instead of four.
+// The smaller is found by comparing cross products, then divided once (IEEE).
+// The limiter arithmetic is FP64 for both storage types, on d, D and e
+// rescaled by the power of two nearest 1 / |f_c| (exact, and the fractions are
+// homogeneous of degree 0): squares of values near the Maxwellian's tail
+// (f ~ 1e-22 and below on common grids) underflow in FP32, and the adjoint
+// uses p on its own, not only p grad f.
 template <typename T>
 __device__ __forceinline__ void slope1(const Cell<T> &g, T fc, const T (&fn)[4], int lim, T &gx, T &gy, T &p)
 {
-    T lo = fc, hi = fc;
+    // FP64 from the differences (the face vectors of a cell add up to zero),
+    // with g.Sx, g.Sy as they are
+    T dq[4], hi = 0, lo = 0;
     gx = 0;
     gy = 0;
 #pragma unroll
     for (int q = 0; q < 4; q++) {
-        T b = fc;
-        if (g.nb[q] >= 0) {
-            b = (T)0.5 * (fc + fn[q]);
-            lo = fmin(lo, fn[q]);
-            hi = fmax(hi, fn[q]);
-        }
-        gx += b * g.Sx[q];
-        gy += b * g.Sy[q];
+        dq[q] = fn[q] - fc;
+        const T b = sizeof(T) == 8 ? dq[q] : (T)0.5 * (fc + fn[q]);
+        hi = max2(hi, dq[q]);
+        lo = min2(lo, dq[q]);
+        gx = madd(b, g.Sx[q], gx);
+        gy = madd(b, g.Sy[q], gy);
     }
-    gx *= g.iV;
-    gy *= g.iV;
-    double pd = 1.0;
+    const T h = sizeof(T) == 8 ? (T)0.5 * g.iV : g.iV;
+    gx *= h;
+    gy *= h;
+    p = 1;
     if (lim) {
         int ex = 0;
         (void)frexp((double)fc, &ex);
         const double sc = ldexp(1.0, -ex);
-        const double fcd = (double)fc * sc, e = kVkKappa * fcd, e2 = e * e;
-        const double hid = (double)hi * sc, lod = (double)lo * sc, gxd = (double)gx * sc, gyd = (double)gy * sc;
-        double bn = 1.0, bd = 1.0;   // smallest fraction so far (the cap 1 / 1)
+        const double e = kVkKappa * ((double)fc * sc), e2 = e * e;
+        const double Dh = (double)hi * sc, Dl = (double)lo * sc, gxd = (double)gx * sc, gyd = (double)gy * sc;
+        double dh = 0, dl = 0;       // largest increment of either sign
 #pragma unroll
         for (int q = 0; q < 4; q++) {
-            const double dq = gxd * (double)g.rx[q] + gyd * (double)g.ry[q];
-            const double D = dq > 0 ? hid - fcd : lod - fcd;
-            const double den = D * D + 2.0 * dq * dq + dq * D + e2;
-            const double num = D * D + e2 + 2.0 * dq * D;
-            if (den > 0 && num * bd < bn * den) {
-                bn = num;
-                bd = den;
-            }
+            const double t = fma(gxd, (double)g.rx[q], gyd * (double)g.ry[q]);
+            dh = max2(dh, t);
+            dl = min2(dl, t);
         }
-        pd = bn / bd;
+        const double ph = fma(Dh, Dh, e2), pl = fma(Dl, Dl, e2);
+        const double nh = fma(2.0 * dh, Dh, ph), mh = fma(dh, fma(2.0, dh, Dh), ph);
+        const double nl = fma(2.0 * dl, Dl, pl), ml = fma(dl, fma(2.0, dl, Dl), pl);
+        const bool low = !(mh > 0) || nl * mh < nh * ml;
+        const double n = low ? nl : nh, m = low ? ml : mh;
+        p = n < m ? (T)(n / m) : (T)1;   // 0 / 0: no increment, no limit
     }
-    p = (T)pd;
 }
 
 // the wave's cell of patch p, or -1 for an idle wave of a partial patch
@@ -134,73 +184,77 @@ __device__ __forceinline__ int patch_cell(const DevSolve &d, int p)
     return w < cnt ? c0 + w : -1;
 }
 
-// Limited slopes of f[par] into G and the wall cell's dF (PSI = false), or
-// the limiter factors into psi (PSI = true).
+// A launch takes the rows in slabs of kSlab velocities, one after the other:
+// each XCD all its patches for the first slab, then all for the second, so
+// that a row of patches and its neighbours fit the XCD's L2 together.  With
+// whole rows the neighbours came from memory again (256x128 cells with 48x48
+// velocities in FP64, reads over the arrays' size: slopes 2.0, E 2.3).  us
+// there, with slabs of 128 / 256 / 512 / all velocities: slopes 793 / 806 /
+// 829 / 884, c 802 / 799 / 801 / 837, psi 590 / 611 / 625 / 670, B 960 / 939 /
+// 948 / 965, E 888 / 894 / 920 / 1000.
+constexpr int kSlab = 256;
+__device__ __forceinline__ int slab_cell(const DevSolve &d, int b, int &k0, int &k1)
+{
+    const int per = (d.np + 7) >> 3, i = b >> 3, slab = i / per, p = (b & 7) * per + i - slab * per;
+    k0 = slab * kSlab;
+    k1 = min(k0 + kSlab, d.nv);
+    return p < d.np ? patch_cell(d, p) : -1;
+}
+static int slab_grid(const DevSolve &d) { return 8 * ((d.np + 7) / 8) * ((d.nv + kSlab - 1) / kSlab); }
+
+// Limited slopes of f[par] into G (PSI = false), or the limiter factors into
+// psi (PSI = true).
 template <typename T, bool PSI>
 __global__ __launch_bounds__(kSoBlock) void k_so_slope(DevSolve d, int par)
 {
-    using T2 = typename Vec2<T>::type;
-    const int p = xcd_item(d.np, blockIdx.x);
-    if (p < 0) return;
-    const int c = patch_cell(d, p);
-    if (c < 0) return;   // no barrier in this kernel
-    const int lane = threadIdx.x % kWave, nv = d.nv, n1 = d.n1, lim = d.limiter;
+    int k0, k1;
+    const int c = slab_cell(d, blockIdx.x, k0, k1);
+    if (c < 0) return;
+    const int lane = threadIdx.x % kWave, nv = d.nv, lim = d.limiter, rowb = nv * 2 * (int)sizeof(T);
     const Cell<T> g = load_cell<T>(d, c, false);
-    const T2 *__restrict__ f = static_cast<const T2 *>(d.f[par]);
-    T2 *__restrict__ G = static_cast<T2 *>(d.G);
-    T2 *__restrict__ psi = static_cast<T2 *>(d.psi);
-    const int wl = g.nb[0] <= -2 ? -2 - g.nb[0] : -1;
-    double S0x = 0, S0y = 0, mdF = 0;
-    if (wl >= 0) {
-        S0x = uni(d.S[8 * c]);
-        S0y = uni(d.S[8 * c + 1]);
-    }
-    int a = lane % n1, b = lane / n1;
-    const int da = kWave % n1, db = kWave / n1;
-    for (int k = lane; k < nv; k += kWave) {
-        const T2 fc = f[g.row + k];
-        T f1[4], f2[4];
+    const __amdgpu_buffer_rsrc_t own = cell_row(d.f[par], c, rowb);
+    const __amdgpu_buffer_rsrc_t dst = PSI ? cell_row(d.psi, c, rowb) : cell_row(d.G, c, 2 * rowb);
+    __amdgpu_buffer_rsrc_t nbr[4];
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const T2 t = f[g.nrow[q] + k];   // boundary faces read the own row and ignore it
-            f1[q] = t.x;
-            f2[q] = t.y;
-        }
+    for (int q = 0; q < 4; q++) nbr[q] = cell_row(d.f[par], g.nb[q] >= 0 ? g.nb[q] : c, rowb);
+    for (int k = k0 + lane; k < k1; k += kWave) {
+        const int off = k * 2 * (int)sizeof(T);
+        const Vals<T, 1> fc = row_load<T, 1, false>(own, off);
+        Vals<T, 1> fn[4];
+#pragma unroll
+        for (int q = 0; q < 4; q++) fn[q] = row_load<T, 1, false>(nbr[q], off);
+        const T f1[4] = {fn[0].x[0], fn[1].x[0], fn[2].x[0], fn[3].x[0]};
+        const T f2[4] = {fn[0].y[0], fn[1].y[0], fn[2].y[0], fn[3].y[0]};
         T g1x, g1y, p1, g2x, g2y, p2;
-        slope1(g, fc.x, f1, lim, g1x, g1y, p1);
-        slope1(g, fc.y, f2, lim, g2x, g2y, p2);
+        slope1(g, fc.x[0], f1, lim, g1x, g1y, p1);
+        slope1(g, fc.y[0], f2, lim, g2x, g2y, p2);
         if constexpr (PSI) {
-            __builtin_nontemporal_store(p1, &psi[g.row + k].x);
-            __builtin_nontemporal_store(p2, &psi[g.row + k].y);
+            row_store<T, 1, true>(dst, off, Vals<T, 1>{{p1}, {p2}});
         } else {
-            T2 o1, o2;
-            o1.x = p1 * g1x;
-            o1.y = p1 * g1y;
-            o2.x = p2 * g2x;
-            o2.y = p2 * g2y;
-            __builtin_nontemporal_store(o1.x, &G[2 * (g.row + k)].x);
-            __builtin_nontemporal_store(o1.y, &G[2 * (g.row + k)].y);
-            __builtin_nontemporal_store(o2.x, &G[2 * (g.row + k) + 1].x);
-            __builtin_nontemporal_store(o2.y, &G[2 * (g.row + k) + 1].y);
-            if (wl >= 0) {
-                const double s0 = d.vx[a] * S0x + d.vy[b] * S0y;
-                if (s0 > 0) mdF += d.wx[a] * d.wy[b] * s0 * (double)(o1.x * g.rx[0] + o1.y * g.ry[0]);
-            }
-        }
-        a += da;
-        b += db;
-        if (a >= n1) {
-            a -= n1;
-            b++;
+            const Slopes<T> o = {{p1 * g1x, p2 * g2x}, {p1 * g1y, p2 * g2y}};
+            slope_store(dst, k, nv, o);
         }
     }
-    if constexpr (!PSI) {
-        if (wl >= 0) {
-            double acc[1] = {mdF};
-            wave_sum<1>(acc);
-            if (lane == 0) d.dF[wl] = acc[0] / d.wall_A[wl];
-        }
+}
+
+// dF_l: what the slopes of the wall cell add to the wall flux F_l; one block
+// per element
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_so_wall(DevSolve d)
+{
+    __shared__ double red[kBlock / kWave];
+    const int l = blockIdx.x, c = d.wall_cell[l];
+    const double S0x = d.S[8 * c], S0y = d.S[8 * c + 1];
+    const T rx = (T)d.rf[8 * c], ry = (T)d.rf[8 * c + 1];
+    double acc[1] = {0};
+    for (int k = threadIdx.x; k < d.nv; k += kBlock) {
+        const int a = k % d.n1, b = k / d.n1;
+        const Slopes<T> o = slopes_at<T>(d, c, k);
+        const double s0 = d.vx[a] * S0x + d.vy[b] * S0y;
+        if (s0 > 0) acc[0] += d.wx[a] * d.wy[b] * s0 * (double)(o.x[0] * rx + o.y[0] * ry);
     }
+    block_sum<1>(acc, red);
+    if (threadIdx.x == 0) d.dF[l] = acc[0] / d.wall_A[l];
 }
 
 // c = sum_q (v.S_q) G_u . (m_q - x_u) with u the upwind cell of face q
@@ -208,46 +262,37 @@ __global__ __launch_bounds__(kSoBlock) void k_so_slope(DevSolve d, int par)
 template <typename T>
 __global__ __launch_bounds__(kSoBlock) void k_so_corr(DevSolve d)
 {
-    using T2 = typename Vec2<T>::type;
-    const int p = xcd_item(d.np, blockIdx.x);
-    if (p < 0) return;
-    const int c = patch_cell(d, p);
+    int k0, k1;
+    const int c = slab_cell(d, blockIdx.x, k0, k1);
     if (c < 0) return;
-    const int lane = threadIdx.x % kWave, nv = d.nv, n1 = d.n1;
+    const int lane = threadIdx.x % kWave, nv = d.nv, n1 = d.n1, rowb = nv * 2 * (int)sizeof(T);
     const Cell<T> g = load_cell<T>(d, c, true);
-    const T2 *__restrict__ G = static_cast<const T2 *>(d.G);
-    T2 *__restrict__ out = static_cast<T2 *>(d.corr);
-    int a = lane % n1, b = lane / n1;
+    const __amdgpu_buffer_rsrc_t own = cell_row(d.G, c, 2 * rowb), dst = cell_row(d.corr, c, rowb);
+    __amdgpu_buffer_rsrc_t nbr[4];
+    neighbour_rows(d.G, g, 2 * rowb, nbr);
+    int a = (k0 + lane) % n1, b = (k0 + lane) / n1;
     const int da = kWave % n1, db = kWave / n1;
-    for (int k = lane; k < nv; k += kWave) {
+    for (int k = k0 + lane; k < k1; k += kWave) {
         const T v1 = (T)d.vx[a], v2 = (T)d.vy[b];
-        const T2 o1 = G[2 * (g.row + k)], o2 = G[2 * (g.row + k) + 1];
+        const Slopes<T> o = slope_load<T>(own, k, nv, true);
         // a neighbour's slopes are needed only where it is upwind
         T sq[4];
-        T2 n1v[4], n2v[4];
+        Slopes<T> n[4];
 #pragma unroll
         for (int q = 0; q < 4; q++) {
-            sq[q] = v1 * g.Sx[q] + v2 * g.Sy[q];
-            n1v[q] = n2v[q] = T2{0, 0};
-            if (!(sq[q] > 0) && g.nb[q] >= 0) {
-                n1v[q] = G[2 * (g.nrow[q] + k)];
-                n2v[q] = G[2 * (g.nrow[q] + k) + 1];
-            }
+            sq[q] = madd(v2, g.Sy[q], v1 * g.Sx[q]);
+            n[q] = slope_load<T>(nbr[q], k, nv, !(sq[q] > 0));
         }
-        T c1 = 0, c2 = 0;
+        Vals<T, 1> r = {{0}, {0}};
 #pragma unroll
         for (int q = 0; q < 4; q++) {
-            const T s = sq[q];
-            if (s > 0) {
-                c1 += s * (o1.x * g.rx[q] + o1.y * g.ry[q]);
-                c2 += s * (o2.x * g.rx[q] + o2.y * g.ry[q]);
-            } else if (g.nb[q] >= 0) {
-                c1 += s * (n1v[q].x * g.nx[q] + n1v[q].y * g.ny[q]);
-                c2 += s * (n2v[q].x * g.nx[q] + n2v[q].y * g.ny[q]);
-            }
+            const T sp = max0(sq[q]), sm = min0(sq[q]);
+            r.x[0] = madd(sp, madd(o.y[0], g.ry[q], o.x[0] * g.rx[q]), r.x[0]);
+            r.y[0] = madd(sp, madd(o.y[1], g.ry[q], o.x[1] * g.rx[q]), r.y[0]);
+            r.x[0] = madd(sm, madd(n[q].y[0], g.ny[q], n[q].x[0] * g.nx[q]), r.x[0]);
+            r.y[0] = madd(sm, madd(n[q].y[1], g.ny[q], n[q].x[1] * g.nx[q]), r.y[0]);
         }
-        __builtin_nontemporal_store(c1, &out[g.row + k].x);
-        __builtin_nontemporal_store(c2, &out[g.row + k].y);
+        row_store<T, 1, true>(dst, k * 2 * (int)sizeof(T), r);
         a += da;
         b += db;
         if (a >= n1) {
@@ -262,61 +307,45 @@ __global__ __launch_bounds__(kSoBlock) void k_so_corr(DevSolve d)
 template <typename T>
 __global__ __launch_bounds__(kSoBlock) void k_so_adj_b(DevSolve d, int par)
 {
-    using T2 = typename Vec2<T>::type;
-    const int p = xcd_item(d.np, blockIdx.x);
-    if (p < 0) return;
-    const int c = patch_cell(d, p);
+    int k0, k1;
+    const int c = slab_cell(d, blockIdx.x, k0, k1);
     if (c < 0) return;
-    const int lane = threadIdx.x % kWave, nv = d.nv, n1 = d.n1, obj = d.objective;
+    const int lane = threadIdx.x % kWave, nv = d.nv, n1 = d.n1, obj = d.objective, rowb = nv * 2 * (int)sizeof(T);
     const Cell<T> g = load_cell<T>(d, c, false);
-    const T2 *__restrict__ phi = static_cast<const T2 *>(d.phi[par]);
-    const T2 *__restrict__ psi = static_cast<const T2 *>(d.psi);
-    T2 *__restrict__ B = static_cast<T2 *>(d.G);
+    const __amdgpu_buffer_rsrc_t own = cell_row(d.phi[par], c, rowb), lim = cell_row(d.psi, c, rowb);
+    const __amdgpu_buffer_rsrc_t dst = cell_row(d.G, c, 2 * rowb);
+    __amdgpu_buffer_rsrc_t nbr[4];
+    neighbour_rows(d.phi[par], g, rowb, nbr);
     const int wl = g.nb[0] <= -2 ? -2 - g.nb[0] : -1;
     const T Phi_w = wl >= 0 ? uni((T)d.Phi[par][wl]) : (T)0;
-    int a = lane % n1, b = lane / n1;
+    int a = (k0 + lane) % n1, b = (k0 + lane) / n1;
     const int da = kWave % n1, db = kWave / n1;
-    for (int k = lane; k < nv; k += kWave) {
+    for (int k = k0 + lane; k < k1; k += kWave) {
+        const int off = k * 2 * (int)sizeof(T);
         const double v1d = d.vx[a], v2d = d.vy[b];
         const T v1 = (T)v1d, v2 = (T)v2d;
-        const T2 pu = phi[g.row + k], ps = psi[g.row + k];
+        const Vals<T, 1> pu = row_load<T, 1, false>(own, off), ps = row_load<T, 1, false>(lim, off);
         // a neighbour's phi is needed only where it is downwind
         T sq[4];
-        T2 pd[4];
+        Vals<T, 1> pd[4];
 #pragma unroll
         for (int q = 0; q < 4; q++) {
-            sq[q] = v1 * g.Sx[q] + v2 * g.Sy[q];
-            pd[q] = T2{0, 0};
-            if (sq[q] > 0 && g.nb[q] >= 0) pd[q] = phi[g.nrow[q] + k];
+            sq[q] = madd(v2, g.Sy[q], v1 * g.Sx[q]);
+            pd[q] = row_load<T, 1, false>(nbr[q], sq[q] > 0 ? off : kOutside);
         }
-        T b1x = 0, b1y = 0, b2x = 0, b2y = 0;
+        if (wl >= 0) pd[0].x[0] = Phi_w - (T)mJ_of(obj, v1d, v2d);
+        Slopes<T> o = {{0, 0}, {0, 0}};
 #pragma unroll
         for (int q = 0; q < 4; q++) {
-            const T s = sq[q];
-            if (s > 0) {
-                T d1 = 0, d2 = 0;
-                if (g.nb[q] >= 0) {
-                    d1 = pd[q].x;
-                    d2 = pd[q].y;
-                } else if (g.nb[q] <= -2) {
-                    d1 = Phi_w - (T)mJ_of(obj, v1d, v2d);
-                }
-                const T a1 = s * (pu.x - d1), a2 = s * (pu.y - d2);
-                b1x += a1 * g.rx[q];
-                b1y += a1 * g.ry[q];
-                b2x += a2 * g.rx[q];
-                b2y += a2 * g.ry[q];
-            }
+            const T s = max0(sq[q]);
+            const T a1 = s * (pu.x[0] - pd[q].x[0]), a2 = s * (pu.y[0] - pd[q].y[0]);
+            o.x[0] = madd(a1, g.rx[q], o.x[0]);
+            o.y[0] = madd(a1, g.ry[q], o.y[0]);
+            o.x[1] = madd(a2, g.rx[q], o.x[1]);
+            o.y[1] = madd(a2, g.ry[q], o.y[1]);
         }
-        // plain stores: non-temporal ones made this kernel 0.26 ms slower on
-        // the 256x128 C-grid with 2304 velocities (they help the slopes' G)
-        T2 o1, o2;
-        o1.x = b1x * ps.x;
-        o1.y = b1y * ps.x;
-        o2.x = b2x * ps.y;
-        o2.y = b2y * ps.y;
-        B[2 * (g.row + k)] = o1;
-        B[2 * (g.row + k) + 1] = o2;
+        slope_store(dst, k, nv,
+                    Slopes<T>{{o.x[0] * ps.x[0], o.x[1] * ps.y[0]}, {o.y[0] * ps.x[0], o.y[1] * ps.y[0]}});
         a += da;
         b += db;
         if (a >= n1) {
@@ -332,40 +361,30 @@ __global__ __launch_bounds__(kSoBlock) void k_so_adj_b(DevSolve d, int par)
 template <typename T>
 __global__ __launch_bounds__(kSoBlock) void k_so_adj_e(DevSolve d)
 {
-    using T2 = typename Vec2<T>::type;
-    const int p = xcd_item(d.np, blockIdx.x);
-    if (p < 0) return;
-    const int c = patch_cell(d, p);
+    int k0, k1;
+    const int c = slab_cell(d, blockIdx.x, k0, k1);
     if (c < 0) return;
-    const int lane = threadIdx.x % kWave, nv = d.nv;
+    const int lane = threadIdx.x % kWave, nv = d.nv, rowb = nv * 2 * (int)sizeof(T);
     const Cell<T> g = load_cell<T>(d, c, true);
-    const T2 *__restrict__ B = static_cast<const T2 *>(d.G);
-    T2 *__restrict__ out = static_cast<T2 *>(d.corr);
-    for (int k = lane; k < nv; k += kWave) {
-        const T2 o1 = B[2 * (g.row + k)], o2 = B[2 * (g.row + k) + 1];
-        T2 n1v[4], n2v[4];
+    const __amdgpu_buffer_rsrc_t own = cell_row(d.G, c, 2 * rowb), dst = cell_row(d.corr, c, rowb);
+    __amdgpu_buffer_rsrc_t nbr[4];
+    neighbour_rows(d.G, g, 2 * rowb, nbr);
+    for (int k = k0 + lane; k < k1; k += kWave) {
+        const Slopes<T> o = slope_load<T>(own, k, nv, true);
+        Slopes<T> n[4];
+#pragma unroll
+        for (int q = 0; q < 4; q++) n[q] = slope_load<T>(nbr[q], k, nv, true);
+        T e[2] = {0, 0};
 #pragma unroll
         for (int q = 0; q < 4; q++) {
-            n1v[q] = B[2 * (g.nrow[q] + k)];
-            n2v[q] = B[2 * (g.nrow[q] + k) + 1];
-        }
-        T e1 = 0, e2 = 0;
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const T t1 = (o1.x * g.Sx[q] + o1.y * g.Sy[q]) * g.iV;
-            const T t2 = (o2.x * g.Sx[q] + o2.y * g.Sy[q]) * g.iV;
-            if (g.nb[q] >= 0) {
-                const T u1 = (n1v[q].x * g.Sx[q] + n1v[q].y * g.Sy[q]) * g.iVn[q];
-                const T u2 = (n2v[q].x * g.Sx[q] + n2v[q].y * g.Sy[q]) * g.iVn[q];
-                e1 += (T)0.5 * (t1 - u1);
-                e2 += (T)0.5 * (t2 - u2);
-            } else {
-                e1 += t1;
-                e2 += t2;
+            for (int i = 0; i < 2; i++) {
+                const T t = madd(o.y[i], g.Sy[q], o.x[i] * g.Sx[q]) * g.iV;
+                const T u = madd(n[q].y[i], g.Sy[q], n[q].x[i] * g.Sx[q]) * g.iVn[q];
+                e[i] += g.nb[q] >= 0 ? (T)0.5 * (t - u) : t;
             }
         }
-        __builtin_nontemporal_store(e1, &out[g.row + k].x);
-        __builtin_nontemporal_store(e2, &out[g.row + k].y);
+        row_store<T, 1, true>(dst, k * 2 * (int)sizeof(T), Vals<T, 1>{{e[0]}, {e[1]}});
     }
 }
 
@@ -391,10 +410,10 @@ __global__ __launch_bounds__(kBlock) void k_so_objective_elem(DevSolve d, int pa
         const double vn = v1 * n1 + v2 * n2;
         const double wm = d.wx[a] * d.wy[b] * mJ_of(d.objective, v1, v2);
         if (vn > 0) {
-            const T2 fc = f[g.row + k];
+            const T2 fc = f[(size_t)c * d.nv + k];
             T f1[4];
 #pragma unroll
-            for (int q = 0; q < 4; q++) f1[q] = f[g.nrow[q] + k].x;
+            for (int q = 0; q < 4; q++) f1[q] = f[(size_t)(g.nb[q] >= 0 ? g.nb[q] : c) * d.nv + k].x;
             T gx, gy, p1;
             slope1(g, fc.x, f1, d.limiter, gx, gy, p1);
             const double delta = (double)((p1 * gx) * g.rx[0] + (p1 * gy) * g.ry[0]);
@@ -413,28 +432,30 @@ __global__ __launch_bounds__(kBlock) void k_so_objective_elem(DevSolve d, int pa
 
 hipError_t launch_so_slopes(const DevSolve &d, int par, hipStream_t st)
 {
-    DVM_DISPATCH(d.mixed, hipLaunchKernelGGL((k_so_slope<T, false>), dim3(xcd_grid(d.np)), dim3(kSoBlock), 0, st, d, par));
+    DVM_DISPATCH(d.mixed, hipLaunchKernelGGL((k_so_slope<T, false>), dim3(slab_grid(d)), dim3(kSoBlock), 0, st, d, par));
+    if (hipError_t e = hipGetLastError()) return e;
+    if (d.nw > 0) DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(k_so_wall<T>, dim3(d.nw), dim3(kBlock), 0, st, d));
     return hipGetLastError();
 }
 
 hipError_t launch_so_correction(const DevSolve &d, int par, hipStream_t st)
 {
     if (hipError_t e = launch_so_slopes(d, par, st)) return e;
-    DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(k_so_corr<T>, dim3(xcd_grid(d.np)), dim3(kSoBlock), 0, st, d));
+    DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(k_so_corr<T>, dim3(slab_grid(d)), dim3(kSoBlock), 0, st, d));
     return hipGetLastError();
 }
 
 hipError_t launch_so_freeze(const DevSolve &d, int fpar, hipStream_t st)
 {
-    DVM_DISPATCH(d.mixed, hipLaunchKernelGGL((k_so_slope<T, true>), dim3(xcd_grid(d.np)), dim3(kSoBlock), 0, st, d, fpar));
+    DVM_DISPATCH(d.mixed, hipLaunchKernelGGL((k_so_slope<T, true>), dim3(slab_grid(d)), dim3(kSoBlock), 0, st, d, fpar));
     return hipGetLastError();
 }
 
 hipError_t launch_so_adjoint_term(const DevSolve &d, int par, hipStream_t st)
 {
-    DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(k_so_adj_b<T>, dim3(xcd_grid(d.np)), dim3(kSoBlock), 0, st, d, par));
+    DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(k_so_adj_b<T>, dim3(slab_grid(d)), dim3(kSoBlock), 0, st, d, par));
     if (hipError_t e = hipGetLastError()) return e;
-    DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(k_so_adj_e<T>, dim3(xcd_grid(d.np)), dim3(kSoBlock), 0, st, d));
+    DVM_DISPATCH(d.mixed, hipLaunchKernelGGL(k_so_adj_e<T>, dim3(slab_grid(d)), dim3(kSoBlock), 0, st, d));
     return hipGetLastError();
 }
 

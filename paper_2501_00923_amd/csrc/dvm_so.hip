@@ -22,13 +22,13 @@
 // order), one wave per cell, a lane per velocity; per-cell constants in
 // scalar registers.  Each kernel reads its cell's row and its interior
 // neighbours' rows (in L2 for the same reasons as in the sweeps) and writes
-// one row.  All are bound by memory; 256x128 cells with 48x48 velocities
-// in FP64, us: slopes 806 (from 1045, when the limiter took four fractions and
-// bound them), psi 611 (867), c 799 (868), B 939 (1084), E 894 (1004).  Rows
-// go through buffer accesses whose range check drops
-// what is not wanted (a boundary face's neighbour, a face that the velocity
-// does not cross that way), so a step issues its loads together without a
-// branch.  FP32 expressions keep their order and roundings.
+// one row.  All are bound by memory; 256x128 cells with 48x48 velocities in
+// FP64, us: slopes 806 (1045 when the limiter took four fractions and bound
+// them), psi 611 (867), c 799 (868), B 939 (1084), E 894 (1004).  Rows go
+// through buffer accesses whose range check drops what is not wanted (a
+// boundary face's neighbour, a face that the velocity does not cross that
+// way), so a step issues its loads together without a branch.  FP32
+// expressions keep their order and roundings.
 
 #include "dvm_walk.h"
 

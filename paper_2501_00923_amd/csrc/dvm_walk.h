@@ -151,7 +151,7 @@ struct alignas(16) AdjRow {
     double e, ec, ecc, pad;
 };
 
-// the workgroup's dynamic LDS (launch bytes: sweep_lds of dvm_internal.h)
+// the workgroup's dynamic LDS (launch bytes: primal_lds, adjoint_lds)
 extern __shared__ __align__(16) unsigned char sweep_smem[];
 
 // The adjoint's sums of a thread over the walks before the current one, parked

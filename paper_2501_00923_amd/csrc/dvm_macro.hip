@@ -43,13 +43,25 @@ constexpr double kMacroCFL = 1000.0;
 // is what flows into the neighbour, so
 //   r_c = sum_q O_cq - sum_q O_nq' + (boundary inflow) + V/tau (W - m(P'))
 // needs every row once, by its own cell (k_macro_flux), and a sum over faces
-// (k_macro_resid): f is read once and no neighbour row with it.  The
+// (k_macro_resid): f is read once and no neighbour row with it, but across the
+// cuts of the mesh (cut_face).  The
 // collision part takes the moments of f from the sweep (W) and those of the
 // equilibrium from 1-D sums.  k_macro_flux leaves O_cq [face][moment] in the
 // face-block table mO (the blocks come after it) and the rest of r_c in mr.
 // 256x128 cells with 64x64 velocities in FP64 516 us (725 with each cell
 // reading its upwind neighbours' rows), 128x64 with 32x32 in FP32 35 us (64).
 // ---------------------------------------------------------------------------
+// Faces whose two sides take their vectors from nodes stored apart: the
+// O-grid's seam and the C-grid's wake cut (n: the neighbour across face q of
+// c).  Only inside the mesh is S_nq' the very negative of S_cq; on a cut the
+// residual sums the neighbour's row with the cell's own vector, as the sweep
+// does, or the iteration would not stop at the sweep's solution.
+__device__ __forceinline__ bool cut_face(const DevSolve &d, int c, int q, int n)
+{
+    const int m = d.cell_of[c], i = m % d.ni;
+    return n >= 0 && (d.topo == 0 ? (q == 1 && i == d.ni - 1) || (q == 3 && i == 0) : q == 0 && m < d.ni);
+}
+
 template <typename T, int V>
 __device__ __forceinline__ void macro_flux_cell(const DevSolve &d, int par, int c, bool act, int lane)
 {
@@ -82,11 +94,19 @@ __device__ __forceinline__ void macro_flux_cell(const DevSolve &d, int par, int 
         Sy[q] = uni(d.S[8 * c + 2 * q + 1]);
     }
     const int rowb = d.nv * 2 * (int)sizeof(T), bstep = d.lm.brow * d.n1 * 2 * (int)sizeof(T);
-    const __amdgpu_buffer_rsrc_t src = row_rsrc(static_cast<const char *>(d.f[par]) + (size_t)c * rowb, rowb);
-    const bool edge = nb[0] < 0 || nb[1] < 0 || nb[2] < 0 || nb[3] < 0;
+    const char *f0 = static_cast<const char *>(d.f[par]);
+    const __amdgpu_buffer_rsrc_t src = row_rsrc(f0 + (size_t)c * rowb, rowb);
+    // faces whose inflow is summed here, and their source rows
+    bool edge[4];
+    __amdgpu_buffer_rsrc_t inflow[4];
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        edge[q] = uni((int)(nb[q] < 0 || cut_face(d, c, q, nb[q]))) != 0;
+        inflow[q] = row_rsrc(nb[q] >= 0 ? f0 + (size_t)nb[q] * rowb : static_cast<const char *>(nb[q] == -1 ? d.fd : d.gw2), rowb);
+    }
+    const bool any = edge[0] || edge[1] || edge[2] || edge[3];
     const int wl = nb[0] <= -2 ? -2 - nb[0] : -1;
     const double ratio = wl >= 0 ? d.F[par][wl] / d.D[wl] : 0.0;
-    const __amdgpu_buffer_rsrc_t far = row_rsrc(d.fd, rowb), wall = row_rsrc(d.gw2, rowb);
     __syncthreads();
     const double thw2 = 0.5 * d.theta_w;
     double O[4][4] = {}, in[4] = {0, 0, 0, 0};
@@ -115,18 +135,21 @@ __device__ __forceinline__ void macro_flux_cell(const DevSolve &d, int par, int 
                 O[q][2] = fma(rf.wv, t, O[q][2]);
                 O[q][3] = fma(rf.wh, t, fma(rf.w, tz, O[q][3]));
             }
-            if (edge) {
-                // inflow through the far-field and wall faces
-                const Vals<T, V> gf = row_load<T, V, false>(far, off), gw = row_load<T, V, false>(wall, off);
+            if (any) {
+                // inflow through the far-field, wall and cut faces
 #pragma unroll
                 for (int q = 0; q < 4; q++) {
-                    if (nb[q] >= 0) continue;
+                    if (!edge[q]) continue;
+                    const Vals<T, V> g = row_load<T, V, false>(inflow[q], off);
 #pragma unroll
                     for (int v = 0; v < V; v++) {
                         const double v1 = col[v].v, ws = col[v].w * rf.w * min0(v1 * Sx[q] + rf.v * Sy[q]);
-                        const double g = ratio * (double)gw.x[v];
-                        const double i1 = ws * (nb[q] == -1 ? (double)gf.x[v] : g);
-                        const double i2 = ws * (nb[q] == -1 ? (double)gf.y[v] : thw2 * g);
+                        double g1 = (double)g.x[v], g2 = (double)g.y[v];
+                        if (q == 0 && wl >= 0) {
+                            g1 *= ratio;
+                            g2 = thw2 * g1;
+                        }
+                        const double i1 = ws * g1, i2 = ws * g2;
                         in[0] += i1;
                         in[1] = fma(v1, i1, in[1]);
                         in[2] = fma(rf.v, i1, in[2]);
@@ -140,7 +163,7 @@ __device__ __forceinline__ void macro_flux_cell(const DevSolve &d, int par, int 
     const double v1[8] = {O[2][0], O[2][1], O[2][2], O[2][3], O[3][0], O[3][1], O[3][2], O[3][3]};
     const double s0 = wave_scatter8(v0), s1 = wave_scatter8(v1);
     double ins = 0;
-    if (edge) {
+    if (any) {
         const double v2[8] = {in[0], in[1], in[2], in[3], 0, 0, 0, 0};
         ins = wave_scatter8(v2);
     }
@@ -195,7 +218,7 @@ __global__ __launch_bounds__(kBlock) void k_macro_resid(DevSolve d)
     for (int q = 0; q < 4; q++) {
         const int n = d.nbr[4 * c + q];
         r += d.mO[64 * (size_t)c + 4 * q + m];
-        if (n >= 0) r -= d.mO[64 * (size_t)n + 4 * back_face(d, n, c) + m];
+        if (n >= 0 && !cut_face(d, c, q, n)) r -= d.mO[64 * (size_t)n + 4 * back_face(d, n, c) + m];
     }
     d.mr[4 * c + m] = r;
 }

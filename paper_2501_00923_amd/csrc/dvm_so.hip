@@ -137,20 +137,22 @@ template <typename T>
 __device__ __forceinline__ void slope1(const Cell<T> &g, T fc, const T (&fn)[4], int lim, T &gx, T &gy, T &p)
 {
     // FP64 from the differences (the face vectors of a cell add up to zero),
-    // with g.Sx, g.Sy as they are
-    T dq[4], hi = 0, lo = 0;
+    // with g.Sx, g.Sy as they are; FP32 from the values, so that D is taken in
+    // FP64 without a rounding to FP32 before
+    constexpr bool kDiff = sizeof(T) == 8;
+    T hi = kDiff ? (T)0 : fc, lo = hi;
     gx = 0;
     gy = 0;
 #pragma unroll
     for (int q = 0; q < 4; q++) {
-        dq[q] = fn[q] - fc;
-        const T b = sizeof(T) == 8 ? dq[q] : (T)0.5 * (fc + fn[q]);
-        hi = max2(hi, dq[q]);
-        lo = min2(lo, dq[q]);
+        const T x = kDiff ? fn[q] - fc : fn[q];
+        const T b = kDiff ? x : (T)0.5 * (fc + fn[q]);
+        hi = max2(hi, x);
+        lo = min2(lo, x);
         gx = madd(b, g.Sx[q], gx);
         gy = madd(b, g.Sy[q], gy);
     }
-    const T h = sizeof(T) == 8 ? (T)0.5 * g.iV : g.iV;
+    const T h = kDiff ? (T)0.5 * g.iV : g.iV;
     gx *= h;
     gy *= h;
     p = 1;
@@ -159,7 +161,8 @@ __device__ __forceinline__ void slope1(const Cell<T> &g, T fc, const T (&fn)[4],
         (void)frexp((double)fc, &ex);
         const double sc = ldexp(1.0, -ex);
         const double e = kVkKappa * ((double)fc * sc), e2 = e * e;
-        const double Dh = (double)hi * sc, Dl = (double)lo * sc, gxd = (double)gx * sc, gyd = (double)gy * sc;
+        const double f0 = kDiff ? 0.0 : (double)fc;
+        const double Dh = ((double)hi - f0) * sc, Dl = ((double)lo - f0) * sc, gxd = (double)gx * sc, gyd = (double)gy * sc;
         double dh = 0, dl = 0;       // largest increment of either sign
 #pragma unroll
         for (int q = 0; q < 4; q++) {

@@ -350,11 +350,13 @@ __device__ __forceinline__ void moments_cell(const DevSolve &d, int par, int c, 
 // of one cell: phi . dg/dP for P = (rho, u1, u2, theta) from
 // A0 = sum w g1 qq, A1 = sum w g1 c1 qq, A2, A3 = sum w g1 |c|^2 qq and
 // A4 = sum w g1 phi2 (qq = phi1 + theta/2 phi2, c = v - u); the rho_tau sum
-// sum w (phi . (g - f)) = A0 - R, R = sum w phi . f; the wall multiplier sum
-// Pw over the wall face's incoming velocities.  Per walk the sums over
-// the grid rows carry w Y c2^p (AdjRow); the factors w gc X(v1), c1 join once
-// per walk.  Shared by the adjoint sweep's epilogue and k_adjoint_moments, so
-// both give the same bits.
+// T = sum w (phi . (g - f)); the wall multiplier sum Pw over the wall face's
+// incoming velocities.  Per walk the sums over the grid rows carry w Y c2^p
+// (AdjRow) and R = sum w phi . f; the factors w gc X(v1), c1 join once per
+// walk.  T takes the difference of A0 and R there, lane by lane: g and f nearly
+// cancel near the continuum, and the cells' totals subtracted at the end lose
+// twice the rounding (relative to A0 1.4e-16 against 0.8e-16).  Shared by the
+// adjoint sweep's epilogue and k_adjoint_moments, so both give the same bits.
 // ---------------------------------------------------------------------------
 // Per-cell constants: the frozen velocity u1, theta/2, theta_w/2, the wall
 // face vector and wall element (-1: none), objective.
@@ -432,13 +434,13 @@ struct AdjMoments {
             t[2] = fma(g, Qc[v], t[2]);
             t[3] = fma(gQ, c1 * c1, fma(g, Qcc[v], t[3]));
             t[4] = fma(g, E[v], t[4]);
-            t[5] = fma(col[v].w, R[v], t[5]);
+            t[5] += fma(-col[v].w, R[v], gQ);
         }
 #pragma unroll
         for (int i = 0; i < 6; i++) m[i] = t[i];
         clear();
     }
-    // totals: A0..A4, R, Pw
+    // totals: A0..A4, T, Pw
     __device__ __forceinline__ void total(double (&o)[7])
     {
 #pragma unroll
@@ -465,7 +467,7 @@ __device__ __forceinline__ void adjoint_store(const DevSolve &d, double rho, dou
     double s = (q < 2 ? (q == 0 ? P0 : P1) : (q == 2 ? P2 : P3)) * M;
     s += dpp_move<0x128>(s);                                    // lane ^ 8
     s += dpp_move<0x124>(s);                                    // lane - 4 in the row of 16
-    if (lane == 4) s = (acc[0] - acc[5]) * itau;
+    if (lane == 4) s = acc[5] * itau;
     if (act && lane < 5) ao[lane] = s;
     if (act && wl >= 0 && lane == 0) Phi[wl] = -acc[6] / (d.wall_A[wl] * d.D[wl]);
 }

@@ -14,7 +14,9 @@ SOURCES = [os.path.join(CSRC, f) for f in ("dvm_kernels.hip", "dvm_sens.hip", "d
 # -packed-fp32-ops: keep the compiler from emitting packed FP32 VALU ops.
 # -ffp-contract=off: every a*b+c is rounded as written, so a kernel body gives
 # the same bits whichever kernel inlines it (single solve vs batch) and the
-# velocity-face products v.S that decide upwinding round like the oracle's.
+# velocity-face products v.S that decide upwinding in the sweeps round like the
+# oracle's.  (The second-order terms write theirs with fma in FP64: where the
+# two signs differ, v.S and so the term are of rounding size.)
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function", "-Wno-unused-command-line-argument"]

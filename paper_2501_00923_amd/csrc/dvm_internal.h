@@ -24,7 +24,7 @@ constexpr int kEqState = 20;       // doubles per cell of mstate: P' (4), dP'/dW
 constexpr int kPatchI = 2, kPatchJ = 2, kPatchCells = kPatchI * kPatchJ;
 constexpr int kTileI = 32, kTileJ = 16;
 
-// How a wave's lanes walk one cell's velocities (Walk in dvm_kernels.hip).
+// How a wave's lanes walk one cell's velocities (Walk in dvm_walk.h).
 // In units of V adjacent velocities (V = 2 in FP32 with an even n1), a grid
 // row holds na units.  Walk i of `isteps` gives lane l the unit
 // k = i ks + l, column m + i as and row r of r = k / width, m = k % width,
@@ -39,7 +39,9 @@ struct LaneMap {
 
 // Two shapes of walk.  "phase": the units in storage order, 64 a step; the
 // column of a lane repeats after isteps = na / gcd(64, na) steps, so the steps
-// are taken isteps apart.  "block": lane rows of la units, 64 / la of them.
+// are taken isteps apart; with na odd that is mostly one step a walk (27x31
+// velocities 14 walks, 43x39 27), whose lanes then set up a column each step.
+// "block": lane rows of la units, 64 / la of them.
 // The one with the fewer steps, a walk's own set-up counted a sixteenth of
 // a step (an eighth in FP32); a block walk with several pieces per grid row
 // touches cache lines twice and counts half more.  Measured on 128x64 cells,
@@ -107,6 +109,12 @@ inline LaneMap lane_map(int n1, int n2, int mixed)
 //           145 us; the 256x128 C-grid with 2304 velocities in FP64, 2.4 and
 //           3.6 GB: 489 and 695 against 501 and 717 us; running backwards
 //           every other time 491 and 700)
+// A group of a batch goes by its own members' sum, though the other groups'
+// rows pass through the cache between two of its sweeps.  Going by the sum over
+// all groups measured, us a sweep: 134 + 201 MB 84 -> 85, 201 + 201 MB 99.6 ->
+// 102.5, 268 + 403 MB 186 -> 183, 402 + 201 MB 148 -> 145, twice 134 + 201 MB
+// 165 -> 158; the code before this rule (all rows non-temporal) 88, 102, 205,
+// 152 and 176.
 enum { kMemKeep = 0, kMemTurn = 1, kMemStream = 2 };
 inline int sweep_memory(size_t bytes)
 {
@@ -207,7 +215,7 @@ struct DevSolve {
     // second-order scheme (order 2 only; null otherwise)
     const double *rf;        // [nc][4][2] face midpoint minus the cell's centroid
     const double *rn;        // [nc][4][2] face midpoint minus the neighbour's centroid (interior faces)
-    void *G;                 // [nc][nv][4] limited slopes (f1x, f1y, f2x, f2y); adjoint: B (storage type)
+    void *G;                 // [nc] rows of 4 nv: limited slopes, adjoint: B (storage type; order in a row: Slopes)
     void *corr;              // [nc][nv][2] held flux correction c; adjoint: held term E (storage type)
     void *psi;               // [nc][nv][2] limiter factors of the frozen f (storage type)
     double *dF;              // [nw] held wall-flux correction
@@ -219,7 +227,7 @@ struct DevSolve {
     double *mx[2];           // [nc][4] red-black iterates
 };
 
-// dynamic LDS of the patch kernels (layouts in dvm_kernels.hip); a thread of
+// dynamic LDS of the patch kernels (layouts in dvm_walk.h and dvm_kernels.hip); a thread of
 // the adjoint's parks kWalkSums sums there between walks
 constexpr int kWalkSums = 6;
 inline unsigned factor_lds(const LaneMap &m) { return 32u * m.n2p + 16u * m.n1p; }

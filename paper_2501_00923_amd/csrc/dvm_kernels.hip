@@ -5,11 +5,12 @@
 // and a wave64 reading consecutive velocities streams whole cache lines.
 // Cells are numbered on the device in sweep order (see dvm_internal.h).
 //
-// Sweeps: one workgroup per patch of up to kPatchCells cells, one wave per
-// cell.  A wave walks its cell's velocities 64 or 128 at a time (Walk below)
-// and reads the neighbour rows it needs from L2 (the neighbouring patch ran
-// shortly before or runs alongside on the same XCD; a neighbour in the same
-// patch is in L1), far-field and wall rows from tables.  The FP64 velocity
+// Sweeps: a workgroup takes a patch of up to kPatchCells cells, one wave per
+// cell, or, where rows are summed in parts (sweep_parts), one or two of its
+// cells, one wave per part.  A wave walks its cell's velocities 64 or 128 at a
+// time (dvm_walk.h) and reads the neighbour rows it needs from L2 (the
+// neighbouring patch ran shortly before or runs alongside on the same XCD; a
+// neighbour in the same patch is in L1), far-field and wall rows from tables.  The FP64 velocity
 // moments of the new row are summed in registers and reduced across the wave
 // in a fixed order, so the next sweep finds W^{n+1} ready and f is streamed
 // once per sweep.  The Maxwellian is evaluated as rho/(2 pi theta) * ex[a] *
@@ -17,8 +18,8 @@
 // i.e. n1 + n2 exponentials per cell instead of n1*n2.
 //
 // What bounds them, 256x128 C-grid with 2304 velocities: memory (FP64 primal
-// 488 us, adjoint 694 us: 4.9 and 5.2 TB/s of the rows' own bytes, against
-// 5.1-5.4 for a plain copy of that size; FP32 256 and 355 us).  States that
+// 469 us, adjoint 653 us: 5.2 and 5.5 TB/s of the rows' own bytes, against
+// 5.75 and 5.82 for a stream of that mix; FP32 257 and 356 us).  States that
 // fit the MALL are bound by instruction issue and, below some ten thousand
 // cells, by the latency of a patch's prologue and steps (64x32 cells with 256
 // velocities: 7.2 and 8.2 us; 9.7 and 12.8 us with a walk in storage order,
@@ -678,7 +679,8 @@ __device__ __forceinline__ void adjoint_unit(const DevSolve &d, int par, const S
 // adjoint sweep's epilogue, so the next sweep sees what a sweep that had
 // produced this phi would have left.  CORR: phi is first corrected in place
 // by the collision invariant -(z . Psi, z_3) of the adjoint prediction
-// (z [nc][4]), and the moments are those of the result.
+// (z [nc][4]), and the moments are those of the result; its rows bypass the
+// memory-side cache whatever the sweeps' rule (sweep_memory).
 template <typename T, int V, bool CORR>
 __device__ __forceinline__ void adjoint_moments_cell(const DevSolve &d, int par, const double *z, int c, bool act, int w,
                                                      int lane)

@@ -24,8 +24,7 @@
 // The residual's moments vanish at the discrete solution, so the prediction
 // leaves the solution of the plain iteration unchanged.  The work is small
 // next to the sweeps (a few passes over the velocity grid per cell, every K
-// sweeps), so it favours plain, fixed-order FP64 code: one velocity per
-// lane, moment sums reduced across the wave in a fixed order.
+// sweeps), so it favours plain FP64 code, all sums in a fixed order.
 
 #include <math.h>
 

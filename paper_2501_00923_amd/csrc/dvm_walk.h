@@ -24,9 +24,10 @@ __device__ __forceinline__ bool pair_velocities(int n1)
 // whole walk down its rows (LaneMap of dvm_internal.h), so every factor of
 // v1 is a per-lane constant of the inner loop, and the sums over the rows
 // carry only the v2 factors (from LDS); the v1 factors join once per walk.
-// Compared with a column that changes every step this takes the vector
-// instructions per velocity from 100 to 72 (FP64 primal), 105 to 70 (FP32
-// primal), 168 to 88 (FP64 adjoint) and 142 to 85 (FP32 adjoint).
+// Vector instructions per 64 velocities, 256x128 cells with 48x48 velocities,
+// set-up and sums included, a column that changes every step against this: FP64
+// primal 107 -> 89, adjoint 165 -> 95, FP32 primal 108 -> 77, adjoint 130 -> 89.
+// (Where a walk has one step only, lane_map, nothing is shared between steps.)
 // Lanes outside the grid run along on padded table entries (v = 1, weight 0)
 // and buffer accesses that the row's range check drops.
 // ---------------------------------------------------------------------------
@@ -104,8 +105,9 @@ __device__ __forceinline__ void row_store(__amdgpu_buffer_rsrc_t r, int off, con
 }
 
 // Reciprocal: hardware estimate and Newton steps, two in FP64 (error about
-// one ulp) and one in FP32, where it is the correctly rounded 1 / x (checked
-// for every mantissa) at a third of the division's instructions.
+// one ulp) and one in FP32, where a run over every mantissa of one binade gave
+// the correctly rounded 1 / x, at a third of the division's instructions.  (x
+// and 1 / x normal and finite; 0 and infinity give NaN.)
 __device__ __forceinline__ double recip(double x)
 {
     double r = __builtin_amdgcn_rcp(x);

@@ -362,11 +362,16 @@ __device__ void centroid_rel(const Dual (&X)[4], const Dual (&Y)[4], Dual &cx, D
 // is phi_c - phi_down: the neighbour's phi, 0 at the far field,
 // (Phi_l - m_J, 0) at the wall (Phi_l: the wall multiplier of this phi).
 // The per-face and per-cell sums are mapped to c's four corners.
+// The cell's number is uniform over its wave, so its faces and its neighbours'
+// rows are held in scalar registers (256 -> 218 vector registers, two waves a
+// SIMD instead of one): with the slopes, 256x128 cells with 48x48 velocities in
+// FP64 6780 -> 4270 us, 128x64 with 32x32 831 -> 566 (6735 and 815 with slope
+// rows that held both components together).
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_mesh_sens_cell_so(DevSolve d, int fpar, int ppar)
 {
     using T2 = typename Vec2<T>::type;
-    const int w = (int)(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+    const int w = uni((int)(threadIdx.x / kWave)), lane = threadIdx.x % kWave;
     const int c = blockIdx.x * (kBlock / kWave) + w;
     if (c >= d.nc) return;                      // whole waves; the kernel has no block barrier
     const int nv = d.nv, n1 = d.n1, obj = d.objective;

@@ -43,11 +43,11 @@ constexpr double kMacroCFL = 1000.0;
 //   r_c = sum_q O_cq - sum_q O_nq' + (boundary inflow) + V/tau (W - m(P'))
 // needs every row once, by its own cell (k_macro_flux), and a sum over faces
 // (k_macro_resid): f is read once and no neighbour row with it, but across the
-// cuts of the mesh (cut_face).  The
-// collision part takes the moments of f from the sweep (W) and those of the
-// equilibrium from 1-D sums.  k_macro_flux leaves O_cq [face][moment] in the
-// face-block table mO (the blocks come after it) and the rest of r_c in mr.
-// 256x128 cells with 64x64 velocities in FP64 516 us (725 with each cell
+// cuts of the mesh (cut_face).  The collision part takes the moments of f from
+// the sweep (W) and those of the equilibrium from 1-D sums.  k_macro_flux
+// leaves O_cq [face][moment] in the face-block table mO (the blocks come after
+// it) and the rest of r_c in mr.
+// 256x128 cells with 64x64 velocities in FP64 454 us (725 with each cell
 // reading its upwind neighbours' rows), 128x64 with 32x32 in FP32 35 us (64).
 // ---------------------------------------------------------------------------
 // Faces whose two sides take their vectors from nodes stored apart: the

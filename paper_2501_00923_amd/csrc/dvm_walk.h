@@ -26,7 +26,8 @@ __device__ __forceinline__ bool pair_velocities(int n1)
 // carry only the v2 factors (from LDS); the v1 factors join once per walk.
 // Vector instructions per 64 velocities, 256x128 cells with 48x48 velocities,
 // set-up and sums included, a column that changes every step against this: FP64
-// primal 107 -> 89, adjoint 165 -> 95, FP32 primal 108 -> 77, adjoint 130 -> 89.
+// primal 107 -> 89, FP32 primal 108 -> 77, adjoint with the residual's sums 165
+// -> 114 and 130 -> 101, without (all but a call's last sweep) 95 and 89.
 // (Where a walk has one step only, lane_map, nothing is shared between steps.)
 // Lanes outside the grid run along on padded table entries (v = 1, weight 0)
 // and buffer accesses that the row's range check drops.
